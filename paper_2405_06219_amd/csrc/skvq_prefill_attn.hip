@@ -42,6 +42,7 @@ constexpr int kThreads = 2 * kQBlock;
 constexpr int kKTile = 64;      // keys per tile
 constexpr int kKStride = 136;   // halves per K row in LDS (272 B: 16-byte aligned, rows on different banks)
 constexpr int kVStride = 72;    // halves per V^T row in LDS (144 B: 16-byte aligned, rows on different banks)
+constexpr int kXcds = 8;        // workgroup i of a grid runs on chiplet i % 8
 constexpr float kLog2e = 1.4426950408889634f;
 // The running reference sits kBias below the largest score it was set from (that key's weight is
 // 2^kBias) and moves when a score exceeds it by more than kSlack: weights stay below 2^15, which fp16
@@ -70,14 +71,19 @@ __global__ __launch_bounds__(kThreads, 2) void prefill_attn_kernel(const __half 
                                                               const __half *__restrict__ k,
                                                               const __half *__restrict__ v, float *__restrict__ out_f32,
                                                               __half *__restrict__ out_f16, int T, int Hq, int Hk,
-                                                              float sm_scale) {
+                                                              int n_heads, int first_block, float sm_scale) {
   __shared__ __align__(16) Smem sm;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int col = lane & 31, h = lane >> 5;
+  // grid (heads, query blocks, further heads): workgroups start in the order of their length over all
+  // heads, see launch_prefill_attention
+  const int x = blockIdx.x + gridDim.x * blockIdx.z;
+  if (x >= n_heads) return;  // (the last slice of heads may be ragged)
+  const int flat = n_heads % kXcds == 0 ? (x % kXcds) * (n_heads / kXcds) + x / kXcds : x;
   const int n_qblocks = (T + kQBlock - 1) / kQBlock;
-  const int qb = n_qblocks - 1 - (int)blockIdx.x;  // the longest blocks start first
-  const int hq = blockIdx.y, b = blockIdx.z, hk = hq / (Hq / Hk);
+  const int qb = n_qblocks - 1 - (first_block + (int)blockIdx.y);  // the longest blocks start first
+  const int b = flat / Hq, hq = flat % Hq, hk = hq / (Hq / Hk);
   const __half *qh = q + ((size_t)b * Hq + hq) * (size_t)T * kD;
   const __half *kh = k + ((size_t)b * Hk + hk) * (size_t)T * kD;
   const __half *vh = v + ((size_t)b * Hk + hk) * (size_t)T * kD;
@@ -330,13 +336,32 @@ __global__ __launch_bounds__(kThreads, 2) void prefill_attn_kernel(const __half 
 
 }  // namespace
 
+// A workgroup's length is the number of tiles its queries see: block j of a head takes 4 (j + 1)
+// trips of the tile loop, and a compute unit holds one workgroup.  The grid therefore runs over the
+// heads first and over the query blocks, longest first, second: all workgroups start in descending
+// order of length (the one-tile blocks fill the end) and every chiplet, which is dealt every eighth
+// workgroup, gets the same lengths.  With the blocks of a head as the fast index instead, each head
+// ended in short blocks followed by the next head's long ones, chiplet 0 got the longest block of
+// every eight, and the compute units were busy 77 % of the time (now 97 %: 13.2 -> 11.1 ms for 32 q / 8 kv heads x 32k
+// tokens, 168 -> 121 us with the quantizer for 2 x 32 heads x 1913 tokens).
+// When the heads divide by eight, chiplet c takes heads c n/8 .. (c + 1) n/8 - 1, so that the query
+// heads of a kv head share one L2.
 hipError_t launch_prefill_attention(const Layout &L, const __half *q, const __half *k, const __half *v,
                                     float *out_f32, __half *out_f16, long long T, hipStream_t s) {
-  if (T <= 0 || T > 0x3fffffffll || L.Hq > 65535 || L.B > 65535) return hipErrorInvalidValue;
+  if (T <= 0 || T > 0x3fffffffll || L.Hq > 65535 || L.B > 65535 || (long long)L.B * L.Hq > 0x7fffffffll)
+    return hipErrorInvalidValue;
   const int n_qblocks = (int)((T + kQBlock - 1) / kQBlock);
-  hipLaunchKernelGGL(prefill_attn_kernel, dim3(n_qblocks, L.Hq, L.B), dim3(kThreads), 0, s, q, k, v, out_f32, out_f16,
-                     (int)T, L.Hq, L.Hk, L.sm_scale);
-  return hipGetLastError();
+  const int n_heads = L.B * L.Hq;
+  const int heads_x = n_heads < (1 << 22) ? n_heads : 1 << 22, heads_z = (n_heads + heads_x - 1) / heads_x;
+  constexpr int kMaxGridY = 65535;
+  for (int first = 0; first < n_qblocks; first += kMaxGridY) {
+    const int blocks_y = n_qblocks - first < kMaxGridY ? n_qblocks - first : kMaxGridY;
+    hipLaunchKernelGGL(prefill_attn_kernel, dim3(heads_x, blocks_y, heads_z), dim3(kThreads), 0, s, q, k, v, out_f32,
+                       out_f16, (int)T, L.Hq, L.Hk, n_heads, first, L.sm_scale);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
 }
 
 }  // namespace skvq

@@ -1,0 +1,38 @@
+"""Edges of the kernels' dispatch rules and tiles, against the oracle (through the C ABI)."""
+import numpy as np
+import pytest
+import torch
+
+import parity_util as P
+
+pytestmark = pytest.mark.gpu
+
+D = 128
+
+
+def prefill_inputs(B, Hq, Hk, T, seed):
+    rng = np.random.default_rng(seed)
+    q = rng.standard_normal((B, Hq, T, D)).astype(np.float16)
+    k = (rng.standard_normal((B, Hk, T, D)) * 10 ** rng.uniform(-1.0, 1.0, (1, Hk, 1, D))).astype(np.float16)
+    v = (rng.standard_normal((B, Hk, T, D)) * 10 ** rng.uniform(-1.0, 1.0, (1, Hk, 1, D))).astype(np.float16)
+    return q, k, v
+
+
+# heads that divide by the eight chiplets (each takes neighbouring heads) and heads that do not, at lengths
+# on either side of a query block and of a key tile
+@pytest.mark.parametrize("B,Hq,Hk,T", [(1, 8, 2, 513), (1, 16, 16, 255), (2, 12, 3, 257), (1, 7, 7, 256), (1, 1, 1, 65),
+                                       (3, 8, 1, 63)])
+def test_prefill_attention_grid(B, Hq, Hk, T):
+    from oracle import skvq_oracle as O
+    from paper_2405_06219_amd import binding as Bd
+    print("case", B, Hq, Hk, T, flush=True)
+    q, k, v = prefill_inputs(B, Hq, Hk, T, 4100 + T)
+    perm = np.tile(np.arange(D, dtype=np.int32), (Hk, 1))
+    one = np.ones((Hk, 1), np.float32)
+    ref = O.OracleCache(B, Hq, Hk, 128, 1.5, 8, 8, perm, perm, one, one).prefill_attention(q, k, v)
+    gpu = Bd.SkvqCache(B, Hq, Hk, 128, 1.5, 8, 8, perm, perm, one, one)
+    out = gpu.skvq_prefill_attention(*(torch.from_numpy(x).to("cuda:0") for x in (q, k, v)))
+    torch.cuda.synchronize()
+    # fp32 accumulation of fp16 products and weights of ~22 bits: 1e-4 was the largest seen on such inputs
+    # (|v| up to 40); the library's bound for every attention output is P.TOL = 2e-3
+    assert np.abs(out.cpu().numpy() - ref).max() <= P.TOL
