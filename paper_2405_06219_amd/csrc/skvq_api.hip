@@ -553,10 +553,15 @@ int skvq_append_decode_attention(skvq_cache *c, const void *k_new, const void *v
   if (nq > c->L.Tcap) return SKVQ_ERR_CAPACITY;
   hipStream_t s = (hipStream_t)stream;
   const int n_splits = choose_splits(c, nq);
-  // One launch pays when few workgroups do the append (one per kv head, of n_splits): with one or
-  // two chunks per kv head every (other) workgroup would wait for its own append, which costs more
-  // than the separate launch (measured at 16 sequences x 32 heads x 32k tokens: 240 against 236 us).
-  if (append_fusable(c->L, T + 1, keep) && n_splits >= kMinSplitsForOneLaunch) {
+  // One launch pays when few workgroups do the append (one per kv head, of n_splits), and when every
+  // workgroup of the launch has a compute unit to itself, however many of them append: the append then
+  // lengthens the call by less than the launch it replaces (one launch against two, us per call: 1 x 4
+  // heads x 800 tokens 11.0 / 12.9, 8 x 32 x 4000 23.4 / 24.9, 12 x 8 x 20000 36.6 / 39.3, 8 x 32 x 32k
+  // 106.0 / 107.5).  Past that, a workgroup that starts late waits for its own append with nothing
+  // beside it: 16 x 32 x 32k tokens 240 / 236.
+  const long long workgroups = (long long)c->L.B * c->L.Hk * (n_splits > 1 ? n_splits : 1);
+  const bool few_append = n_splits >= kMinSplitsForOneLaunch || workgroups <= c->n_cus;
+  if (append_fusable(c->L, T + 1, keep) && few_append) {
     hipError_t e = launch_decode(c->L, (const __half *)q, (float *)out_f32, (__half *)out_f16, T + 1, c->n_kept,
                                  n_splits, 1, s, (const __half *)k_new, (const __half *)v_new);
     if (e != hipSuccess) return fail_hip(c, e, "skvq_append_decode_attention launch");

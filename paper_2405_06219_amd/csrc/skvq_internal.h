@@ -135,7 +135,7 @@ hipError_t launch_decode_mfma(const Layout &L, const __half *q, long long T, lon
 // workgroup per chunk (at most four query heads per kv head), and the token that leaves the
 // window, if any, is packed rather than copied to a sink row (a sink row has other readers in
 // the same launch).
-constexpr int kMinSplitsForOneLaunch = 4;  // chunks per kv head from which the one-launch step is used
+constexpr int kMinSplitsForOneLaunch = 4;  // chunks per kv head from which the one-launch step is used whatever their number
 inline bool append_fusable(const Layout &L, long long T_after, bool leaving_token_is_kept) {
   const long long T = T_after - 1;  // tokens cached before
   return decode_passes(L.R) == 1 && !(T >= L.W && leaving_token_is_kept);

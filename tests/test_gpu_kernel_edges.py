@@ -36,3 +36,22 @@ def test_prefill_attention_grid(B, Hq, Hk, T):
     # fp32 accumulation of fp16 products and weights of ~22 bits: 1e-4 was the largest seen on such inputs
     # (|v| up to 40); the library's bound for every attention output is P.TOL = 2e-3
     assert np.abs(out.cpu().numpy() - ref).max() <= P.TOL
+
+
+# steps that append inside the attention launch with one, two and three chunks per kv head (few workgroups),
+# from an empty cache, across a V block's and a tile's edge, and the two-launch form beside it (300 heads)
+@pytest.mark.parametrize("batch,heads,context,splits", [(1, 2, 0, 0), (1, 3, 190, 0), (2, 2, 700, 2), (1, 2, 900, 3),
+                                                        (75, 4, 140, 0)])
+def test_step_of_few_workgroups(batch, heads, context, splits):
+    from paper_2405_06219_amd import synth
+    print("case", batch, heads, context, splits, flush=True)
+    w = synth.Workload("few", batch, heads, heads, context, 2.0 if heads == 3 else 1.5, group_size=64, window=16, seed=9)
+    pair, k, v, q = P.make_pair(w, extra_tokens=36)
+    if context:
+        pair.prefill(k, v)
+    if splits:
+        pair.gpu.skvq_set_num_splits(splits)
+    for s in range(4 if batch > 2 else 36):
+        out, ref = pair.append_decode_both(*synth.make_new_token(w, s), q)
+        assert np.abs(out - ref).max() <= P.TOL, s
+    pair.assert_buffers_equal()
