@@ -341,6 +341,53 @@ struct TileData {
   uint2_t vt0, vt1;                  // 3-bit units: their 8 bytes of top bits
 };
 
+// The workgroup builds the table of 3-level operands while its first loads are in flight (one barrier
+// inside; the table is complete after the caller's next one).
+__device__ __forceinline__ void build_ternary_table(uint2_t (*lut4)[81], uint4_t *lut, const int tid) {
+  // While the loads are in flight the workgroup builds the table: entry f (a base-3 number of
+  // eight digits, digit i = code of token i) is the operand itself, register m = codes of
+  // tokens 2m (low half) and 2m+1 (high half) as fp16 subnormals c * 2^(8-24).
+  if (tid < 162) {
+    const int half = tid >= 81, x = half ? tid - 81 : tid;
+    const unsigned d0 = x % 3, d1 = (x / 3) % 3, d2 = (x / 9) % 3, d3 = x / 27;
+    lut4[half][x] = uint2_t{(d0 << 8) | (d1 << 24), (d2 << 8) | (d3 << 24)};
+  }
+  __syncthreads();
+  // Thread t < 486 keeps the low half of its entries (digits t % 81) and walks through every
+  // sixth high half from t / 81 on: one read per entry instead of two, all reads first, then
+  // all writes (one LDS latency, not one per entry).
+  constexpr int kWalk = 6, kSteps = (81 + kWalk - 1) / kWalk;
+  const unsigned first_hi = tid / 81u, lo = tid - 81u * first_hi;
+  if (first_hi < kWalk) {
+    const uint2_t lo4 = lut4[0][lo];
+    uint2_t hi4[kSteps];
+#pragma unroll
+    for (int i = 0; i < kSteps; ++i) hi4[i] = lut4[1][min(first_hi + kWalk * i, 80u)];
+#pragma unroll
+    for (int i = 0; i < kSteps; ++i) {
+      const unsigned hi = first_hi + kWalk * i;
+      if (hi < 81u) lut[81u * hi + lo] = uint4_t{lo4.x, lo4.y, hi4[i].x, hi4[i].y};
+    }
+  }
+}
+
+// The eight fields of a 3-level unit as byte offsets into the table (field * 16), two operations per
+// field.  sh: the unit's first byte within `raw`.
+__device__ __forceinline__ void ternary_fields(const Unit16 &raw, const int sh, unsigned (&f)[8]) {
+  const unsigned u0 = __builtin_amdgcn_alignbyte(raw.y, raw.x, sh);
+  const unsigned u1 = __builtin_amdgcn_alignbyte(raw.z, raw.y, sh);
+  const unsigned u2 = __builtin_amdgcn_alignbyte(raw.w, raw.z, sh);
+  const unsigned u3 = raw.w >> (8 * sh);
+  f[0] = (u0 << 4) & 0x1fff0u;
+  f[1] = (u0 >> 9) & 0x1fff0u;
+  f[2] = __builtin_amdgcn_alignbit(u1, u0, 22) & 0x1fff0u;
+  f[3] = (u1 >> 3) & 0x1fff0u;
+  f[4] = __builtin_amdgcn_alignbit(u2, u1, 16) & 0x1fff0u;
+  f[5] = (u2 << 3) & 0x1fff0u;
+  f[6] = (u2 >> 10) & 0x1fff0u;
+  f[7] = __builtin_amdgcn_alignbit(u3, u2, 23) & 0x1fff0u;
+}
+
 // What one wavefront loads for one slice of 4 fp16 ring tokens.
 struct RingData {
   uint4_t k;      // lane (token = l/16, piece = l%16): 8 channels of the token's key row
@@ -375,10 +422,10 @@ __global__ __launch_bounds__(kThreads, 2) void decode_mfma_kernel(Layout L, cons
                                                                   const __half *__restrict__ knew,
                                                                   const __half *__restrict__ vnew, long long te,
                                                                   ChunkPlan plan, MergeOut mo) {
-  // grid (n_splits, Hk * passes, B): R is the number of query heads one workgroup serves; a kv
-  // head with more than four (or with three) query heads is served by `passes` workgroups per
-  // chunk, each with R of its L.R query heads (the last one possibly with fewer: the missing
-  // heads are computed with a zero query and not stored).
+  // grid (n_splits, Hk * passes, B): R is the number of query heads one workgroup serves; where
+  // decode_wide_kernel does not exist (four groups per head, unequal ones) a kv head with more than
+  // four rows is served by `passes` workgroups per chunk, each with R of its rows (the last one
+  // possibly with fewer: the missing rows are computed with a zero query and not stored).
   //   With n_new > 1 query tokens per sequence (the last n_new cached tokens are theirs) the rows
   // of a kv head are its L.R query heads times the n_new tokens, row x = token x / L.R, head
   // x % L.R; query token j does not see the fp16 tokens after its own.
@@ -578,31 +625,7 @@ __global__ __launch_bounds__(kThreads, 2) void decode_mfma_kernel(Layout L, cons
   Tile buf_a, buf_b, buf_c;
   buf_a = load_tile(min(tile_a, tile_cap));
   if (TERNARY) {
-    // While the loads are in flight the workgroup builds the table: entry f (a base-3 number of
-    // eight digits, digit i = code of token i) is the operand itself, register m = codes of
-    // tokens 2m (low half) and 2m+1 (high half) as fp16 subnormals c * 2^(8-24).
-    if (tid < 162) {
-      const int half = tid >= 81, x = half ? tid - 81 : tid;
-      const unsigned d0 = x % 3, d1 = (x / 3) % 3, d2 = (x / 9) % 3, d3 = x / 27;
-      sm.lut4[half][x] = uint2_t{(d0 << 8) | (d1 << 24), (d2 << 8) | (d3 << 24)};
-    }
-    __syncthreads();
-    // Thread t < 486 keeps the low half of its entries (digits t % 81) and walks through every
-    // sixth high half from t / 81 on: one read per entry instead of two, all reads first, then
-    // all writes (one LDS latency, not one per entry).
-    constexpr int kWalk = 6, kSteps = (81 + kWalk - 1) / kWalk;
-    const unsigned first_hi = tid / 81u, lo = tid - 81u * first_hi;
-    if (first_hi < kWalk) {
-      const uint2_t lo4 = sm.lut4[0][lo];
-      uint2_t hi4[kSteps];
-#pragma unroll
-      for (int i = 0; i < kSteps; ++i) hi4[i] = sm.lut4[1][min(first_hi + kWalk * i, 80u)];
-#pragma unroll
-      for (int i = 0; i < kSteps; ++i) {
-        const unsigned hi = first_hi + kWalk * i;
-        if (hi < 81u) sm.lut[81u * hi + lo] = uint4_t{lo4.x, lo4.y, hi4[i].x, hi4[i].y};
-      }
-    }
+    build_ternary_table(sm.lut4, sm.lut, tid);
   }
   {
     asm volatile("" ::: "memory");
@@ -980,20 +1003,8 @@ __global__ __launch_bounds__(kThreads, 2) void decode_mfma_kernel(Layout L, cons
         for (int n = 0; n < 8; ++n)
           acc[n] = __builtin_amdgcn_mfma_f32_16x16x32_f16(unpack_v4_field(w[n]), pop[n * NACC / 8], acc[n], 0, 0, 0);
       } else if (TERNARY) {
-        const unsigned u0 = __builtin_amdgcn_alignbyte(raw.y, raw.x, unit_sh);
-        const unsigned u1 = __builtin_amdgcn_alignbyte(raw.z, raw.y, unit_sh);
-        const unsigned u2 = __builtin_amdgcn_alignbyte(raw.w, raw.z, unit_sh);
-        const unsigned u3 = raw.w >> (8 * unit_sh);
-        // byte offsets into the table (field * 16), two operations per field
         unsigned f[8];
-        f[0] = (u0 << 4) & 0x1fff0u;
-        f[1] = (u0 >> 9) & 0x1fff0u;
-        f[2] = __builtin_amdgcn_alignbit(u1, u0, 22) & 0x1fff0u;
-        f[3] = (u1 >> 3) & 0x1fff0u;
-        f[4] = __builtin_amdgcn_alignbit(u2, u1, 16) & 0x1fff0u;
-        f[5] = (u2 << 3) & 0x1fff0u;
-        f[6] = (u2 >> 10) & 0x1fff0u;
-        f[7] = __builtin_amdgcn_alignbit(u3, u2, 23) & 0x1fff0u;
+        ternary_fields(raw, unit_sh, f);
         uint4_t aop[8];
 #pragma unroll
         for (int n = 0; n < 8; ++n)
@@ -1159,52 +1170,5 @@ __global__ __launch_bounds__(kThreads, 2) void decode_mfma_kernel(Layout L, cons
 }
 
 }  // namespace
-
-// The launcher of the kernels with KL-level keys and VL-level values.
-template <int KL, int VL>
-hipError_t launch_decode_mfma_fmt(const Layout &L, const __half *q, long long T, long long nq, int n_sink,
-                                  int n_splits, int n_new, const __half *knew, const __half *vnew, long long te,
-                                  MergeOut mo, hipStream_t s) {
-  if (T <= 0 || nq < 0 || nq > SKVQ_MAX_QUANT_TOKENS || T - nq > 0x7fffffff || n_splits < 1 ||
-      n_splits > SKVQ_MAX_SPLITS)
-    return hipErrorInvalidValue;
-  if (n_new < 1 || n_new > SKVQ_MAX_NEW_TOKENS || L.R > 8) return hipErrorInvalidValue;
-  const int n_rows = n_new * L.R;
-  const int passes = decode_passes(n_rows), rk = n_rows == 1 ? 1 : n_rows == 2 ? 2 : 4;
-  if ((knew != nullptr) != (vnew != nullptr) || (knew && (passes != 1 || n_new != 1))) return hipErrorInvalidValue;
-  if (knew && T - 1 >= L.W && (te < 0 || te >= L.Tcap || te != nq - 1)) return hipErrorInvalidValue;
-  if ((long long)L.Hk * passes > 65535) return hipErrorInvalidValue;
-  if (mo.mode != kMergeSeparate && !mo.out_f32) return hipErrorInvalidValue;
-  if (mo.mode == kMergeDirect && n_splits != 1) return hipErrorInvalidValue;
-  const dim3 grid(n_splits, L.Hk * passes, L.B), block(kThreads);
-  const ChunkPlan plan = plan_chunks(L, T, nq, n_sink, n_splits, knew != nullptr);
-#define SKVQ_LAUNCH(RR, MM, GG, UU) \
-  hipLaunchKernelGGL((decode_mfma_kernel<RR, KL, VL, MM, GG, UU>), grid, block, 0, s, L, q, T, nq, n_sink, n_splits, passes, n_new, knew, vnew, te, plan, mo)
-#define SKVQ_LAUNCH_NG(RR, MM)                                                                   \
-  switch (L.NG) {                                                                                \
-    case 1: SKVQ_LAUNCH(RR, MM, 1, false); break;                                                \
-    case 2: if (L.uneq) SKVQ_LAUNCH(RR, MM, 2, true); else SKVQ_LAUNCH(RR, MM, 2, false); break; \
-    case 4: if (L.uneq) SKVQ_LAUNCH(RR, MM, 4, true); else SKVQ_LAUNCH(RR, MM, 4, false); break; \
-    default: return hipErrorInvalidValue;                                                        \
-  }
-#define SKVQ_LAUNCH_META(RR)                                                \
-  switch (L.meta_fmt) {                                                     \
-    case SKVQ_META_F32: SKVQ_LAUNCH_NG(RR, SKVQ_META_F32) break;            \
-    case SKVQ_META_F16: SKVQ_LAUNCH_NG(RR, SKVQ_META_F16) break;            \
-    case SKVQ_META_FP8_E4M3: SKVQ_LAUNCH_NG(RR, SKVQ_META_FP8_E4M3) break;  \
-    default: return hipErrorInvalidValue;                                   \
-  }
-  if (L.k_levels != KL || L.v_levels != VL) return hipErrorInvalidValue;
-  switch (rk) {
-    case 1: SKVQ_LAUNCH_META(1) break;
-    case 2: SKVQ_LAUNCH_META(2) break;
-    case 4: SKVQ_LAUNCH_META(4) break;
-    default: return hipErrorInvalidValue;
-  }
-#undef SKVQ_LAUNCH_META
-#undef SKVQ_LAUNCH_NG
-#undef SKVQ_LAUNCH
-  return hipGetLastError();
-}
 
 }  // namespace skvq

@@ -123,22 +123,29 @@ hipError_t launch_decode(const Layout &L, const __half *q, float *out_f32, __hal
 
 // Matrix-core chunk kernel (skvq_decode_mfma.hip): packed chunks and the fp16 tokens (n_sink sink
 // rows, then the window's T - nq - n_sink ring tokens); writes partials 0..n_splits-1 (n_splits
-// >= 1 even when nothing is packed yet).  A workgroup serves 1, 2 or 4 query heads of a kv head;
-// kv heads with 5..8 query heads are read by two workgroups per chunk.
-// (n_rows = query heads per kv head x query tokens)
-inline int decode_passes(int n_rows) { return n_rows > 4 ? (n_rows + 3) / 4 : 1; }
+// >= 1 even when nothing is packed yet).
+// A kv head's rows (query heads x query tokens) are served four to a workgroup, or sixteen by the kernel
+// for more than four rows, which exists for one and two equal groups per head (with four groups or
+// unequal ones its factors and operands do not fit the registers: it spills in the tile loop and is no
+// faster than the workgroups of four rows that it would replace).
+constexpr int kWideRows = 16;
+inline int rows_per_workgroup(const Layout &L, int n_rows) { return n_rows > 4 && L.NG <= 2 && !L.uneq ? kWideRows : 4; }
+inline int decode_passes(const Layout &L, int n_rows) {  // workgroups per chunk
+  const int rows = rows_per_workgroup(L, n_rows);
+  return (n_rows + rows - 1) / rows;
+}
 // te: with knew / vnew, the packed row of the token that leaves the window.
 hipError_t launch_decode_mfma(const Layout &L, const __half *q, long long T, long long nq, int n_sink,
                               int n_splits, int n_new, const __half *knew, const __half *vnew, long long te,
                               MergeOut mo, hipStream_t s);
 // Whether the decode of T_after tokens (one query token) may append the newest token itself: one
-// workgroup per chunk (at most four query heads per kv head), and the token that leaves the
+// workgroup per chunk, and the token that leaves the
 // window, if any, is packed rather than copied to a sink row (a sink row has other readers in
 // the same launch).
 constexpr int kMinSplitsForOneLaunch = 4;  // chunks per kv head from which the one-launch step is used whatever their number
 inline bool append_fusable(const Layout &L, long long T_after, bool leaving_token_is_kept) {
   const long long T = T_after - 1;  // tokens cached before
-  return decode_passes(L.R) == 1 && !(T >= L.W && leaving_token_is_kept);
+  return decode_passes(L, L.R) == 1 && !(T >= L.W && leaving_token_is_kept);
 }
 constexpr int kMfmaWavesPerGroup = 8;  // wavefronts per workgroup of the matrix-core kernel
 

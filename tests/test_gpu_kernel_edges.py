@@ -55,3 +55,46 @@ def test_step_of_few_workgroups(batch, heads, context, splits):
         out, ref = pair.append_decode_both(*synth.make_new_token(w, s), q)
         assert np.abs(out - ref).max() <= P.TOL, s
     pair.assert_buffers_equal()
+
+
+# more than four rows per kv head in one workgroup: 5 .. 16 and 64 rows, every code format with one and two
+# groups, packed regions of none, one and a few tokens around a tile's and a V block's edge, sinks, one and
+# more chunks
+WIDE_CASES = [
+    # q heads, kv heads, query tokens, context, batch, K bits, V bits, group, meta, sinks, window, chunks
+    (5, 1, 1, 16 + 1, 1, 2.0, 1.5, 128, "f32", 0, 16, 0),
+    (8, 1, 2, 16 + 63, 2, 2.0, 1.5, 128, "e4m3", 0, 16, 0),
+    (6, 2, 5, 16 + 64, 1, 2.0, 1.5, 64, "f32", 0, 16, 1),
+    (8, 2, 2, 16 + 65, 1, 2.0, 2.0, 128, "f16", 0, 16, 0),
+    (8, 2, 4, 700, 1, 2.0, 2.0, 64, "e4m3", 5, 32, 3),
+    (8, 1, 8, 1100, 1, 2.0, 4.0, 128, "e4m3", 0, 128, 0),
+    (4, 1, 4, 33 + 95, 3, 2.0, 4.0, 64, "f16", 0, 33, 0),
+    (7, 1, 2, 33 + 97, 1, 3.0, 3.0, 128, "f32", 1, 33, 0),
+    (6, 1, 2, 900, 1, 3.0, 3.0, 64, "e4m3", 0, 128, 2),
+    (8, 1, 1, 800, 1, 4.0, 1.5, 128, "f16", 0, 128, 4),
+    (8, 4, 3, 600, 1, 4.0, 1.5, 64, "f32", 3, 128, 0),
+    (5, 1, 3, 520, 1, 4.0, 2.0, 128, "f32", 0, 64, 0),
+    (8, 2, 4, 2000, 1, 4.0, 4.0, 64, "e4m3", 5, 128, 5),
+    (5, 1, 2, 12, 1, 4.0, 4.0, 128, "f32", 0, 16, 0),   # nothing packed
+]
+
+
+@pytest.mark.parametrize("case", WIDE_CASES, ids=lambda c: "-".join(map(str, c)))
+def test_many_rows_per_kv_head(case):
+    from paper_2405_06219_amd import synth
+    print("case", case, flush=True)
+    hq, hk, n_new, context, batch, k_bits, v_bits, group, meta, sinks, window, splits = case
+    w = synth.Workload("rows", batch, hq, hk, context, v_bits, group_size=group, window=window, k_bits=k_bits, seed=31)
+    pair, k, v, q1 = P.make_pair(w, extra_tokens=n_new + 6, n_sink=sinks, meta=meta, max_new_tokens=n_new)
+    pair.prefill(k, v)
+    if splits:
+        pair.gpu.skvq_set_num_splits(splits)
+    for s in range(n_new):
+        pair.append(*synth.make_new_token(w, s))
+    q = np.random.default_rng(context).standard_normal((batch, n_new, hq, D)).astype(np.float16)
+    out = pair.gpu.skvq_decode_attention_multi(torch.from_numpy(q).to(pair.device)).cpu().numpy()
+    assert np.abs(out - pair.ref.decode_multi(q)).max() <= P.TOL
+    for s in range(4):   # with more than four query heads per kv head: the step's append inside the launch
+        out, ref = pair.append_decode_both(*synth.make_new_token(w, 50 + s), q1)
+        assert np.abs(out - ref).max() <= P.TOL, s
+    pair.assert_buffers_equal()
