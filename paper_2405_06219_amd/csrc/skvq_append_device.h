@@ -124,18 +124,6 @@ constexpr unsigned kKsig0 = 0x58643120u, kKsig1 = 0xefdbca97u;
 __device__ __forceinline__ int ksig(int d, int e) { return ((d ? kKsig1 : kKsig0) >> (4 * e)) & 15; }
 __device__ __forceinline__ int vtau(int nn, int m) { return m < 3 ? (nn & 1) + 6 * (nn >> 1) + 2 * m : 12 + nn; }
 
-// Sixteen top bits of one key dword (position e at bit e) -> their places in the plane dword
-// (d = 0: the even key dword of the pair, d = 1: the odd one).
-__device__ __forceinline__ unsigned place_key_top_bits(unsigned y, int d) {
-  const unsigned x = (y & 0xffu) | ((y & 0xff00u) << 8);  // e = 0..7 at bits 0..7, e = 8..15 at bits 16..23
-  // d = 0: positions e -> {0,2,1,3,4,6,8,5}
-  const unsigned a = (x & 0x00190019u) | ((x & 0x00220022u) << 1) | ((x & 0x00040004u) >> 1) |
-                     ((x & 0x00400040u) << 2) | ((x & 0x00800080u) >> 2);
-  // d = 1: positions e -> {7,9,10,12,11,13,15,14}
-  const unsigned b = ((x & 0x00910091u) << 7) | ((x & 0x00260026u) << 8) | ((x & 0x00480048u) << 9);
-  return d ? b : a;
-}
-
 // 3-bit K row from the append kernel's lanes (lane l: positions 2l, 2l+1): the 2-bit plane as
 // store_k_row, then the top-bit plane (16 lanes form a dword).
 __device__ __forceinline__ void store_k_row3(uint8_t *row, int lane, unsigned c0, unsigned c1) {

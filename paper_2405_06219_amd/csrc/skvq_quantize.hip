@@ -26,121 +26,149 @@ namespace {
 // positions 16n .. 16n+15 of token i: it gathers them through the permutation, reduces
 // min/max with the other lanes of its group, and encodes them (Eq. 2).  Its sixteen key codes
 // are dword n of the token's packed row, so a wavefront stores 256 contiguous bytes.  Its
-// sixteen value codes are exactly the codes (n, i) of units j = 0..15, which a second set of
-// lanes (j = lane % 16, two fields each) collects from LDS to build the units.
+// sixteen value codes are exactly the codes (n, i) of units j = 0..15: they go to LDS a byte each,
+// the codes of a field's eight tokens side by side, and a second set of lanes (j = lane % 16, two
+// fields each) reads its sixteen codes at once and sums them into bit fields with byte-wise dot
+// products.
+//
+// Bound by HBM in the plain 2-bit / 3-level configuration, by vector instructions in the others
+// (3-bit codes in two unequal groups with FP8 pairs, 2 x 32 heads x 20011 tokens: 222 -> 163 us, 900 -> 469
+// vector instructions per wavefront of 8 tokens, with the byte fields, the group by group minima, the
+// fp16 minima and differences and the one-instruction FP8 pairs).
 // ---------------------------------------------------------------------------------------
 constexpr int kRowStride = 136;  // halves per parked row: 272 B keeps 16-byte alignment and
                                  // puts the same channel of the 8 rows in 8 different banks
 
-// The value of another lane of the same row of 16, chosen by a DPP control word.
+// Minimum / maximum of three finite fp16 numbers as one instruction (fminf / fmaxf first re-canonicalize
+// every operand, one more instruction each, for the sake of signalling NaNs that cannot occur here).
+__device__ __forceinline__ _Float16 min3_half(_Float16 a, _Float16 b, _Float16 c) {
+  _Float16 r;
+  asm("v_min3_f16 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "v"(c));
+  return r;
+}
+__device__ __forceinline__ _Float16 max3_half(_Float16 a, _Float16 b, _Float16 c) {
+  _Float16 r;
+  asm("v_max3_f16 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "v"(c));
+  return r;
+}
+
+// A group's {minimum, -maximum} as two fp16 numbers: one minimum takes both further.
+typedef _Float16 half2_t __attribute__((ext_vector_type(2)));
+// With another lane of the same row of 16, chosen by a DPP control word.  (The compiler does not see a
+// vector instruction in the assembly: the wait that a DPP read of its result wants is part of it.)
 template <int CTRL>
-__device__ __forceinline__ float lane_move(float v) {
-  return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), CTRL, 0xF, 0xF, true));
+__device__ __forceinline__ unsigned min_with_lane(unsigned v) {
+  unsigned r;
+  const unsigned other = (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, 0xF, 0xF, true);
+  asm("v_pk_min_f16 %0, %1, %2\n\ts_nop 1" : "=v"(r) : "v"(v), "v"(other));
+  return r;
+}
+// Over the lanes of a group of 2, 4 or 8 neighbours: lane ^ 1, lane ^ 2, then the mirror image within
+// the eight (both quads hold their own result by then); data-parallel moves.
+__device__ __forceinline__ unsigned min_of_neighbours(unsigned v, int lanes) {
+  if (lanes > 1) v = min_with_lane<0xB1>(v);   // quad_perm [1, 0, 3, 2]
+  if (lanes > 2) v = min_with_lane<0x4E>(v);   // quad_perm [2, 3, 0, 1]
+  if (lanes > 4) v = min_with_lane<0x141>(v);  // row_half_mirror
+  return v;
 }
 
-// Minimum / maximum of finite numbers as single instructions (fminf / fmaxf first re-canonicalize every
-// operand, one more instruction each, for the sake of signalling NaNs that cannot occur here).
-__device__ __forceinline__ float min3_raw(float a, float b, float c) {
-  float r;
-  asm("v_min3_f32 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "v"(c));
-  return r;
-}
-__device__ __forceinline__ float max3_raw(float a, float b, float c) {
-  float r;
-  asm("v_max3_f32 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "v"(c));
-  return r;
-}
-__device__ __forceinline__ float min_raw(float a, float b) {
-  float r;
-  asm("v_min_f32 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
-  return r;
-}
-__device__ __forceinline__ float max_raw(float a, float b) {
-  float r;
-  asm("v_max_f32 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
-  return r;
-}
-
-// Gathers positions 16n..16n+15 of one parked row into x and finds the group's Eq. 2 parameters.
-__device__ __forceinline__ void gather16(const __half *row, const int4 (&pm)[4], float alpha, int G, float top,
-                                         int fmt, bool uneq, unsigned gmap, int lane, float (&x)[16],
-                                         GroupParams &gp) {
+// Gathers positions 16n..16n+15 of one parked row into x and finds the group's Eq. 2
+// parameters.  grp: the group of the lane's positions, of NG.
+__device__ __forceinline__ void gather16(const __half *row, const int4 (&pm)[4], float alpha, int G, int NG, float top,
+                                         int fmt, bool uneq, int grp, _Float16 (&x)[16], GroupParams &gp) {
   const int ch[16] = {pm[0].x, pm[0].y, pm[0].z, pm[0].w, pm[1].x, pm[1].y, pm[1].z, pm[1].w,
                       pm[2].x, pm[2].y, pm[2].z, pm[2].w, pm[3].x, pm[3].y, pm[3].z, pm[3].w};
 #pragma unroll
-  for (int e = 0; e < 16; ++e) x[e] = __half2float(row[ch[e]]);
-  float mn = min3_raw(x[0], x[1], x[2]), mx = max3_raw(x[0], x[1], x[2]);
+  for (int e = 0; e < 16; ++e) x[e] = reinterpret_cast<const _Float16 *>(row)[ch[e]];
+  _Float16 mn = min3_half(x[0], x[1], x[2]), mx = max3_half(x[0], x[1], x[2]);
 #pragma unroll
   for (int e = 3; e < 15; e += 2) {
-    mn = min3_raw(mn, x[e], x[e + 1]);
-    mx = max3_raw(mx, x[e], x[e + 1]);
+    mn = min3_half(mn, x[e], x[e + 1]);
+    mx = max3_half(mx, x[e], x[e + 1]);
   }
-  mn = min_raw(mn, x[15]);
-  mx = max_raw(mx, x[15]);
+  mn = min3_half(mn, x[15], x[15]);
+  mx = max3_half(mx, x[15], x[15]);
+  unsigned both = __builtin_bit_cast(unsigned, half2_t{mn, -mx});
+  asm("s_nop 1" : "+v"(both));  // (as in min_with_lane)
   if (uneq) {
-    // unequal groups: the other seven 16-position pieces of the token sit in the other seven lanes
-    // of this lane's group of eight; take those that belong to the same group
-    const int n = lane & 7, g = tile_group(gmap, n);
-    const float tmn = mn, tmx = mx;
+    // unequal groups: the token's eight lanes, group by group, with the other groups' lanes out of the
+    // running (eight instructions per group; a shuffle through LDS and a test per other lane took ten
+    // times as many)
+    const unsigned own = both;
 #pragma unroll
-    for (int k = 1; k < 8; ++k) {
-      const int other = (n + k) & 7;
-      const float omn = __shfl(tmn, (lane & ~7) + other), omx = __shfl(tmx, (lane & ~7) + other);
-      if (tile_group(gmap, other) == g) {
-        mn = fminf(mn, omn);
-        mx = fmaxf(mx, omx);
+    for (int g = 0; g < 4; ++g)
+      if (g < NG) {  // (uniform)
+        unsigned v = grp == g ? own : 0x7c007c00u;  // +infinity twice
+        asm("s_nop 1" : "+v"(v));
+        v = min_of_neighbours(v, 8);
+        both = grp == g ? v : both;
       }
-    }
   } else {
-    // the group's other lanes are neighbours within eight: lane ^ 1, lane ^ 2, then the mirror
-    // image within the eight (both quads hold their own result by then); data-parallel moves
-    const int lanes = G / 16;
-    if (lanes > 1) {
-      mn = min_raw(mn, lane_move<0xB1>(mn));  // quad_perm [1, 0, 3, 2]
-      mx = max_raw(mx, lane_move<0xB1>(mx));
-    }
-    if (lanes > 2) {
-      mn = min_raw(mn, lane_move<0x4E>(mn));  // quad_perm [2, 3, 0, 1]
-      mx = max_raw(mx, lane_move<0x4E>(mx));
-    }
-    if (lanes > 4) {
-      mn = min_raw(mn, lane_move<0x141>(mn));  // row_half_mirror
-      mx = max_raw(mx, lane_move<0x141>(mx));
-    }
+    both = min_of_neighbours(both, G / 16);
   }
-  gp = group_params(mn, mx, alpha, top, fmt);
+  const half2_t r = __builtin_bit_cast(half2_t, both);
+  gp = group_params((float)r[0], -(float)r[1], alpha, top, fmt);
 }
 
 // code = rint(clamp(y, 0, top)): clamping first gives the same integer because the bounds are
 // integers; adding 1.5 * 2^23 rounds to the nearest integer, ties to even, and leaves the code
-// in the low bits of the sum.
-__device__ __forceinline__ unsigned code_in_low_bits(float x, const GroupParams &gp, float top) {
-  const float y = __fmul_rn(__fsub_rn(x, gp.lo), gp.inv);
+// in the low bits of the sum.  y = (x - lo) * inv, each operation rounded once: the difference is a
+// multiply-add with the factor 1 (`one`, which the compiler does not see through: the instruction then
+// takes the fp16 number as it is, and no conversion is needed).
+__device__ __forceinline__ unsigned code_in_low_bits(_Float16 x, const GroupParams &gp, float top, float one) {
+  const float d = __builtin_fmaf((float)x, one, -gp.lo);
+  const float y = __fmul_rn(d, gp.inv);
   return __float_as_uint(__fadd_rn(__builtin_amdgcn_fmed3f(y, 0.0f, top), 12582912.0f));
 }
 
+constexpr unsigned weights4(unsigned a, unsigned b, unsigned c, unsigned d) { return a | (b << 8) | (c << 16) | (d << 24); }
+__device__ __forceinline__ unsigned dot4(unsigned bytes, unsigned weights, unsigned add = 0u) {
+  return __builtin_amdgcn_udot4(bytes, weights, add, false);
+}
+
 // The 16 codes of a lane as row words.  BITS = 2: two bits each in .x (position 16n + e at bits
-// [2e, 2e+2)); BITS = 3: the low two bits like that in .x and the top bits in .y (position e at bit e);
-// BITS = 4: four bits each in .x (e = 0..7 at bits [4e, 4e+4)) and .y (e = 8..15).  alignbit shifts
-// each code into the word from the top.
+// [2e, 2e+2)); BITS = 4: four bits each in .x (e = 0..7 at bits [4e, 4e+4)) and .y (e = 8..15):
+// alignbit shifts each code into the word from the top.  BITS = 3: the low two bits in .x as for two,
+// the top bits in .y where the plane dword of the pair of key dwords wants them (kKsig; `odd`: n is
+// odd), by dot products over four codes at a time.
 template <int BITS>
-__device__ __forceinline__ uint2 pack16(const float (&x)[16], const GroupParams &gp, float top) {
+__device__ __forceinline__ uint2 pack16(const _Float16 (&x)[16], const GroupParams &gp, float top, float one, bool odd) {
   unsigned w0 = 0, w1 = 0;
+  if constexpr (BITS == 3) {
+    unsigned four[4];
 #pragma unroll
-  for (int e = 0; e < 16; ++e) {
-    const unsigned r = code_in_low_bits(x[e], gp, top);
-    if (BITS == 2) {
-      w0 = __builtin_amdgcn_alignbit(r, w0, 2);
-    } else if (BITS == 3) {
-      w0 = __builtin_amdgcn_alignbit(r, w0, 2);
-      w1 = __builtin_amdgcn_alignbit(r >> 2, w1, 1);
-    } else if (e < 8) {
-      w0 = __builtin_amdgcn_alignbit(r, w0, 4);
-    } else {
-      w1 = __builtin_amdgcn_alignbit(r, w1, 4);
+    for (int k = 0; k < 4; ++k) {
+      unsigned r[4];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) r[e] = code_in_low_bits(x[4 * k + e], gp, top, one);
+      const unsigned a = __builtin_amdgcn_perm(r[1], r[0], 0x0c0c0400u), b = __builtin_amdgcn_perm(r[3], r[2], 0x0c0c0400u);
+      four[k] = __builtin_amdgcn_perm(b, a, 0x05040100u);
+      w0 |= dot4(four[k] & 0x03030303u, weights4(1, 4, 16, 64)) << (8 * k);
+    }
+    // positions e = 0..3 and 4..7 of a half: even dwords at bits {0, 2, 1, 3}, 4 + {0, 2, 4, 1}, odd ones
+    // at 7 + {0, 2, 3, 5}, 11 + {0, 2, 4, 3}
+    static_assert(kKsig0 == 0x58643120u && kKsig1 == 0xefdbca97u, "the weights below follow these places");
+    const unsigned wa = odd ? weights4(1, 4, 8, 32) : weights4(1, 4, 2, 8);
+    const unsigned wb = odd ? weights4(1, 4, 16, 8) : weights4(1, 4, 16, 2);
+    const int sa = odd ? 7 : 0, sb = odd ? 11 : 4;
+    unsigned half[2];
+#pragma unroll
+    for (int k = 0; k < 2; ++k)  // (the masked bytes are four times the bit)
+      half[k] = ((dot4(four[2 * k] & 0x04040404u, wa) << sa) | (dot4(four[2 * k + 1] & 0x04040404u, wb) << sb)) >> 2;
+    w1 = half[0] | (half[1] << 16);
+  } else {
+#pragma unroll
+    for (int e = 0; e < 16; ++e) {
+      const unsigned r = code_in_low_bits(x[e], gp, top, one);
+      if (BITS == 2) {
+        w0 = __builtin_amdgcn_alignbit(r, w0, 2);
+      } else if (e < 8) {
+        w0 = __builtin_amdgcn_alignbit(r, w0, 4);
+      } else {
+        w1 = __builtin_amdgcn_alignbit(r, w1, 4);
+      }
     }
   }
-  if (BITS == 3) w1 >>= 16;
   return make_uint2(w0, w1);
 }
 
@@ -184,12 +212,10 @@ __global__ __launch_bounds__(256) void prefill_kernel(Layout L, const __half *__
   constexpr bool TERNARY = VL == 3;
   // (everything in LDS is private to one wavefront: the four wavefronts never wait for each other)
   __shared__ __align__(16) __half rows[4][2][8][kRowStride];  // [wave][K|V][token][channel]
-  __shared__ unsigned vq[VL == 4 || VL == 8 ? 4 : 1][8][8];   // [wave][token i][n]: 16 codes, j-minor
-  __shared__ unsigned vqtop[VL == 8 ? 4 : 1][8][8];           // 3-bit codes: their top bits, j-minor
-  __shared__ uint2 vq4[VL == 16 ? 4 : 1][8][8 + 1];           // the same for 4-bit codes
-  // ternary codes, one byte each: [wave][position j of the 16][piece n][token i] ...
-  __shared__ __align__(16) uint8_t vbytes[TERNARY ? 4 : 1][16][8][8];
-  // ... and the 13-bit fields made of them, in the order of the block's bytes: field 8j + n
+  // value codes, one byte each: [wave][position j of the 16][piece n][token i] (3-level codes in token
+  // order, the others' tokens 0, 2, 4, 6 before 1, 3, 5, 7) ...
+  __shared__ __align__(16) uint8_t vbytes[4][16][8][8];
+  // ... and the 13-bit fields made of 3-level codes, in the order of the block's bytes: field 8j + n
   __shared__ __align__(4) unsigned short vfields[TERNARY ? 4 : 1][128 + 4];
 
   // (the wavefront's number in a scalar register: everything derived from it stays scalar)
@@ -269,25 +295,22 @@ __global__ __launch_bounds__(256) void prefill_kernel(Layout L, const __half *__
   wave_lds_sync();
 
   GroupParams gk, gv;
-  constexpr int kKBits = KL == 16 ? 4 : KL == 8 ? 3 : 2, kVBits = VL == 16 ? 4 : VL == 8 ? 3 : 2;
-  float x[16];
-  gather16(rows[wave][0][i], pk, ak, cfg_G, (float)(KL - 1), cfg_fmt, uneq, gmap, lane, x, gk);
-  const uint2 kw = pack16<kKBits>(x, gk, (float)(KL - 1));
-  gather16(rows[wave][1][i], pv, av, cfg_G, (float)(VL - 1), cfg_fmt, uneq, gmap, lane, x, gv);
-  uint2 vw = make_uint2(0u, 0u);
-  if constexpr (TERNARY) {
+  constexpr int kKBits = KL == 16 ? 4 : KL == 8 ? 3 : 2;
+  float one = 1.0f;
+  asm("" : "+v"(one));
+  _Float16 x[16];
+  gather16(rows[wave][0][i], pk, ak, cfg_G, cfg_NG, (float)(KL - 1), cfg_fmt, uneq, grp, x, gk);
+  const uint2 kw = pack16<kKBits>(x, gk, (float)(KL - 1), one, n & 1);
+  gather16(rows[wave][1][i], pv, av, cfg_G, cfg_NG, (float)(VL - 1), cfg_fmt, uneq, grp, x, gv);
+  {
     // the sum's low byte is the code: sixteen byte stores, no packing
-    uint8_t *col = &vbytes[wave][0][n][i];
+    uint8_t *col = &vbytes[wave][0][n][TERNARY ? i : (i >> 1) + 4 * (i & 1)];
 #pragma unroll
-    for (int e = 0; e < 16; ++e) col[64 * e] = (uint8_t)code_in_low_bits(x[e], gv, 2.0f);
-  } else {
-    vw = pack16<kVBits>(x, gv, (float)(VL - 1));
+    for (int e = 0; e < 16; ++e) col[64 * e] = (uint8_t)code_in_low_bits(x[e], gv, (float)(VL - 1), one);
   }
   unsigned ktop = 0;
-  if (KL == 8) {  // the plane dword of a pair of key dwords comes from two lanes
-    ktop = place_key_top_bits(kw.y, n & 1);
-    ktop |= __shfl_xor(ktop, 1);
-  }
+  if (KL == 8)  // the plane dword of a pair of key dwords comes from two lanes
+    ktop = kw.y | __builtin_amdgcn_update_dpp(0, (int)kw.y, 0xB1, 0xF, 0xF, true);
   // packed key rows and (scale, zero) pairs of the wavefront's rows: scalar bases at row t0, the
   // lane's row and piece as 32-bit offsets
   if (valid) {
@@ -307,70 +330,54 @@ __global__ __launch_bounds__(256) void prefill_kernel(Layout L, const __half *__
       meta_store_pair(reinterpret_cast<uint8_t *>(L.v_meta) + first, i * cfg_NG + grp, MetaPair{gv.scale, gv.lo, gv.stored}, cfg_fmt);
     }
   }
-  // rows past the packed region leave zeros in the block
-  if (VL == 16) {
-    vq4[wave][i][n] = valid ? vw : make_uint2(0u, 0u);
-  } else if (!TERNARY) {
-    vq[wave][i][n] = valid ? vw.x : 0u;
-    if (VL == 8) vqtop[wave][i][n] = valid ? vw.y : 0u;
-  }
   wave_lds_sync();
 
   // V units of sub-block kb = wave.  Lane (j = lane % 16, nh = lane / 16) builds fields 2nh and
   // 2nh+1 of unit j from the codes of its eight tokens.
   const int j = lane & 15, nh = lane >> 4;
   uint8_t *dst = L.v_codes + (head * L.n_vblocks + blk) * v_block_bytes_of(VL);
-  if (VL == 16) {
-    // fields 2nh and 2nh+1 are dwords 2nh and 2nh+1 of the 32-byte unit
-    unsigned wa = 0, wb = 0;
-#pragma unroll
-    for (int ii = 0; ii < 8; ++ii) {
-      const uint2 qa = vq4[wave][ii][2 * nh], qb = vq4[wave][ii][2 * nh + 1];
-      const unsigned ca = ((j < 8 ? qa.x : qa.y) >> (4 * (j & 7))) & 15u;
-      const unsigned cb = ((j < 8 ? qb.x : qb.y) >> (4 * (j & 7))) & 15u;
-      wa |= ca << (16 * (ii & 1) + 4 * (ii >> 1));
-      wb |= cb << (16 * (ii & 1) + 4 * (ii >> 1));
-    }
-    reinterpret_cast<uint2 *>(dst + 512 * wave + 32 * j)[nh] = make_uint2(wa, wb);
-  } else if (VL == 4 || VL == 8) {
-    unsigned w = 0;
-#pragma unroll
-    for (int ii = 0; ii < 8; ++ii) {
-      const unsigned ca = (vq[wave][ii][2 * nh] >> (2 * j)) & 3u;
-      const unsigned cb = (vq[wave][ii][2 * nh + 1] >> (2 * j)) & 3u;
-      w |= (ca << (16 * (ii & 1) + 2 * (ii >> 1))) | (cb << (8 + 16 * (ii & 1) + 2 * (ii >> 1)));
-    }
-    if (VL == 4) {
+  uint4 c = *reinterpret_cast<const uint4 *>(&vbytes[wave][j][2 * nh][0]);
+  if (n_valid < 8) {  // (a scalar condition) codes of rows that do not exist count as zero
+    const int first = TERNARY ? min(n_valid, 4) : (n_valid + 1) >> 1, second = n_valid - first;  // of .x and .z, of .y and .w
+    const unsigned lo = first >= 4 ? ~0u : (1u << (8 * first)) - 1u, hi = (1u << (8 * second)) - 1u;  // (second < 4)
+    c.x &= lo, c.z &= lo, c.y &= hi, c.w &= hi;
+  }
+  if constexpr (VL == 16) {
+    // a field is a dword, token 2m (2m + 1) at bits 4m of its low (high) half: neighbouring bytes to one,
+    // then two bytes of the even and two of the odd tokens
+    auto field = [](unsigned even, unsigned odd) {
+      return __builtin_amdgcn_perm(odd | (odd >> 4), even | (even >> 4), 0x06040200u);
+    };
+    reinterpret_cast<uint2 *>(dst + 512 * wave + 32 * j)[nh] = make_uint2(field(c.x, c.y), field(c.z, c.w));
+  } else if constexpr (VL == 4 || VL == 8) {
+    // token 2m (2m + 1) at bits 2m of the low (high) half, the second field eight bits up
+    constexpr unsigned kTwoBits = weights4(1, 4, 16, 64), kLow = VL == 8 ? 0x03030303u : ~0u;
+    const unsigned w = dot4(c.x & kLow, kTwoBits) | (dot4(c.z & kLow, kTwoBits) << 8) |
+                       (dot4(c.y & kLow, kTwoBits) << 16) | (dot4(c.w & kLow, kTwoBits) << 24);
+    if constexpr (VL == 4) {
       reinterpret_cast<unsigned *>(dst + 256 * wave)[4 * j + nh] = w;
     } else {
       // 24-byte units: the 2-bit plane, then the two dwords of top bits (fields 4J .. 4J+3 in
-      // dword J = nh / 2, built by the lanes nh = 2J and 2J + 1)
+      // dword J = nh / 2, built by the lanes nh = 2J and 2J + 1).  The top bits of the lane's two fields
+      // side by side -- pair m at bits 2m, 2m + 1 of each half, times four -- then pairs 0..2 and pair 3
+      // to their places (vtau).
       unsigned *unit = reinterpret_cast<unsigned *>(dst + 384 * wave + 24 * j);
       unit[nh] = w;
-      unsigned h = 0;
-      const int na = (2 * nh) & 3;  // n % 4 of field 2nh; field 2nh+1 has na + 1
-#pragma unroll
-      for (int ii = 0; ii < 8; ++ii) {
-        const unsigned ta = (vqtop[wave][ii][2 * nh] >> j) & 1u;
-        const unsigned tb = (vqtop[wave][ii][2 * nh + 1] >> j) & 1u;
-        h |= (ta << (16 * (ii & 1) + vtau(na, ii >> 1))) | (tb << (16 * (ii & 1) + vtau(na + 1, ii >> 1)));
-      }
+      auto tops = [](unsigned a, unsigned b) {
+        return dot4(b & 0x04040404u, weights4(2, 8, 32, 128), dot4(a & 0x04040404u, weights4(1, 4, 16, 64)));
+      };
+      const unsigned t = (tops(c.x, c.z) >> 2) | (tops(c.y, c.w) << 14);
+      const int up = 6 * (nh & 1);
+      unsigned h = ((t & 0x003f003fu) << up) | ((t & 0x00c000c0u) << (6 + 2 * (nh & 1)));
       h |= __shfl_xor(h, 16);
       if ((nh & 1) == 0) unit[4 + (nh >> 1)] = h;
     }
   } else {
     // A field is the base-3 number whose digit i is token i's code: the codes of tokens 0..3 and 4..7
-    // arrive as the bytes of two dwords, and a byte-wise dot product with (1, 3, 9, 27) sums four
-    // digits at once.
-    uint4 c = *reinterpret_cast<const uint4 *>(&vbytes[wave][j][2 * nh][0]);
-    if (n_valid < 8) {  // (a scalar condition) bytes of rows that do not exist count as zero
-      const unsigned lo = n_valid >= 4 ? ~0u : (1u << (8 * n_valid)) - 1u;
-      const unsigned hi = n_valid <= 4 ? 0u : (1u << (8 * (n_valid - 4))) - 1u;
-      c.x &= lo, c.z &= lo, c.y &= hi, c.w &= hi;
-    }
-    constexpr unsigned kPowers = 1u | (3u << 8) | (9u << 16) | (27u << 24);
-    const unsigned fa = __builtin_amdgcn_udot4(c.x, kPowers, __umul24(81u, __builtin_amdgcn_udot4(c.y, kPowers, 0u, false)), false);
-    const unsigned fb = __builtin_amdgcn_udot4(c.z, kPowers, __umul24(81u, __builtin_amdgcn_udot4(c.w, kPowers, 0u, false)), false);
+    // are the bytes of two dwords, and a byte-wise dot product with (1, 3, 9, 27) sums four digits at once.
+    constexpr unsigned kPowers = weights4(1, 3, 9, 27);
+    const unsigned fa = dot4(c.x, kPowers, __umul24(81u, dot4(c.y, kPowers)));
+    const unsigned fb = dot4(c.z, kPowers, __umul24(81u, dot4(c.w, kPowers)));
     reinterpret_cast<unsigned *>(vfields[wave])[4 * j + nh] = fa | (fb << 16);  // fields 8j + 2nh and the next
     wave_lds_sync();
     // The sub-block's 208 bytes are its 128 fields of 13 bits in a row.  Lane d < 52 builds dword d:

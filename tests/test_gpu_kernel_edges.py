@@ -98,3 +98,22 @@ def test_many_rows_per_kv_head(case):
         out, ref = pair.append_decode_both(*synth.make_new_token(w, 50 + s), q1)
         assert np.abs(out - ref).max() <= P.TOL, s
     pair.assert_buffers_equal()
+
+
+# the prompt quantizer at every number of tokens of a last sub-block (1 .. 8) and at a V block's edge, for
+# every value width, with equal and unequal groups, compact pairs and values down to fp16's subnormals
+@pytest.mark.parametrize("packed,k_bits,v_bits,group,meta,bounds", [
+    (1, 3.0, 3.0, 64, "e4m3", [0, 32, 128]), (2, 4.0, 4.0, 32, "e4m3", [0, 16, 32, 64, 128]), (3, 2.0, 2.0, 64, "f16", [0, 112, 128]),
+    (4, 2.0, 4.0, 64, "f32", None), (5, 4.0, 4.0, 64, "e4m3", None), (6, 3.0, 3.0, 32, "f16", [0, 48, 64, 112, 128]),
+    (7, 4.0, 1.5, 32, "e4m3", None), (8, 3.0, 3.0, 128, "f32", None), (31, 3.0, 3.0, 64, "e4m3", [0, 80, 128]),
+    (33, 2.0, 2.0, 128, "e4m3", None), (37, 2.0, 1.5, 64, "e4m3", [0, 96, 128]), (35, 4.0, 2.0, 128, "f32", None)])
+def test_prompt_quantizer_tails(packed, k_bits, v_bits, group, meta, bounds):
+    from paper_2405_06219_amd import synth
+    print("case", packed, k_bits, v_bits, group, meta, bounds, flush=True)
+    w = synth.Workload("tails", 2, 3, 3, 16 + packed, v_bits, group_size=group, window=16, k_bits=k_bits, seed=packed)
+    pair, k, v, _ = P.make_pair(w, meta=meta, group_bounds=bounds)
+    k[0, 1, 0] = (k[0, 1, 0].astype(np.float32) * 1e-6).astype(np.float16)    # subnormal
+    v[1, 2, packed - 1] = (v[1, 2, packed - 1].astype(np.float32) * 2e-6).astype(np.float16)
+    v[0, 0, 0] = -0.0
+    pair.prefill(k, v)
+    pair.assert_buffers_equal()
