@@ -141,11 +141,15 @@ int choose_splits(const skvq_cache *c, long long n_quant, int n_new = 1) {
   if (c->forced_splits > 0) {
     s = c->forced_splits;
   } else {
-    // one workgroup per compute unit over all (sequence, kv head) pairs, but every wavefront of
-    // a workgroup should have at least two tiles
+    // one workgroup per compute unit over all (sequence, kv head) pairs, but every wavefront of a
+    // workgroup should have at least two tiles where the partials take a second launch to combine.  Up
+    // to kMaxMergeLast chunks they do not, and a short cache is read faster in more, shorter chunks
+    // (one, four and eight chunks, us per step: 1 x 4 heads x 2048 tokens 12.3 / 10.3 / 9.0, 4 x 800
+    // 9.8 / 9.3 / 8.0, 32 q / 8 kv x 3000 4-bit 21.2 / 13.7 / 11.0).
     const long long heads = (long long)c->L.B * c->L.Hk * decode_passes(c->L, c->L.R * n_new);
     s = c->n_cus / heads;
-    const long long cap = tiles / (2 * kMfmaWavesPerGroup);
+    long long cap = tiles / (2 * kMfmaWavesPerGroup);
+    if (merges_in_launch(c->L, kMaxMergeLast, n_new) && cap < kMaxMergeLast) cap = kMaxMergeLast;
     if (s > cap) s = cap;
   }
   if (s > SKVQ_MAX_SPLITS) s = SKVQ_MAX_SPLITS;
@@ -236,13 +240,14 @@ int skvq_create(const skvq_config *cfg, const skvq_buffers *bufs, skvq_cache **o
   L.v_win = (__half *)bufs->v_win;
   L.workspace = (float *)bufs->workspace;
 
-  // constants: [perm_k | perm_v | clip_k | clip_v | gmaps | kept token numbers], one allocation
+  // constants: [perm_k | perm_v | clip_k | clip_v | gmaps | kept token numbers | tickets], one allocation
   const size_t n_perm = (size_t)L.Hk * kD, n_clip = (size_t)L.Hk * L.NG;
   const size_t off_pv = n_perm * 4, off_ck = off_pv + n_perm * 4;
   const size_t off_cv = off_ck + ((n_clip * 4 + 15) & ~(size_t)15);
   const size_t off_gm = off_cv + ((n_clip * 4 + 15) & ~(size_t)15);
   const size_t off_ids = off_gm + (((size_t)L.Hk * 4 + 15) & ~(size_t)15);
-  const size_t total = off_ids + (((size_t)L.S * 4 + 15) & ~(size_t)15);
+  const size_t off_tk = off_ids + (((size_t)L.S * 4 + 15) & ~(size_t)15);
+  const size_t total = off_tk + 2 * (size_t)L.B * L.Hk * 4;  // (tickets of the workspace's and of the static scratch's calls)
   std::vector<uint8_t> host(total, 0);
   std::memcpy(host.data(), cfg->perm_k, n_perm * 4);
   std::memcpy(host.data() + off_pv, cfg->perm_v, n_perm * 4);
@@ -270,6 +275,7 @@ int skvq_create(const skvq_config *cfg, const skvq_buffers *bufs, skvq_cache **o
   L.clip_v = (const float *)(d + off_cv);
   L.gmaps = (const unsigned *)(d + off_gm);
   c->dev_kept_ids = (int *)(d + off_ids);
+  L.tickets = (int *)(d + off_tk);  // (zero, as `host` is)
 
   int dev = 0;
   hipDeviceProp_t prop;
@@ -537,6 +543,7 @@ int skvq_decode_attention_static(skvq_cache *c, const void *q, void *out_f32, vo
   if (!c->static_scratch) return SKVQ_ERR_HIP;  // the lookup at creation failed; last_error says why
   Layout L = c->L;
   L.workspace = c->static_scratch;  // the kernels take it as they take the caller's workspace
+  L.tickets += (size_t)L.B * L.Hk;
   hipError_t e = launch_decode(L, (const __half *)q, (float *)out_f32, (__half *)out_f16, c->n_tokens, c->n_kept,
                                choose_splits(c, counts_now(c).n_quant), 1, (hipStream_t)stream);
   if (e != hipSuccess) return fail_hip(c, e, "skvq_decode_attention_static launch");

@@ -4,8 +4,8 @@
 // The packed region of every (sequence, kv head) is cut into n_splits chunks of whole 64-token
 // tiles; the chunk kernel (skvq_decode_mfma.hip) keeps a running (max, sum, weighted value sum)
 // per query head (online softmax) and writes one partial per chunk, in original channel order.
-// A kv head read as one chunk has its output written by the chunk kernel; several chunks' partials
-// are combined by the merge kernel below.
+// A kv head read as one chunk has its output written by the chunk kernel, which also combines the
+// partials of a few chunks; many chunks' partials are combined by the merge kernel below.
 #include <hip/hip_runtime.h>
 #include <hip/hip_fp16.h>
 
@@ -112,7 +112,8 @@ hipError_t launch_decode(const Layout &L, const __half *q, float *out_f32, __hal
   MergeOut mo;
   mo.out_f32 = out_f32;
   mo.out_f16 = out_f16;
-  mo.mode = n_splits == 1 ? kMergeDirect : kMergeSeparate;
+  mo.mode = n_splits == 1 ? kMergeDirect : merges_in_launch(L, n_splits, n_new) ? kMergeLast : kMergeSeparate;
+  mo.tickets = L.tickets;
   hipError_t e = launch_decode_mfma(L, q, T, n.n_quant, (int)n.n_sink, n_splits, n_new, k_new, v_new, te, mo, s);
   if (e != hipSuccess || mo.mode != kMergeSeparate) return e;
   // the fp16 tokens are folded into the chunks' partials

@@ -5,15 +5,13 @@
 // unequal (whole 16-position pieces of the head, mapped to groups by Layout::gmap: then every
 // piece has its own score accumulator and weight operand).  This header is compiled
 // once per (K format, V format) pair (SKVQ_KL, SKVQ_VL) by skvq_decode_mfma_inst.hip.
-// A kv head that is read as one chunk has its output written by that chunk's workgroup; several
-// chunks leave partials for merge_kernel.  (Merging them inside this launch was built twice and
-// dropped.  With device-scope fences: each fence writes back and invalidates a whole L2, 25 us over
-// 256 workgroups.  With all chunks of a kv head on one XCD -- workgroup i of a grid runs on XCD
-// i % 8 -- and the hand-off through that XCD's L2 (stores acknowledged, a ticket from an atomic
-// counter, the last workgroup reads the partials): correct, and as long as the second launch:
-// acknowledgement 0.3 us + ticket 0.8 us + reading and combining 32 partials 1.6 - 2.8 us on the
-// slowest workgroup's tail, against 3.0 us for merge_kernel, of which 2.0 us is what any dependent
-// launch costs.)
+// A kv head that is read as one chunk has its output written by that chunk's workgroup; of a few
+// chunks the workgroup that ends last combines the partials (merge_by_last); many leave them to
+// merge_kernel.  (With many, merging inside this launch takes as long as the second launch or longer:
+// acknowledgement 0.3 us + ticket 0.8 us + reading and combining 32 partials 1.6 - 2.8 us on the slowest
+// workgroup's tail, against 3.0 us for merge_kernel, of which 2.0 us is what any dependent launch costs.
+// With device-scope fences each fence writes back and invalidates a whole L2: 25 us over 256
+// workgroups.)
 //
 // One workgroup of 8 wavefronts per chunk (one per compute unit when the cache is long
 // enough).  Per wavefront, per tile of 64 packed tokens:
@@ -263,6 +261,7 @@ struct Smem {
   // ([head][...][wave]: the epilogue reads a head's eight entries as two 16-byte pieces)
   alignas(16) float wm[R][kNW], wl[R][kNW], wz[R][NG][kNW], rm[R][kNW], rl[R][kNW];
   float ring_o[kNW][R][kD];            // per wave: its ring slices' outputs, original channel order
+  int ticket;                          // kMergeLast: workgroups of the kv head that ended before this one
 };
 
 // One 4-channel step of the score product.  The A operand of step ST lives in lanes
@@ -413,6 +412,50 @@ inline ChunkPlan plan_chunks(const Layout &L, long long T, long long nq, int n_s
   const long long n_win = (T - nq) - n_sink;
   p.slot0 = (int)((T - n_win) % L.W);
   return p;
+}
+
+// The chunks of a kv head combined in the same launch: every workgroup writes its partials through to
+// memory (agent-scope stores: the chunks run on different chiplets, whose L2 caches do not see each
+// other's lines), waits until they are there, and takes a ticket; the last one reads all partials, in
+// one round trip, and writes the output.  No fence: those write back and invalidate whole L2 caches.
+// Up to kMaxMergeLast chunks this takes less than the second launch, us per step: 32 heads x 32768 tokens
+// (8 chunks) 20.9 -> 19.8, 8 x 8 kv heads x 6007 tokens 4-bit (4 chunks, four rows) with its prefill's
+// share 24.5 -> 23.4; with 12 or more chunks it takes longer (32 chunks, four rows, 131072 tokens: 21.5
+// -> 23.5), and merge_kernel combines them.
+template <int R>
+__device__ __forceinline__ void merge_by_last(const float *base, int *ticket, int n_splits, int tid,
+                                              bool row_exists, int &shared, float *out_f32, __half *out_f16) {
+  __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0): this wavefront's partials have arrived
+  asm volatile("" ::: "memory");
+  __syncthreads();
+  if (tid == 0) shared = __hip_atomic_fetch_add(ticket, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  __syncthreads();
+  if (shared != n_splits - 1) return;
+  if (tid == 0) __hip_atomic_store(ticket, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  if (tid >= R * kD || !row_exists) return;
+  float m[kMaxMergeLast], l[kMaxMergeLast], v[kMaxMergeLast], top = -INFINITY;
+#pragma unroll
+  for (int i = 0; i < kMaxMergeLast; ++i) {
+    const float *part = base + (long long)min(i, n_splits - 1) * kPartialStride;
+    m[i] = __hip_atomic_load(part, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    l[i] = __hip_atomic_load(part + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    v[i] = __hip_atomic_load(part + 4 + (tid & (kD - 1)), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
+#pragma unroll
+  for (int i = 0; i < kMaxMergeLast; ++i) {
+    if (i >= n_splits) l[i] = 0.f;
+    if (l[i] > 0.f) top = fmaxf(top, m[i]);
+  }
+  float num = 0.f, den = 0.f;
+#pragma unroll
+  for (int i = 0; i < kMaxMergeLast; ++i) {
+    const float w = l[i] > 0.f ? exp2f(m[i] - top) : 0.f;
+    num = w > 0.f ? fmaf(w, v[i], num) : num;
+    den = fmaf(w, l[i], den);
+  }
+  const float o = num / den;
+  *out_f32 = o;
+  if (out_f16) *out_f16 = __float2half_rn(o);
 }
 
 template <int R, int KL, int VL, int META, int NG, bool UNEQ>
@@ -1160,12 +1203,29 @@ __global__ __launch_bounds__(kThreads, 2) void decode_mfma_kernel(Layout L, cons
     } else {
       float *part =
           L.workspace + (row_index(head0 + r) * (SKVQ_MAX_SPLITS + 1) + sp) * kPartialStride;
-      part[4 + ch] = num;
-      if (p == 0) {
-        part[0] = m;
-        part[1] = den;
+      if (mo.mode == kMergeLast) {
+        __hip_atomic_store(part + 4 + ch, num, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (p == 0) {
+          __hip_atomic_store(part, m, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+          __hip_atomic_store(part + 1, den, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+      } else {
+        part[4 + ch] = num;
+        if (p == 0) {
+          part[0] = m;
+          part[1] = den;
+        }
       }
     }
+  }
+  if (mo.mode == kMergeLast) {
+    const int r = min(tid >> 7, R - 1);
+    const bool row_exists = head0 + r < n_rows;
+    const long long row = row_index(row_exists ? head0 + r : head0), idx = row * kD + (tid & (kD - 1));
+    const float *base = L.workspace + row * (SKVQ_MAX_SPLITS + 1) * kPartialStride;
+    float *o32 = mo.out_f32 + idx;
+    __half *o16 = mo.out_f16 ? mo.out_f16 + idx : nullptr;
+    merge_by_last<R>(base, mo.tickets + head, n_splits, tid, row_exists, sm.ticket, o32, o16);
   }
 }
 

@@ -48,17 +48,20 @@ struct Layout {
   float *workspace;
   const int *perm_k, *perm_v;    // device copies [Hk][D]
   const float *clip_k, *clip_v;  // device copies [Hk][NG]
+  int *tickets;                  // device [B][Hk], see MergeOut
 };
 
 // Where the chunk partials of a decode call are combined.
 enum MergeMode {
   kMergeSeparate = 0,  // the chunk kernel writes partials, merge_kernel combines them (a second launch)
-  kMergeDirect = 1     // one chunk per kv head: its workgroup writes the output itself
+  kMergeDirect = 1,    // one chunk per kv head: its workgroup writes the output itself
+  kMergeLast = 2       // few chunks: the workgroup of a kv head that ends last combines them (see merge_by_last)
 };
 struct MergeOut {
   float *out_f32;
   __half *out_f16;  // or null
   int mode;         // MergeMode
+  int *tickets;     // kMergeLast: one counter per (sequence, kv head), zero before and after a launch
 };
 
 // Where the T cached tokens of a sequence live (Section 3.2 with the attention-sink rule): the
@@ -142,6 +145,11 @@ hipError_t launch_decode_mfma(const Layout &L, const __half *q, long long T, lon
 // workgroup per chunk, and the token that leaves the
 // window, if any, is packed rather than copied to a sink row (a sink row has other readers in
 // the same launch).
+constexpr int kMaxMergeLast = 8;  // chunks per kv head up to which the last workgroup combines them
+// (the kernel for more than four rows leaves its partials to merge_kernel)
+inline bool merges_in_launch(const Layout &L, int n_splits, int n_new) {
+  return n_splits <= kMaxMergeLast && L.R * n_new <= 4;
+}
 constexpr int kMinSplitsForOneLaunch = 4;  // chunks per kv head from which the one-launch step is used whatever their number
 inline bool append_fusable(const Layout &L, long long T_after, bool leaving_token_is_kept) {
   const long long T = T_after - 1;  // tokens cached before

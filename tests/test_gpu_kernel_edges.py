@@ -117,3 +117,25 @@ def test_prompt_quantizer_tails(packed, k_bits, v_bits, group, meta, bounds):
     v[0, 0, 0] = -0.0
     pair.prefill(k, v)
     pair.assert_buffers_equal()
+
+
+# chunks combined by the workgroup that ends last (2 .. 8) and by the second launch (9): one to four rows, a
+# partly filled last pass of rows, chunks of one tile, the same counters call after call
+@pytest.mark.parametrize("hq,hk,n_new,context,batch,splits", [(2, 2, 1, 128 + 65, 1, 2), (3, 3, 1, 700, 2, 8), (4, 2, 1, 900, 1, 7),
+                                                              (6, 2, 1, 640, 2, 3), (8, 2, 1, 700, 1, 8), (4, 1, 1, 800, 3, 9),
+                                                              (2, 1, 2, 700, 1, 5), (3, 3, 3, 1000, 1, 8), (4, 4, 1, 2048, 1, 0)])
+def test_chunks_combined_in_the_launch(hq, hk, n_new, context, batch, splits):
+    from paper_2405_06219_amd import synth
+    print("case", hq, hk, n_new, context, batch, splits, flush=True)
+    w = synth.Workload("last", batch, hq, hk, context, 1.5, group_size=128, seed=77)
+    pair, k, v, _ = P.make_pair(w, extra_tokens=8, max_new_tokens=n_new)
+    pair.prefill(k, v)
+    pair.gpu.skvq_set_num_splits(splits)
+    rng = np.random.default_rng(context)
+    for s in range(3):
+        q = rng.standard_normal((batch, n_new, hq, D)).astype(np.float16)
+        o16 = torch.empty(q.shape, dtype=torch.float16, device=pair.device)
+        out = pair.gpu.skvq_decode_attention_multi(torch.from_numpy(q).to(pair.device), out_f16=o16).cpu().numpy()
+        assert np.abs(out - pair.ref.decode_multi(q)).max() <= P.TOL, s
+        assert np.array_equal(o16.cpu().numpy(), out.astype(np.float16))
+        pair.append(*synth.make_new_token(w, s))
