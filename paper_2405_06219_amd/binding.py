@@ -178,12 +178,14 @@ def skvq_validate_config(cfg: skvq_config) -> int:
 
 def _stream_ptr(stream) -> int:
     if stream is None:
-        stream = torch.cuda.current_stream()
+        # the current device's current stream, as torch.cuda.current_stream() names it, without the Stream
+        # object (2.8 us a call, of 8 us that a short decode step takes)
+        return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
     return int(stream.cuda_stream)
 
 
 def _dev_ptr(t: torch.Tensor, dtype, shape) -> int:
-    if not (t.is_cuda and t.is_contiguous() and t.dtype == dtype and tuple(t.shape) == tuple(shape)):
+    if not (t.shape == shape and t.dtype == dtype and t.is_cuda and t.is_contiguous()):
         raise ValueError(f"expected contiguous cuda {dtype} tensor of shape {tuple(shape)}, got {t.dtype} "
                          f"{tuple(t.shape)} on {t.device}")
     return t.data_ptr()
