@@ -32,7 +32,7 @@ namespace {
 // products.
 //
 // Bound by HBM in the plain 2-bit / 3-level configuration, by vector instructions in the others
-// (3-bit codes in two unequal groups with FP8 pairs, 2 x 32 heads x 20011 tokens: 222 -> 163 us, 900 -> 469
+// (3-bit codes in two unequal groups with FP8 pairs, 2 x 32 heads x 20011 tokens: 222 -> 165 us, 850 -> 469
 // vector instructions per wavefront of 8 tokens, with the byte fields, the group by group minima, the
 // fp16 minima and differences and the one-instruction FP8 pairs).
 // ---------------------------------------------------------------------------------------
