@@ -10,7 +10,7 @@
 //        (its column), the scores of the tokens 8 h .. 8 h + 7 of both blocks of 32: the running
 //        reference and the sums are plain registers of a lane, and
 //   PV   O^T[channel][row] by v_mfma_f32_16x16x32_f16: A = the V unit, B = the lane's own weights as
-//        they are (high and low fp16 parts, two accumulators): no weight goes through LDS.
+//        they are (high and low fp16 parts, one chain of products): no weight goes through LDS.
 //
 // What the lane = token kernel does per row, in as many workgroups per chunk as there are four rows
 // (each unpacking all codes again), is done once here: loads, unpacking, table reads, (scale, zero).

@@ -139,3 +139,25 @@ def test_chunks_combined_in_the_launch(hq, hk, n_new, context, batch, splits):
         assert np.abs(out - pair.ref.decode_multi(q)).max() <= P.TOL, s
         assert np.array_equal(o16.cpu().numpy(), out.astype(np.float16))
         pair.append(*synth.make_new_token(w, s))
+
+
+def test_chunks_combined_in_the_launch_replayed():
+    """The counters of a captured call are as they were after every replay (eager calls in between)."""
+    from paper_2405_06219_amd import synth
+    w = synth.Workload("replay", 1, 4, 2, 900, 1.5, group_size=128, seed=8)
+    pair, k, v, q = P.make_pair(w)
+    pair.prefill(k, v)
+    pair.gpu.skvq_set_num_splits(6)
+    qd = torch.from_numpy(q).to(pair.device)
+    out = torch.empty(q.shape, dtype=torch.float32, device=pair.device)
+    eager = pair.gpu.skvq_decode_attention(qd).cpu().numpy()
+    assert np.abs(eager - pair.ref.decode(q)).max() <= P.TOL
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        pair.gpu.skvq_decode_attention(qd, out_f32=out)
+    for _ in range(4):
+        out.zero_()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert np.abs(out.cpu().numpy() - eager).max() <= 1e-5   # the wavefronts' sums in another order
+        assert np.abs(pair.gpu.skvq_decode_attention(qd).cpu().numpy() - eager).max() <= 1e-5
