@@ -241,9 +241,10 @@ int skvq_decode_attention_static(skvq_cache *cache, const void *q, void *out_f32
 /* One decode step of Algorithm 1 with l = 1 as a single call: skvq_quantize_append(k_new, v_new)
  * followed by skvq_decode_attention(q), same arguments, same results in the cache and in the
  * outputs, same errors.  When a kv head is read by one workgroup per chunk (at most four query
- * heads, or one or two equal groups per head), it is split into at least four chunks (long caches,
- * few sequences) or the launch has a compute unit for every workgroup, and the token that leaves
- * the window is packed (not kept as a sink), both run as one launch: the workgroup that reads the
+ * heads; more with one or two equal groups per head, where the cache is long for the compute units at
+ * hand), it is split into at least four chunks (long caches, few sequences) or the launch has a compute
+ * unit for every workgroup, and the token that leaves the window is packed (not kept as a sink), both
+ * run as one launch: the workgroup that reads the
  * last packed rows quantizes the leaving token itself before it reads them, and the new token's
  * fp16 row is taken from k_new / v_new; otherwise the two kernels are launched one after the
  * other.  k_new and v_new must stay valid until the call has finished on the stream. */
@@ -307,7 +308,8 @@ int skvq_calibrate_clip(skvq_cache *cache, const void *k, const void *v, int64_t
  * attends over the cached tokens 0 .. T - n_new + j, each in the form it is stored in now.
  * q: DEVICE fp16 [B][n_new][Hq][D]; out_f32: DEVICE fp32 [B][n_new][Hq][D]; out_f16 likewise or
  * NULL.  n_new = 1 is skvq_decode_attention.  The packed cache is read once per four
- * (query token, query head) rows of a kv head.
+ * (query token, query head) rows of a kv head, or once per sixteen (one or two equal groups per head,
+ * where the cache is long for the compute units at hand).
  * SKVQ_ERR_INVALID_ARG if n_new > max_new_tokens or n_new exceeds the tokens in the window. */
 #define SKVQ_MAX_NEW_TOKENS 64
 int skvq_decode_attention_multi(skvq_cache *cache, const void *q, int32_t n_new, void *out_f32,

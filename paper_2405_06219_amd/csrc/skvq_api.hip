@@ -134,7 +134,8 @@ int append_with(skvq_cache *c, const void *k_new, const void *v_new, bool keep, 
   return SKVQ_OK;
 }
 
-int choose_splits(const skvq_cache *c, long long n_quant, int n_new = 1) {
+// Chunks per kv head where `rows` rows go to a workgroup.
+int choose_splits(const skvq_cache *c, long long n_quant, int n_new, int rows) {
   if (n_quant <= 0) return 0;
   const long long tiles = (n_quant + 63) / 64;  // a split is a whole number of 64-token tiles
   long long s;
@@ -146,7 +147,7 @@ int choose_splits(const skvq_cache *c, long long n_quant, int n_new = 1) {
     // to kMaxMergeLast chunks they do not, and a short cache is read faster in more, shorter chunks
     // (one, four and eight chunks, us per step: 1 x 4 heads x 2048 tokens 12.3 / 10.3 / 9.0, 4 x 800
     // 9.8 / 9.3 / 8.0, 32 q / 8 kv x 3000 4-bit 21.2 / 13.7 / 11.0).
-    const long long heads = (long long)c->L.B * c->L.Hk * decode_passes(c->L, c->L.R * n_new);
+    const long long heads = (long long)c->L.B * c->L.Hk * decode_passes(c->L.R * n_new, rows);
     s = c->n_cus / heads;
     long long cap = tiles / (2 * kMfmaWavesPerGroup);
     if (merges_in_launch(c->L, kMaxMergeLast, n_new) && cap < kMaxMergeLast) cap = kMaxMergeLast;
@@ -156,6 +157,64 @@ int choose_splits(const skvq_cache *c, long long n_quant, int n_new = 1) {
   if (s > tiles) s = tiles;
   if (s < 1) s = 1;
   return (int)s;
+}
+
+// What a call of more than four rows takes, in ns, with n_splits chunks: the waves of workgroups that the
+// compute units need, each with a start-up, the wavefronts' slices of four fp16 tokens (`teams` of a
+// workgroup's wavefronts share them) and the workgroup's tiles, and the merge launch.
+long long decode_cost(const skvq_cache *c, const DecodePlan &p, long long n_quant, long long n_fp, int teams, int tile_ns) {
+  const long long s = p.n_splits > 1 ? p.n_splits : 1, workgroups = (long long)c->L.B * c->L.Hk * p.passes * s;
+  const long long waves = (workgroups + c->n_cus - 1) / c->n_cus;
+  const long long tiles = ((n_quant + 63) / 64 + s - 1) / s, slices = ((n_fp + 3) / 4 + s * teams - 1) / (s * teams);
+  return waves * (4000 + 800 * slices + tile_ns * tiles) + (s > 1 ? 4000 + 50 * s : 0);
+}
+
+// Whether a decode step appends its new token inside the attention launch (append_fusable granted).
+// That pays when few workgroups do the append (one per kv head, of n_splits), and when every
+// workgroup of the launch has a compute unit to itself, however many of them append: the append then
+// lengthens the call by less than the launch it replaces (one launch against two, us per call: 1 x 4
+// heads x 800 tokens 11.0 / 12.9, 8 x 32 x 4000 23.4 / 24.9, 12 x 8 x 20000 36.6 / 39.3, 8 x 32 x 32k
+// 106.0 / 107.5).  Past that, a workgroup that starts late waits for its own append with nothing
+// beside it: 16 x 32 x 32k tokens 240 / 236.
+bool step_is_one_launch(const skvq_cache *c, const DecodePlan &p) {
+  const long long workgroups = (long long)c->L.B * c->L.Hk * (p.n_splits > 1 ? p.n_splits : 1);
+  return p.passes == 1 && (p.n_splits >= kMinSplitsForOneLaunch || workgroups <= c->n_cus);
+}
+
+// Chunks and rows per workgroup for n_quant packed and n_fp fp16 tokens.  Up to four rows go to
+// decode_mfma_kernel.  More go to it four by four, each workgroup unpacking the chunk's codes again, or to
+// decode_wide_kernel sixteen by sixteen, which takes longer to start, walks the fp16 tokens with two teams
+// of wavefronts instead of eight, and takes longer per tile (more so with two groups and 3 or 4 bits, where
+// it spills).  The wide kernel pays where the compute units have no room for the other workgroups and the
+// chunks are long: the costs of both are compared, with constants fitted to 3600 calls of every format, 5 ..
+// 64 rows, 1 .. 256 kv heads over the batch, 600 .. 160000 tokens, windows of 8 .. 1000 tokens (chosen against
+// the faster: 0.2 % longer on average, 12 % at most).  Narrow and wide, us per call: 8 q / 1 kv x 1000
+// tokens 12.9 / 26.3, x 16000 13.1 / 14.3; 32 q / 8 kv, four query tokens, x 4000 15.9 / 21.0, x 16000 16.1 /
+// 16.0, x 40000 23.0 / 17.1; 8 x 64 q / 8 kv x 4000 19.0 / 21.3, x 16000 35.6 / 29.0; 3-bit in two groups, two
+// query tokens, x 64000 27.7 / 41.9.
+// step: the call is a decode step whose leaving token, if any, is packed; the new token may be appended in the
+// launch (step_is_one_launch) or needs one of its own.
+DecodePlan plan_decode(const skvq_cache *c, long long n_quant, long long n_fp, int n_new, bool step = false) {
+  const Layout &L = c->L;
+  const int n_rows = L.R * n_new;
+  DecodePlan narrow = {choose_splits(c, n_quant, n_new, kNarrowRows), kNarrowRows, decode_passes(n_rows, kNarrowRows)};
+  if (n_rows <= kNarrowRows || L.NG > 2 || L.uneq) return narrow;
+  DecodePlan wide = {choose_splits(c, n_quant, n_new, kWideRows), kWideRows, decode_passes(n_rows, kWideRows)};
+  // workgroups of one chunk are n_splits apart in the grid: they share a chiplet's L2 where that is a
+  // multiple of eight, else each of them has the chunk fetched again
+  const int narrow_tile_ns = narrow.n_splits > 0 && narrow.n_splits % 8 == 0 ? 200 : 250;
+  const bool two = L.NG == 2, three_bit = L.k_levels == 8, four_bit = L.k_levels == 16 && L.v_levels == 16;
+  const int wide_tile_ns = !two ? 340 : three_bit ? 550 : four_bit ? 400 : 350;
+  const int wide_more_ns = !two ? 0 : three_bit ? 6400 : four_bit ? 0 : 1600;  // start-up
+  constexpr int kAppendLaunchNs = 2000;
+  const long long a = decode_cost(c, narrow, n_quant, n_fp, kMfmaWavesPerGroup, narrow_tile_ns) +
+                      (step && step_is_one_launch(c, wide) ? kAppendLaunchNs : 0);
+  const long long b = decode_cost(c, wide, n_quant, n_fp, kWideTeams, wide_tile_ns) + wide_more_ns;
+  return b < a ? wide : narrow;
+}
+DecodePlan plan_decode_now(const skvq_cache *c, int n_new) {
+  const long long n_quant = counts_now(c).n_quant;
+  return plan_decode(c, n_quant, c->n_tokens - n_quant, n_new);
 }
 
 }  // namespace
@@ -456,7 +515,7 @@ int skvq_calibrate_clip(skvq_cache *c, const void *k, const void *v, int64_t T, 
   std::vector<float> h_err(err_n);
   const std::vector<float> start_k = c->clip_k, start_v = c->clip_v;
   const Counts cnt = counts_of(T, L.W, L.S);
-  const int n_splits = choose_splits(c, cnt.n_quant);
+  const DecodePlan plan = plan_decode(c, cnt.n_quant, T - cnt.n_quant, 1);
   int rc = SKVQ_OK;
   for (int which = 0; which < 2 && rc == SKVQ_OK; ++which) {
     std::vector<float> &clip = which ? c->clip_v : c->clip_k;
@@ -467,7 +526,7 @@ int skvq_calibrate_clip(skvq_cache *c, const void *k, const void *v, int64_t T, 
         if (rc != SKVQ_OK) break;
         e = launch_prefill(L, (const __half *)k, (const __half *)v, T, cnt.n_sink, nullptr, stream);
         for (int i = 0; i < n_queries && e == hipSuccess; ++i) {
-          e = launch_decode(L, (const __half *)q + (size_t)i * out_n, d_out, nullptr, T, cnt.n_sink, n_splits, 1, stream);
+          e = launch_decode(L, (const __half *)q + (size_t)i * out_n, d_out, nullptr, T, cnt.n_sink, plan, 1, stream);
           if (e == hipSuccess)
             e = launch_sqerr(L, d_out, (const float *)o_ref + (size_t)i * out_n,
                              d_err + ((size_t)a * n_queries + i) * slots, stream);
@@ -528,7 +587,7 @@ int skvq_decode_attention(skvq_cache *c, const void *q, void *out_f32, void *out
   if (!c || !q || !out_f32) return SKVQ_ERR_INVALID_ARG;
   if (c->n_tokens <= 0) return SKVQ_ERR_STATE;
   hipError_t e = launch_decode(c->L, (const __half *)q, (float *)out_f32, (__half *)out_f16, c->n_tokens, c->n_kept,
-                               choose_splits(c, counts_now(c).n_quant), 1, (hipStream_t)stream);
+                               plan_decode_now(c, 1), 1, (hipStream_t)stream);
   if (e != hipSuccess) return fail_hip(c, e, "skvq_decode_attention launch");
   return SKVQ_OK;
 }
@@ -545,7 +604,7 @@ int skvq_decode_attention_static(skvq_cache *c, const void *q, void *out_f32, vo
   L.workspace = c->static_scratch;  // the kernels take it as they take the caller's workspace
   L.tickets += (size_t)L.B * L.Hk;
   hipError_t e = launch_decode(L, (const __half *)q, (float *)out_f32, (__half *)out_f16, c->n_tokens, c->n_kept,
-                               choose_splits(c, counts_now(c).n_quant), 1, (hipStream_t)stream);
+                               plan_decode_now(c, 1), 1, (hipStream_t)stream);
   if (e != hipSuccess) return fail_hip(c, e, "skvq_decode_attention_static launch");
   return SKVQ_OK;
 }
@@ -559,18 +618,10 @@ int skvq_append_decode_attention(skvq_cache *c, const void *k_new, const void *v
   const long long nq = now.n_quant + (leaves && !keep ? 1 : 0);  // packed rows after the step
   if (nq > c->L.Tcap) return SKVQ_ERR_CAPACITY;
   hipStream_t s = (hipStream_t)stream;
-  const int n_splits = choose_splits(c, nq);
-  // One launch pays when few workgroups do the append (one per kv head, of n_splits), and when every
-  // workgroup of the launch has a compute unit to itself, however many of them append: the append then
-  // lengthens the call by less than the launch it replaces (one launch against two, us per call: 1 x 4
-  // heads x 800 tokens 11.0 / 12.9, 8 x 32 x 4000 23.4 / 24.9, 12 x 8 x 20000 36.6 / 39.3, 8 x 32 x 32k
-  // 106.0 / 107.5).  Past that, a workgroup that starts late waits for its own append with nothing
-  // beside it: 16 x 32 x 32k tokens 240 / 236.
-  const long long workgroups = (long long)c->L.B * c->L.Hk * (n_splits > 1 ? n_splits : 1);
-  const bool few_append = n_splits >= kMinSplitsForOneLaunch || workgroups <= c->n_cus;
-  if (append_fusable(c->L, T + 1, keep) && few_append) {
+  const DecodePlan plan = plan_decode(c, nq, T + 1 - nq, 1, /*step=*/!keep);
+  if (append_fusable(c->L, plan, T + 1, keep) && step_is_one_launch(c, plan)) {
     hipError_t e = launch_decode(c->L, (const __half *)q, (float *)out_f32, (__half *)out_f16, T + 1, c->n_kept,
-                                 n_splits, 1, s, (const __half *)k_new, (const __half *)v_new);
+                                 plan, 1, s, (const __half *)k_new, (const __half *)v_new);
     if (e != hipSuccess) return fail_hip(c, e, "skvq_append_decode_attention launch");
     c->n_tokens = T + 1;
     return SKVQ_OK;
@@ -578,7 +629,7 @@ int skvq_append_decode_attention(skvq_cache *c, const void *k_new, const void *v
   const int rc = append_with(c, k_new, v_new, keep, s, "skvq_append_decode_attention launch (append)");
   if (rc != SKVQ_OK) return rc;
   hipError_t e = launch_decode(c->L, (const __half *)q, (float *)out_f32, (__half *)out_f16, T + 1, c->n_kept,
-                               n_splits, 1, s);
+                               plan, 1, s);
   if (e != hipSuccess) return fail_hip(c, e, "skvq_append_decode_attention launch (decode)");
   return SKVQ_OK;
 }
@@ -590,7 +641,7 @@ int skvq_decode_attention_multi(skvq_cache *c, const void *q, int32_t n_new, voi
   const Counts n = counts_now(c);
   if (n_new > c->max_new || n_new > n.n_win) return SKVQ_ERR_INVALID_ARG;
   hipError_t e = launch_decode(c->L, (const __half *)q, (float *)out_f32, (__half *)out_f16, c->n_tokens, c->n_kept,
-                               choose_splits(c, n.n_quant, n_new), n_new, (hipStream_t)stream);
+                               plan_decode_now(c, n_new), n_new, (hipStream_t)stream);
   if (e != hipSuccess) return fail_hip(c, e, "skvq_decode_attention_multi launch");
   return SKVQ_OK;
 }

@@ -13,15 +13,18 @@ namespace skvq {
 // The launcher of the kernels with KL-level keys and VL-level values.
 template <int KL, int VL>
 hipError_t launch_decode_mfma_fmt(const Layout &L, const __half *q, long long T, long long nq, int n_sink,
-                                  int n_splits, int n_new, const __half *knew, const __half *vnew, long long te,
+                                  DecodePlan shape, int n_new, const __half *knew, const __half *vnew, long long te,
                                   MergeOut mo, hipStream_t s) {
+  const int n_splits = shape.n_splits, passes = shape.passes;
   if (T <= 0 || nq < 0 || nq > SKVQ_MAX_QUANT_TOKENS || T - nq > 0x7fffffff || n_splits < 1 ||
       n_splits > SKVQ_MAX_SPLITS)
     return hipErrorInvalidValue;
   if (n_new < 1 || n_new > SKVQ_MAX_NEW_TOKENS || L.R > 8) return hipErrorInvalidValue;
   const int n_rows = n_new * L.R;
-  const int passes = decode_passes(L, n_rows), per_group = rows_per_workgroup(L, n_rows);
-  const int rk = per_group == kWideRows ? kWideRows : n_rows == 1 ? 1 : n_rows == 2 ? 2 : 4;
+  const bool wide = shape.rows == kWideRows;
+  if ((!wide && shape.rows != kNarrowRows) || passes != decode_passes(n_rows, shape.rows)) return hipErrorInvalidValue;
+  if (wide && (L.NG > 2 || L.uneq)) return hipErrorInvalidValue;
+  const int rk = wide ? kWideRows : n_rows == 1 ? 1 : n_rows == 2 ? 2 : kNarrowRows;
   if ((knew != nullptr) != (vnew != nullptr) || (knew && (passes != 1 || n_new != 1))) return hipErrorInvalidValue;
   if (knew && T - 1 >= L.W && (te < 0 || te >= L.Tcap || te != nq - 1)) return hipErrorInvalidValue;
   if ((long long)L.Hk * passes > 65535) return hipErrorInvalidValue;
@@ -74,6 +77,6 @@ hipError_t launch_decode_mfma_fmt(const Layout &L, const __half *q, long long T,
 }
 
 template hipError_t launch_decode_mfma_fmt<SKVQ_KL, SKVQ_VL>(const Layout &, const __half *, long long, long long,
-                                                             int, int, int, const __half *, const __half *, long long,
+                                                             int, DecodePlan, int, const __half *, const __half *, long long,
                                                              MergeOut, hipStream_t);
 }  // namespace skvq

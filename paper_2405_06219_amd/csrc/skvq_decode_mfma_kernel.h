@@ -465,10 +465,10 @@ __global__ __launch_bounds__(kThreads, 2) void decode_mfma_kernel(Layout L, cons
                                                                   const __half *__restrict__ knew,
                                                                   const __half *__restrict__ vnew, long long te,
                                                                   ChunkPlan plan, MergeOut mo) {
-  // grid (n_splits, Hk * passes, B): R is the number of query heads one workgroup serves; where
-  // decode_wide_kernel does not exist (four groups per head, unequal ones) a kv head with more than
-  // four rows is served by `passes` workgroups per chunk, each with R of its rows (the last one
-  // possibly with fewer: the missing rows are computed with a zero query and not stored).
+  // grid (n_splits, Hk * passes, B): R is the number of query heads one workgroup serves; a kv head
+  // with more than four rows that does not go to decode_wide_kernel (plan_decode) is served by
+  // `passes` workgroups per chunk, each with R of its rows (the last one possibly with fewer: the
+  // missing rows are computed with a zero query and not stored).
   //   With n_new > 1 query tokens per sequence (the last n_new cached tokens are theirs) the rows
   // of a kv head are its L.R query heads times the n_new tokens, row x = token x / L.R, head
   // x % L.R; query token j does not see the fp16 tokens after its own.

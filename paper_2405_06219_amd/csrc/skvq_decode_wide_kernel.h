@@ -1,5 +1,5 @@
 // Matrix-core kernel of skvq_decode_attention for more than four rows per kv head (query heads of the
-// kv head x query tokens): up to sixteen rows per workgroup.  The cache formats, the operands made of
+// kv head x query tokens) over long caches: up to sixteen rows per workgroup.  The cache formats, the operands made of
 // codes, the grid, the shares, the fp16 slices and the partials are those of
 // skvq_decode_mfma_kernel.h; what differs is the shape of the products:
 //
@@ -21,6 +21,8 @@
 //   2-bit keys, 3-level values, one group, 131072 tokens: 4 query tokens 51.4 -> 27.8, 2: 31.5 -> 25.7
 //   the same in two groups with FP8 (scale, zero), 100003 tokens, 4 query tokens: 44.2 -> 29.8
 //   4-bit, two groups, 60000 tokens, 4 query tokens: 37.7 -> 28.4
+// At short caches, and where the compute units have room for the other workgroups, four rows a workgroup are
+// faster (up to twice: plan_decode in skvq_api.hip chooses).
 #pragma once
 #include "skvq_decode_mfma_kernel.h"
 
@@ -28,7 +30,7 @@ namespace skvq {
 namespace {
 
 constexpr int kRowQuad = 4;                      // rows that one wavefront serves in a fp16 slice
-constexpr int kWideTeams = kNW / (kWideRows / kRowQuad);  // wavefronts per row quad
+static_assert(kWideTeams == kNW / (kWideRows / kRowQuad), "wavefronts per row quad");
 constexpr int kWideStride = kD + 4;  // floats per staged output row: sixteen rows on different banks
 constexpr int kTokStride = 80;       // (factor pairs of) the 64 tokens of a tile: two of padding after every
                                      // eight, so that the four lane groups read different banks

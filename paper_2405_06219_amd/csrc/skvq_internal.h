@@ -113,48 +113,49 @@ hipError_t launch_channel_stats(const __half *x, float *part, int B, int Hk, lon
                                 hipStream_t s);
 int reorder_channels(const float *stats, int Hk, int G, int gran, int max_iter, int32_t *perm, int32_t *bounds);
 
+constexpr int kMfmaWavesPerGroup = 8;  // wavefronts per workgroup of the matrix-core kernels
+
+// How a decode call is spread over workgroups: the packed region of every kv head in n_splits chunks,
+// each read by `passes` workgroups of `rows` rows (a kv head's rows: query heads x query tokens).
+// rows is kNarrowRows (decode_mfma_kernel: up to four) or kWideRows (decode_wide_kernel, which exists for
+// one and two equal groups per head only).
+constexpr int kNarrowRows = 4, kWideRows = 16;
+constexpr int kWideTeams = 2;  // wide: wavefronts of a workgroup that share four rows' fp16 tokens
+struct DecodePlan {
+  int n_splits, rows, passes;
+};
+inline int decode_passes(int n_rows, int rows_per_workgroup) { return (n_rows + rows_per_workgroup - 1) / rows_per_workgroup; }
+
 // decode kernels (skvq_decode.hip)
-// n_splits: chunks of the packed region per kv head (>= 1 when n_quant > 0).
+// plan: n_splits >= 1 when n_quant > 0.
 // n_new: query tokens per sequence (q, out: [B][n_new][Hq][D]); the last n_new cached tokens are theirs.
 // n_kept: tokens kept in fp16 by the filter rules, of the T cached ones.
 // k_new, v_new (both or neither): the newest of the T tokens is not in the cache yet, the chunk
 // kernel appends it on the way (see append_fusable); the token that leaves the window, if any, is
 // packed (n_kept is the same before and after).
 hipError_t launch_decode(const Layout &L, const __half *q, float *out_f32, __half *out_f16,
-                         long long T, long long n_kept, int n_splits, int n_new, hipStream_t s,
+                         long long T, long long n_kept, DecodePlan plan, int n_new, hipStream_t s,
                          const __half *k_new = nullptr, const __half *v_new = nullptr);
 
 // Matrix-core chunk kernel (skvq_decode_mfma.hip): packed chunks and the fp16 tokens (n_sink sink
 // rows, then the window's T - nq - n_sink ring tokens); writes partials 0..n_splits-1 (n_splits
 // >= 1 even when nothing is packed yet).
-// A kv head's rows (query heads x query tokens) are served four to a workgroup, or sixteen by the kernel
-// for more than four rows, which exists for one and two equal groups per head (with four groups or
-// unequal ones its factors and operands do not fit the registers: it spills in the tile loop and is no
-// faster than the workgroups of four rows that it would replace).
-constexpr int kWideRows = 16;
-inline int rows_per_workgroup(const Layout &L, int n_rows) { return n_rows > 4 && L.NG <= 2 && !L.uneq ? kWideRows : 4; }
-inline int decode_passes(const Layout &L, int n_rows) {  // workgroups per chunk
-  const int rows = rows_per_workgroup(L, n_rows);
-  return (n_rows + rows - 1) / rows;
-}
 // te: with knew / vnew, the packed row of the token that leaves the window.
 hipError_t launch_decode_mfma(const Layout &L, const __half *q, long long T, long long nq, int n_sink,
-                              int n_splits, int n_new, const __half *knew, const __half *vnew, long long te,
+                              DecodePlan plan, int n_new, const __half *knew, const __half *vnew, long long te,
                               MergeOut mo, hipStream_t s);
-// Whether the decode of T_after tokens (one query token) may append the newest token itself: one
-// workgroup per chunk, and the token that leaves the
-// window, if any, is packed rather than copied to a sink row (a sink row has other readers in
-// the same launch).
 constexpr int kMaxMergeLast = 8;  // chunks per kv head up to which the last workgroup combines them
-// (the kernel for more than four rows leaves its partials to merge_kernel)
+// (the kernel for more than four rows, and several workgroups per chunk, leave their partials to merge_kernel)
 inline bool merges_in_launch(const Layout &L, int n_splits, int n_new) {
-  return n_splits <= kMaxMergeLast && L.R * n_new <= 4;
+  return n_splits <= kMaxMergeLast && L.R * n_new <= kNarrowRows;
 }
 constexpr int kMinSplitsForOneLaunch = 4;  // chunks per kv head from which the one-launch step is used whatever their number
-inline bool append_fusable(const Layout &L, long long T_after, bool leaving_token_is_kept) {
+// Whether the decode of T_after tokens (one query token) may append the newest token itself: one
+// workgroup per chunk, and the token that leaves the window, if any, is packed rather than copied to a
+// sink row (a sink row has other readers in the same launch).
+inline bool append_fusable(const Layout &L, const DecodePlan &plan, long long T_after, bool leaving_token_is_kept) {
   const long long T = T_after - 1;  // tokens cached before
-  return decode_passes(L, L.R) == 1 && !(T >= L.W && leaving_token_is_kept);
+  return plan.passes == 1 && !(T >= L.W && leaving_token_is_kept);
 }
-constexpr int kMfmaWavesPerGroup = 8;  // wavefronts per workgroup of the matrix-core kernel
 
 }  // namespace skvq

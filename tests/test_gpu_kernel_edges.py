@@ -57,9 +57,9 @@ def test_step_of_few_workgroups(batch, heads, context, splits):
     pair.assert_buffers_equal()
 
 
-# more than four rows per kv head in one workgroup: 5 .. 16 and 64 rows, every code format with one and two
-# groups, packed regions of none, one and a few tokens around a tile's and a V block's edge, sinks, one and
-# more chunks
+# more than four rows per kv head, few kv heads (workgroups of four rows): 5 .. 16 and 64 rows, every code
+# format with one and two groups, packed regions of none, one and a few tokens around a tile's and a V block's
+# edge, sinks, one and more chunks
 WIDE_CASES = [
     # q heads, kv heads, query tokens, context, batch, K bits, V bits, group, meta, sinks, window, chunks
     (5, 1, 1, 16 + 1, 1, 2.0, 1.5, 128, "f32", 0, 16, 0),
@@ -78,8 +78,31 @@ WIDE_CASES = [
     (5, 1, 2, 12, 1, 4.0, 4.0, 128, "f32", 0, 16, 0),   # nothing packed
 ]
 
+# ... and with more (sequence, kv head) pairs than the compute units have room for at four rows a workgroup
+# (decode_wide_kernel, sixteen rows a workgroup): 5 .. 16 rows in one pass, 20 and 24 in two (the second one
+# ragged), the same edges and formats
+MANY_HEADS = [
+    (5, 1, 1, 16 + 1, 140, 2.0, 1.5, 128, "f32", 0, 16, 0),
+    (16, 2, 2, 16 + 63, 70, 2.0, 1.5, 128, "e4m3", 0, 16, 0),
+    (6, 2, 5, 16 + 64, 70, 2.0, 1.5, 64, "f32", 0, 16, 1),
+    (10, 2, 4, 16 + 65, 68, 2.0, 1.5, 128, "f32", 0, 16, 0),     # 20 rows
+    (12, 4, 8, 300, 35, 2.0, 1.5, 64, "e4m3", 5, 32, 0),         # 24 rows
+    (10, 2, 4, 700, 24, 2.0, 2.0, 128, "f16", 0, 16, 3),         # 20 rows, three chunks
+    (6, 2, 8, 16 + 70, 68, 3.0, 3.0, 128, "f32", 1, 16, 0),      # 24 rows
+    (8, 2, 4, 700, 24, 2.0, 2.0, 64, "e4m3", 5, 32, 3),
+    (4, 1, 4, 33 + 95, 140, 2.0, 4.0, 64, "f16", 0, 33, 0),
+    (8, 1, 2, 400, 70, 2.0, 4.0, 128, "e4m3", 0, 128, 2),
+    (16, 2, 2, 420, 70, 3.0, 3.0, 64, "e4m3", 0, 64, 0),
+    (8, 1, 1, 300, 140, 4.0, 1.5, 128, "f16", 0, 33, 0),
+    (8, 4, 8, 600, 35, 4.0, 1.5, 64, "f32", 3, 128, 0),
+    (5, 1, 3, 300, 140, 4.0, 2.0, 128, "f32", 0, 64, 0),
+    (16, 4, 4, 300, 35, 4.0, 2.0, 64, "f16", 0, 64, 0),
+    (8, 2, 4, 900, 24, 4.0, 4.0, 64, "e4m3", 5, 128, 5),
+    (5, 1, 2, 12, 140, 4.0, 4.0, 128, "f32", 0, 16, 0),          # nothing packed
+]
 
-@pytest.mark.parametrize("case", WIDE_CASES, ids=lambda c: "-".join(map(str, c)))
+
+@pytest.mark.parametrize("case", WIDE_CASES + MANY_HEADS, ids=lambda c: "-".join(map(str, c)))
 def test_many_rows_per_kv_head(case):
     from paper_2405_06219_amd import synth
     print("case", case, flush=True)
@@ -161,3 +184,36 @@ def test_chunks_combined_in_the_launch_replayed():
         torch.cuda.synchronize()
         assert np.abs(out.cpu().numpy() - eager).max() <= 1e-5   # the wavefronts' sums in another order
         assert np.abs(pair.gpu.skvq_decode_attention(qd).cpu().numpy() - eager).max() <= 1e-5
+
+
+def decode_kernels(call):
+    """Names of the library's kernels that the call launches."""
+    from torch.profiler import ProfilerActivity, profile
+    call()
+    torch.cuda.synchronize()
+    with profile(activities=[ProfilerActivity.CUDA]) as prof:
+        call()
+        torch.cuda.synchronize()
+    known = ("decode_mfma_kernel", "decode_wide_kernel", "merge_kernel", "append_kernel")
+    return [k for e in prof.events() for k in known if k in e.name]
+
+
+# More than four rows per kv head: workgroups of sixteen rows only where those of four do not find room (short
+# caches: 13 us with four rows a workgroup, 26 with sixteen, 8 q / 1 kv x 1000 tokens)
+@pytest.mark.parametrize("kind,batch,hq,hk,n_new,context,window,wide", [
+    ("decode", 1, 8, 1, 1, 1000, 128, False), ("step", 1, 8, 1, 1, 300, 128, False), ("multi", 1, 8, 2, 4, 4000, 128, False),
+    ("decode", 8, 64, 8, 1, 600, 128, False), ("multi", 1, 8, 2, 4, 12, 16, False),
+    ("multi", 70, 8, 2, 4, 100, 16, True), ("decode", 140, 8, 1, 1, 300, 16, True), ("step", 140, 8, 1, 1, 300, 16, True)])
+def test_rows_per_workgroup(kind, batch, hq, hk, n_new, context, window, wide):
+    from paper_2405_06219_amd import synth
+    print("case", kind, batch, hq, hk, n_new, context, window, flush=True)
+    w = synth.Workload("route", batch, hq, hk, context, 1.5, group_size=128, window=window, seed=6)
+    pair, k, v, q = P.make_pair(w, extra_tokens=8, max_new_tokens=n_new)
+    pair.prefill(k, v)
+    dev = pair.device
+    q1, qn = torch.from_numpy(q).to(dev), torch.zeros((batch, n_new, hq, D), dtype=torch.float16, device=dev)
+    kn, vn = (torch.from_numpy(x).to(dev) for x in synth.make_new_token(w, 0))
+    names = decode_kernels({"decode": lambda: pair.gpu.skvq_decode_attention(q1),
+                            "multi": lambda: pair.gpu.skvq_decode_attention_multi(qn),
+                            "step": lambda: pair.gpu.skvq_append_decode_attention(kn, vn, q1)}[kind])
+    assert ("decode_wide_kernel" in names) == wide and ("decode_mfma_kernel" in names) != wide, names
