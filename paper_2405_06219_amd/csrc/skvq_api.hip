@@ -134,8 +134,9 @@ int append_with(skvq_cache *c, const void *k_new, const void *v_new, bool keep, 
   return SKVQ_OK;
 }
 
-// Chunks per kv head where `rows` rows go to a workgroup.
-int choose_splits(const skvq_cache *c, long long n_quant, int n_new, int rows) {
+// Chunks per kv head for n_quant packed and n_fp fp16 tokens, where `rows` rows go to a workgroup.
+// step: see plan_decode.
+int choose_splits(const skvq_cache *c, long long n_quant, long long n_fp, int n_new, int rows, bool step) {
   if (n_quant <= 0) return 0;
   const long long tiles = (n_quant + 63) / 64;  // a split is a whole number of 64-token tiles
   long long s;
@@ -146,11 +147,22 @@ int choose_splits(const skvq_cache *c, long long n_quant, int n_new, int rows) {
     // workgroup should have at least two tiles where the partials take a second launch to combine.  Up
     // to kMaxMergeLast chunks they do not, and a short cache is read faster in more, shorter chunks
     // (one, four and eight chunks, us per step: 1 x 4 heads x 2048 tokens 12.3 / 10.3 / 9.0, 4 x 800
-    // 9.8 / 9.3 / 8.0, 32 q / 8 kv x 3000 4-bit 21.2 / 13.7 / 11.0).
-    const long long heads = (long long)c->L.B * c->L.Hk * decode_passes(c->L.R * n_new, rows);
+    // 9.8 / 9.3 / 8.0, 32 q / 8 kv x 3000 4-bit 21.2 / 13.7 / 11.0) -- once there is enough to share:
+    // combining takes 1.5 us.  128 counts for a tile, 3 for a (row, fp16 token) pair, and chunks are cut from
+    // ten tiles' worth on; without an append to shorten, where the chunks fill a quarter of the compute units
+    // (their tickets and partials then meet in memory), 8 for a pair and from twenty tiles' worth on.  One and
+    // eight chunks, us per call: 1 head x 172 tokens, window 128, 6.9 / 7.9, x 684 8.3 / 7.4; 32 heads, window 4,
+    // 12 tiles 7.7 / 8.8, 31 tiles 10.2 / 8.9, as steps 24 heads, window 128, 10 tiles 10.9 / 9.5.  Over 1080 calls
+    // of 2 .. 31 tiles, 1 .. 4 rows, windows of 4 .. 512: 0.5 % longer on average than with the best number of
+    // chunks, at most 4.6 % longer than in one.
+    const int n_rows = c->L.R * n_new;
+    const long long heads = (long long)c->L.B * c->L.Hk * decode_passes(n_rows, rows);
     s = c->n_cus / heads;
     long long cap = tiles / (2 * kMfmaWavesPerGroup);
-    if (merges_in_launch(c->L, kMaxMergeLast, n_new) && cap < kMaxMergeLast) cap = kMaxMergeLast;
+    const bool crowded = !step && kMaxMergeLast * heads > c->n_cus / 4;
+    const long long work = 128 * tiles + (crowded ? 8 : 3) * n_rows * n_fp;
+    if (merges_in_launch(c->L, kMaxMergeLast, n_new) && cap < kMaxMergeLast && work >= 128 * (crowded ? 20 : 10))
+      cap = kMaxMergeLast;
     if (s > cap) s = cap;
   }
   if (s > SKVQ_MAX_SPLITS) s = SKVQ_MAX_SPLITS;
@@ -197,9 +209,9 @@ bool step_is_one_launch(const skvq_cache *c, const DecodePlan &p) {
 DecodePlan plan_decode(const skvq_cache *c, long long n_quant, long long n_fp, int n_new, bool step = false) {
   const Layout &L = c->L;
   const int n_rows = L.R * n_new;
-  DecodePlan narrow = {choose_splits(c, n_quant, n_new, kNarrowRows), kNarrowRows, decode_passes(n_rows, kNarrowRows)};
+  DecodePlan narrow = {choose_splits(c, n_quant, n_fp, n_new, kNarrowRows, step), kNarrowRows, decode_passes(n_rows, kNarrowRows)};
   if (n_rows <= kNarrowRows || L.NG > 2 || L.uneq) return narrow;
-  DecodePlan wide = {choose_splits(c, n_quant, n_new, kWideRows), kWideRows, decode_passes(n_rows, kWideRows)};
+  DecodePlan wide = {choose_splits(c, n_quant, n_fp, n_new, kWideRows, step), kWideRows, decode_passes(n_rows, kWideRows)};
   // workgroups of one chunk are n_splits apart in the grid: they share a chiplet's L2 where that is a
   // multiple of eight, else each of them has the chunk fetched again
   const int narrow_tile_ns = narrow.n_splits > 0 && narrow.n_splits % 8 == 0 ? 200 : 250;

@@ -217,3 +217,23 @@ def test_rows_per_workgroup(kind, batch, hq, hk, n_new, context, window, wide):
                             "multi": lambda: pair.gpu.skvq_decode_attention_multi(qn),
                             "step": lambda: pair.gpu.skvq_append_decode_attention(kn, vn, q1)}[kind])
     assert ("decode_wide_kernel" in names) == wide and ("decode_mfma_kernel" in names) != wide, names
+
+
+# The chunks that the library chooses, by the partials found in the workspace (one chunk leaves none): one where
+# there is little to share, up to eight combined in the launch, more beyond
+@pytest.mark.parametrize("hq,hk,context,window,chunks", [
+    (1, 1, 16 + 64 * 9, 16, 1), (4, 4, 128 + 64 * 5, 128, 1), (32, 32, 4 + 64 * 16, 4, 1),      # 1.0 .. 1.3 times as long in more
+    (4, 1, 128 + 64 * 3, 128, 3), (1, 1, 128 + 64 * 12, 128, 8), (4, 4, 16 + 64 * 31, 16, 8), (1, 1, 16 + 64 * 160, 16, 10)])
+def test_number_of_chunks(hq, hk, context, window, chunks):
+    from paper_2405_06219_amd import synth
+    print("case", hq, hk, context, window, chunks, flush=True)
+    w = synth.Workload("chunks", 1, hq, hk, context, 2.0, group_size=128, window=window, seed=12)
+    pair, k, v, q = P.make_pair(w)
+    pair.prefill(k, v)
+    space = pair.gpu.buffers["workspace"]
+    space.fill_(0xFF)
+    out, ref = pair.decode_both(q)
+    assert np.abs(out - ref).max() <= P.TOL
+    part = space.cpu().numpy().view(np.uint32).reshape(hq, -1, D + 4)
+    written = (part[:, :, 1] != 0xFFFFFFFF).sum(axis=1)
+    assert (written == (chunks if chunks > 1 else 0)).all(), written
