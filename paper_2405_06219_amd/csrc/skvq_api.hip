@@ -161,7 +161,7 @@ int choose_splits(const skvq_cache *c, long long n_quant, long long n_fp, int n_
     long long cap = tiles / (2 * kMfmaWavesPerGroup);
     const bool crowded = !step && kMaxMergeLast * heads > c->n_cus / 4;
     const long long work = 128 * tiles + (crowded ? 8 : 3) * n_rows * n_fp;
-    if (merges_in_launch(c->L, kMaxMergeLast, n_new) && cap < kMaxMergeLast && work >= 128 * (crowded ? 20 : 10))
+    if (can_merge_last(c->L, kMaxMergeLast, n_new) && cap < kMaxMergeLast && work >= 128 * (crowded ? 20 : 10))
       cap = kMaxMergeLast;
     if (s > cap) s = cap;
   }
@@ -209,9 +209,14 @@ bool step_is_one_launch(const skvq_cache *c, const DecodePlan &p) {
 DecodePlan plan_decode(const skvq_cache *c, long long n_quant, long long n_fp, int n_new, bool step = false) {
   const Layout &L = c->L;
   const int n_rows = L.R * n_new;
-  DecodePlan narrow = {choose_splits(c, n_quant, n_fp, n_new, kNarrowRows, step), kNarrowRows, decode_passes(n_rows, kNarrowRows)};
+  DecodePlan narrow = {choose_splits(c, n_quant, n_fp, n_new, kNarrowRows, step), kNarrowRows, decode_passes(n_rows, kNarrowRows), false};
+  // Combining in the launch pays while every workgroup has a compute unit to itself (always, unless the
+  // caller set the number of chunks): past that a workgroup waits for memory and its ticket while others wait
+  // for its compute unit.  Second launch and in the launch, us per call: 8 x 32 heads x 4000 tokens in eight
+  // chunks 47.1 / 57.5, 16 x 32 x 2000 in two 36.2 / 38.8, in eight 75.9 / 99.4.
+  narrow.merge_last = (long long)L.B * L.Hk * narrow.n_splits <= c->n_cus && can_merge_last(L, narrow.n_splits, n_new);
   if (n_rows <= kNarrowRows || L.NG > 2 || L.uneq) return narrow;
-  DecodePlan wide = {choose_splits(c, n_quant, n_fp, n_new, kWideRows, step), kWideRows, decode_passes(n_rows, kWideRows)};
+  DecodePlan wide = {choose_splits(c, n_quant, n_fp, n_new, kWideRows, step), kWideRows, decode_passes(n_rows, kWideRows), false};
   // workgroups of one chunk are n_splits apart in the grid: they share a chiplet's L2 where that is a
   // multiple of eight, else each of them has the chunk fetched again
   const int narrow_tile_ns = narrow.n_splits > 0 && narrow.n_splits % 8 == 0 ? 200 : 250;

@@ -113,7 +113,7 @@ hipError_t launch_decode(const Layout &L, const __half *q, float *out_f32, __hal
   MergeOut mo;
   mo.out_f32 = out_f32;
   mo.out_f16 = out_f16;
-  mo.mode = n_splits == 1 ? kMergeDirect : merges_in_launch(L, n_splits, n_new) ? kMergeLast : kMergeSeparate;
+  mo.mode = n_splits == 1 ? kMergeDirect : plan.merge_last && can_merge_last(L, n_splits, n_new) ? kMergeLast : kMergeSeparate;
   mo.tickets = L.tickets;
   hipError_t e = launch_decode_mfma(L, q, T, n.n_quant, (int)n.n_sink, plan, n_new, k_new, v_new, te, mo, s);
   if (e != hipSuccess || mo.mode != kMergeSeparate) return e;

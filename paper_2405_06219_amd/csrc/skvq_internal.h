@@ -123,6 +123,7 @@ constexpr int kNarrowRows = 4, kWideRows = 16;
 constexpr int kWideTeams = 2;  // wide: wavefronts of a workgroup that share four rows' fp16 tokens
 struct DecodePlan {
   int n_splits, rows, passes;
+  bool merge_last;  // two or more chunks are combined in the launch (merge_by_last)
 };
 inline int decode_passes(int n_rows, int rows_per_workgroup) { return (n_rows + rows_per_workgroup - 1) / rows_per_workgroup; }
 
@@ -146,7 +147,7 @@ hipError_t launch_decode_mfma(const Layout &L, const __half *q, long long T, lon
                               MergeOut mo, hipStream_t s);
 constexpr int kMaxMergeLast = 8;  // chunks per kv head up to which the last workgroup combines them
 // (the kernel for more than four rows, and several workgroups per chunk, leave their partials to merge_kernel)
-inline bool merges_in_launch(const Layout &L, int n_splits, int n_new) {
+inline bool can_merge_last(const Layout &L, int n_splits, int n_new) {
   return n_splits <= kMaxMergeLast && L.R * n_new <= kNarrowRows;
 }
 constexpr int kMinSplitsForOneLaunch = 4;  // chunks per kv head from which the one-launch step is used whatever their number

@@ -237,3 +237,19 @@ def test_number_of_chunks(hq, hk, context, window, chunks):
     part = space.cpu().numpy().view(np.uint32).reshape(hq, -1, D + 4)
     written = (part[:, :, 1] != 0xFFFFFFFF).sum(axis=1)
     assert (written == (chunks if chunks > 1 else 0)).all(), written
+
+
+# Chunks are combined in the launch up to eight, four rows, and a compute unit for every workgroup
+@pytest.mark.parametrize("batch,hq,hk,splits,merge", [(1, 4, 4, 8, False), (1, 4, 4, 9, True), (2, 64, 16, 8, False),
+                                                      (8, 32, 32, 2, True), (3, 32, 32, 4, True)])
+def test_where_chunks_are_combined(batch, hq, hk, splits, merge):
+    from paper_2405_06219_amd import synth
+    print("case", batch, hq, hk, splits, flush=True)
+    w = synth.Workload("where", batch, hq, hk, 16 + 64 * 9, 1.5, group_size=128, window=16, seed=3)
+    pair, k, v, q = P.make_pair(w)
+    pair.prefill(k, v)
+    pair.gpu.skvq_set_num_splits(splits)
+    out, ref = pair.decode_both(q)
+    assert np.abs(out - ref).max() <= P.TOL
+    qd = torch.from_numpy(q).to(pair.device)
+    assert ("merge_kernel" in decode_kernels(lambda: pair.gpu.skvq_decode_attention(qd))) == merge
