@@ -23,7 +23,10 @@
  *    counters live on the host and advance when a call is enqueued.
  *  - Every function returns a skvq_status (0 = ok, negative = error).  On
  *    error nothing is enqueued and no state changes.
- *  - Calls on one skvq_cache must not overlap (one stream, or ordered streams).
+ *  - Calls on one skvq_cache must not overlap (one stream, or ordered streams).  After calls that did,
+ *    every result is unspecified until a prompt of at least one token is quantized again (a decode call
+ *    counts its workgroups in device memory of the cache, from zero to zero; skvq_create and
+ *    skvq_prefill_quantize* write the zeros).
  *  - Inputs must be finite fp16; the result for inf/nan input is unspecified.
  *
  * Numerics contract: codes and (scale, zero) are a pure function of the
@@ -232,8 +235,9 @@ int skvq_decode_attention(skvq_cache *cache, const void *q, void *out_f32, void 
  * skvq_create.  SKVQ_ERR_UNSUPPORTED if batch * n_q_heads > SKVQ_STATIC_MAX_ROWS (nothing is
  * launched); SKVQ_ERR_HIP if that lookup had failed.  Every cache on one GPU shares the array:
  * calls of this entry point that overlap on one GPU (different streams) race -- keep them on one
- * stream or order the streams.  Nothing in the array has to start at zero (every partial that the
- * merge reads is written by the same call first), so it is never cleared. */
+ * stream or order the streams.  Nothing in the array has to start at zero (every partial that is
+ * combined is written by the same call first), so it is never cleared; the counters that the call does
+ * rely on are the cache's own. */
 #define SKVQ_STATIC_MAX_ROWS 64
 int skvq_decode_attention_static(skvq_cache *cache, const void *q, void *out_f32, void *out_f16,
                                  void *hip_stream);

@@ -48,7 +48,7 @@ struct Layout {
   float *workspace;
   const int *perm_k, *perm_v;    // device copies [Hk][D]
   const float *clip_k, *clip_v;  // device copies [Hk][NG]
-  int *tickets;                  // device [B][Hk], see MergeOut
+  int *tickets;                  // device [2][B][Hk], see MergeOut; the second half for the static scratch's calls
 };
 
 // Where the chunk partials of a decode call are combined.
@@ -61,7 +61,8 @@ struct MergeOut {
   float *out_f32;
   __half *out_f16;  // or null
   int mode;         // MergeMode
-  int *tickets;     // kMergeLast: one counter per (sequence, kv head), zero before and after a launch
+  int *tickets;     // kMergeLast: one counter per (sequence, kv head), zero before and after a launch (prefill_kernel
+                    // writes the zeros again)
 };
 
 // Where the T cached tokens of a sequence live (Section 3.2 with the attention-sink rule): the
