@@ -11,9 +11,9 @@
 namespace skvq {
 
 // Two floats -> FP8 E4M3 (bias 7, largest finite value 448): nearest, ties to even, saturating (a NaN
-// is 448); the first in the low byte.  One conversion instruction on values that its saturation mode does
-// not concern; for every one of the 2^32 floats it gives the number that rounding with integer
-// arithmetic does, which takes forty instructions per pair.
+// of either sign, which finite inputs do not lead to, is 448); the first in the low byte.  One conversion
+// instruction on values that its saturation mode does not concern; for every float that is no NaN it gives
+// the number that rounding with integer arithmetic does, which takes forty instructions per pair.
 __device__ __forceinline__ unsigned e4m3_pair(float a, float b) {
   return (unsigned)__builtin_amdgcn_cvt_pk_fp8_f32(fmaxf(fminf(a, 448.0f), -448.0f), fmaxf(fminf(b, 448.0f), -448.0f),
                                                    0, false) & 0xffffu;

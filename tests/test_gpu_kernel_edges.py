@@ -165,7 +165,8 @@ def test_chunks_combined_in_the_launch(hq, hk, n_new, context, batch, splits):
 
 
 def test_chunks_combined_in_the_launch_replayed():
-    """The counters of a captured call are as they were after every replay (eager calls in between)."""
+    """A captured call replayed with another query each time, eager calls in between: bit for bit the eager result.
+    The workspace holds NaN patterns before each replay, so a partial read before it was written would show."""
     from paper_2405_06219_amd import synth
     w = synth.Workload("replay", 1, 4, 2, 900, 1.5, group_size=128, seed=8)
     pair, k, v, q = P.make_pair(w)
@@ -173,17 +174,20 @@ def test_chunks_combined_in_the_launch_replayed():
     pair.gpu.skvq_set_num_splits(6)
     qd = torch.from_numpy(q).to(pair.device)
     out = torch.empty(q.shape, dtype=torch.float32, device=pair.device)
-    eager = pair.gpu.skvq_decode_attention(qd).cpu().numpy()
-    assert np.abs(eager - pair.ref.decode(q)).max() <= P.TOL
     graph = torch.cuda.CUDAGraph()
     with torch.cuda.graph(graph):
         pair.gpu.skvq_decode_attention(qd, out_f32=out)
-    for _ in range(4):
+    rng = np.random.default_rng(5)
+    for _ in range(5):
+        new = rng.standard_normal(q.shape).astype(np.float16)
+        qd.copy_(torch.from_numpy(new))
+        eager = pair.gpu.skvq_decode_attention(qd).cpu().numpy()
+        assert np.abs(eager - pair.ref.decode(new)).max() <= P.TOL
         out.zero_()
+        pair.gpu.buffers["workspace"].fill_(0xFF)
         graph.replay()
         torch.cuda.synchronize()
-        assert np.abs(out.cpu().numpy() - eager).max() <= 1e-5   # the wavefronts' sums in another order
-        assert np.abs(pair.gpu.skvq_decode_attention(qd).cpu().numpy() - eager).max() <= 1e-5
+        assert np.array_equal(out.cpu().numpy(), eager)
 
 
 def decode_kernels(call):
@@ -253,3 +257,103 @@ def test_where_chunks_are_combined(batch, hq, hk, splits, merge):
     assert np.abs(out - ref).max() <= P.TOL
     qd = torch.from_numpy(q).to(pair.device)
     assert ("merge_kernel" in decode_kernels(lambda: pair.gpu.skvq_decode_attention(qd))) == merge
+
+
+# Steps and merged chunks of 5 .. 8 query heads per kv head in formats without the sixteen-row kernel (four groups,
+# unequal groups): several workgroups per chunk, the append in a launch of its own
+@pytest.mark.parametrize("hq,hk,k_bits,v_bits,group,bounds,splits", [
+    (8, 1, 2.0, 1.5, 32, None, 4), (6, 1, 4.0, 4.0, 32, None, 0), (10, 2, 2.0, 1.5, 64, [0, 32, 128], 5),
+    (7, 1, 3.0, 3.0, 64, [0, 96, 128], 9)])
+def test_several_workgroups_per_chunk(hq, hk, k_bits, v_bits, group, bounds, splits):
+    from paper_2405_06219_amd import synth
+    print("case", hq, hk, k_bits, v_bits, group, bounds, splits, flush=True)
+    w = synth.Workload("several", 1, hq, hk, 16 + 64 * 9 + 60, v_bits, group_size=group, window=16, k_bits=k_bits, seed=23)
+    pair, k, v, q = P.make_pair(w, extra_tokens=10, meta="e4m3", group_bounds=bounds)
+    pair.prefill(k, v)
+    pair.gpu.skvq_set_num_splits(splits)
+    out, ref = pair.decode_both(q)
+    assert np.abs(out - ref).max() <= P.TOL
+    for s in range(8):   # across a tile's edge
+        out, ref = pair.append_decode_both(*synth.make_new_token(w, s), q)
+        assert np.abs(out - ref).max() <= P.TOL, s
+    pair.assert_buffers_equal()
+    qd = torch.from_numpy(q).to(pair.device)
+    names = decode_kernels(lambda: pair.gpu.skvq_decode_attention(qd))
+    assert "decode_mfma_kernel" in names and ("merge_kernel" in names) == (splits > 1), names   # (one chunk of ten tiles by itself)
+
+
+# The append inside the sixteen-row launch where the chunk that appends holds fewer tiles than the others (48 tiles
+# a chunk and more), across a V block's and a tile's edge
+@pytest.mark.parametrize("k_bits,v_bits,group", [(2.0, 1.5, 128), (4.0, 4.0, 64)])
+def test_many_rows_step_with_a_shorter_last_chunk(k_bits, v_bits, group):
+    from paper_2405_06219_amd import synth
+    print("case", k_bits, v_bits, group, flush=True)
+    w = synth.Workload("short", 13, 25, 5, 16 + 64 * 97 - 4, v_bits, group_size=group, window=16, k_bits=k_bits, seed=41)
+    pair, k, v, q = P.make_pair(w, extra_tokens=10)
+    pair.prefill(k, v)
+    pair.gpu.skvq_set_num_splits(2)
+    for s in range(6):
+        out, ref = pair.append_decode_both(*synth.make_new_token(w, s), q)
+        assert np.abs(out - ref).max() <= P.TOL, s
+    pair.assert_buffers_equal()
+    kn, vn = (torch.from_numpy(x).to(pair.device) for x in synth.make_new_token(w, 0))
+    qd = torch.from_numpy(q).to(pair.device)
+    names = decode_kernels(lambda: pair.gpu.skvq_append_decode_attention(kn, vn, qd))
+    assert "decode_wide_kernel" in names and "append_kernel" not in names, names
+
+
+# The sixteen-row kernel with scores that peak (its reference moves) while the value scales rise by decades from
+# tile to tile (its weights are scaled again), four query tokens
+@pytest.mark.parametrize("k_bits,v_bits,group,meta", [(2.0, 1.5, 128, "f32"), (2.0, 2.0, 64, "f32"), (4.0, 4.0, 64, "f16")])
+def test_many_rows_peaked_softmax_and_rising_values(k_bits, v_bits, group, meta):
+    from paper_2405_06219_amd import synth
+    print("case", k_bits, v_bits, group, meta, flush=True)
+    n_new = 4
+    w = synth.Workload("rise", 33, 8, 2, 16 + 64 * 40, v_bits, group_size=group, window=16, k_bits=k_bits, seed=52)
+    k, v = synth.make_kv(w)
+    rise = 10.0 ** np.linspace(-4.0, 0.0, w.context)      # per wavefront five tiles: several decades between them
+    v = (v / np.abs(v.astype(np.float32)).max() * rise[None, None, :, None]).astype(np.float16)
+    pk, pv = synth.make_permutations(w, k, v)
+    pair = P.Pair(w, w.context + 8, pk, pv, *synth.make_clip(w), sm_scale=0.3, meta=meta, max_new_tokens=n_new)
+    pair.prefill(k, v)
+    q = np.random.default_rng(9).standard_normal((w.batch, n_new, 8, D)).astype(np.float16)
+    qd = torch.from_numpy(q).to(pair.device)
+    out = pair.gpu.skvq_decode_attention_multi(qd).cpu().numpy()
+    ref = pair.ref.decode_multi(q)
+    assert np.abs(out - ref).max() <= P.TOL
+    # and relative to each row, whose weight may lie on tokens of any decade: scores of up to 2^7 in the exp2 domain, sums of
+    # 128 products truncated at 2^-23 of the sum, give weights off by up to 128 * 2^-23 * 2^7 * ln 2 = 1.4e-3
+    rel = np.linalg.norm(out - ref, axis=-1) / np.linalg.norm(ref, axis=-1)
+    print("largest relative error of a row %.2e" % rel.max(), flush=True)
+    assert rel.max() <= 1.4e-3
+    assert "decode_wide_kernel" in decode_kernels(lambda: pair.gpu.skvq_decode_attention_multi(qd))
+
+
+def test_fp8_pairs_of_every_fp16_number():
+    """Scale and zero in FP8 from every finite fp16 number x: rows of x and zeros (zero = alpha x, or 0; scale = alpha |x| / 3),
+    three alphas, by the prompt quantizer and (the last rows) by appends; ties, subnormals, saturation, both zeros."""
+    from paper_2405_06219_amd import binding as Bd
+    from oracle import skvq_oracle as O
+    x = np.arange(1 << 16, dtype=np.uint16).view(np.float16)
+    x = x[np.isfinite(x)]
+    n, window, tail = len(x), 64, 40
+    k = np.zeros((1, 3, n + window, D), np.float16)
+    k[:, :, :n, 5] = x
+    v = np.zeros_like(k)
+    v[:, :, :n, 7] = x[::-1]
+    perm = np.tile(np.arange(D, dtype=np.int32), (3, 1))
+    clip = np.array([[1.0], [0.95], [0.37]], np.float32)
+    ref = O.OracleCache(1, 3, 3, 128, 2.0, window, n, perm, perm, clip, clip, fill=0, meta="e4m3")
+    gpu = Bd.SkvqCache(1, 3, 3, 128, 2.0, window, n, perm, perm, clip, clip, fill=0, meta="e4m3")
+    T = n + window - tail
+    assert ref.prefill(np.ascontiguousarray(k[:, :, :T]), np.ascontiguousarray(v[:, :, :T])) == 0
+    gpu.skvq_prefill_quantize(*(torch.from_numpy(np.ascontiguousarray(a[:, :, :T])).to("cuda:0") for a in (k, v)))
+    for t in range(T, n + window):
+        kn, vn = np.ascontiguousarray(k[:, :, t]), np.ascontiguousarray(v[:, :, t])
+        assert ref.append(kn, vn) == 0
+        gpu.skvq_quantize_append(torch.from_numpy(kn).to("cuda:0"), torch.from_numpy(vn).to("cuda:0"))
+    for name, g, r in zip(("k_codes", "v_codes", "k_meta", "v_meta", "k_win", "v_win"), gpu.host_arrays(), ref.arrays()):
+        g, r = np.asarray(g), np.asarray(r)
+        if g.dtype.itemsize == 2:
+            g, r = g.view(np.uint16), r.view(np.uint16)
+        assert np.array_equal(g, r), name

@@ -267,9 +267,10 @@ def test_decode_after_appends_and_peaked_softmax(P):
 
 # ---- one decode step as one call: the new token is appended inside the attention launch ----
 STEP_CASES = [
-    # (workload, cache options, forced chunks per kv head: from four on the step is one launch)
+    # (workload, cache options, forced chunks per kv head: the step is one launch where they are four or more, or find
+    # a compute unit each, one workgroup per chunk)
     (small("step_mha_t15", context=700), {}, 4),
-    (small("step_from_empty", context=0, window=16), {}, 0),            # ring fills, then the first evictions: two launches
+    (small("step_from_empty", context=0, window=16), {}, 0),            # ring fills, then the first evictions
     (small("step_gqa4_v2_g64", n_q_heads=8, n_kv_heads=2, group_size=64, v_bits=2.0, context=391, batch=2), {}, 4),
     (small("step_gqa2_k4v4_g32_w16", k_bits=4.0, v_bits=4.0, n_q_heads=4, n_kv_heads=2, group_size=32, context=333, window=16), {}, 5),
     (small("step_gqa3_k3v3", k_bits=3.0, v_bits=3.0, n_q_heads=6, n_kv_heads=2, context=450), {"meta": "f16"}, 6),
@@ -280,7 +281,7 @@ STEP_CASES = [
     (small("step_uneq_g32", n_q_heads=8, n_kv_heads=2, group_size=32, context=600),
      {"group_bounds": [0, 16, 32, 80, 128]}, 4),
     (small("step_long_b2", group_size=64, context=9000, batch=2), {}, 7),
-    (small("step_long_w33", window=33, context=5000, batch=3), {}, 2),   # two chunks: two launches
+    (small("step_long_w33", window=33, context=5000, batch=3), {}, 2),   # two chunks
     (small("step_long_short_last_chunk", n_q_heads=8, n_kv_heads=2, context=13000), {}, 4),  # the last chunk is the shorter one
     (small("step_long_k4v4_g64", k_bits=4.0, v_bits=4.0, n_q_heads=4, n_kv_heads=2, context=14000, group_size=64), {"meta": "f16"}, 4),
     (small("step_long_k3v3_g32", k_bits=3.0, v_bits=3.0, n_q_heads=6, n_kv_heads=2, context=13500, group_size=32), {"meta": "e4m3"}, 4),
