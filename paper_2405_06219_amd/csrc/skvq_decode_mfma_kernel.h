@@ -420,8 +420,8 @@ inline ChunkPlan plan_chunks(const Layout &L, long long T, long long nq, int n_s
 // one round trip, and writes the output.  No fence: those write back and invalidate whole L2 caches.
 // Up to kMaxMergeLast chunks this takes less than the second launch, us per step: 32 heads x 32768 tokens
 // (8 chunks) 20.9 -> 19.8, 8 x 8 kv heads x 6007 tokens 4-bit (4 chunks, four rows) with its prefill's
-// share 24.5 -> 23.4; with 12 or more chunks it takes longer (32 chunks, four rows, 131072 tokens: 21.5
-// -> 23.5), and merge_kernel combines them.
+// share 24.5 -> 23.4; the same 12 or more chunks take longer this way (32 chunks, four rows, 131072 tokens:
+// 21.5 -> 23.5), and merge_kernel combines them.
 template <int R>
 __device__ __forceinline__ void merge_by_last(const float *base, int *ticket, int n_splits, int tid,
                                               bool row_exists, int &shared, float *out_f32, __half *out_f16) {

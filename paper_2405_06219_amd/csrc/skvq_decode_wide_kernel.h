@@ -1,6 +1,6 @@
 // Matrix-core kernel of skvq_decode_attention for more than four rows per kv head (query heads of the
-// kv head x query tokens) over long caches: up to sixteen rows per workgroup.  The cache formats, the operands made of
-// codes, the grid, the shares, the fp16 slices and the partials are those of
+// kv head x query tokens) over long caches: up to sixteen rows per workgroup.  The cache formats, the
+// operands made of codes, the grid, the shares, the fp16 slices and the partials are those of
 // skvq_decode_mfma_kernel.h; what differs is the shape of the products:
 //
 //   QK   S[token][row] by v_mfma_f32_16x16x32_f16: A = sixteen key rows, B = the rows' reordered
@@ -23,6 +23,11 @@
 //   4-bit, two groups, 60000 tokens, 4 query tokens: 37.7 -> 28.4
 // At short caches, and where the compute units have room for the other workgroups, four rows a workgroup are
 // faster (up to twice: plan_decode in skvq_api.hip chooses).
+// All 256 registers are in use.  With one group per head the tile loop spills nothing, and four of the 21
+// instances five or six registers around it; with two groups every instance spills: 3 - 11 registers with 2-bit
+// keys and 2-bit or 3-level values, 9 - 21 with 4 bits on one side, 17 - 27 on both, 26 - 32 with 3 bits.  With
+// four groups or unequal ones it would be slower than the workgroups of four rows at any length (measured at
+// 131072 and 60000 tokens: 46 -> 88 and 52 -> 54 us a call), so it is not built for them.
 #pragma once
 #include "skvq_decode_mfma_kernel.h"
 
