@@ -178,7 +178,7 @@ long long decode_cost(const skvq_cache *c, const DecodePlan &p, long long n_quan
   const long long s = p.n_splits > 1 ? p.n_splits : 1, workgroups = (long long)c->L.B * c->L.Hk * p.passes * s;
   const long long waves = (workgroups + c->n_cus - 1) / c->n_cus;
   const long long tiles = ((n_quant + 63) / 64 + s - 1) / s, slices = ((n_fp + 3) / 4 + s * teams - 1) / (s * teams);
-  return waves * (4000 + 800 * slices + tile_ns * tiles) + (s > 1 ? 4000 + 50 * s : 0);
+  return waves * (5000 + 800 * slices + tile_ns * tiles) + (s > 1 ? 4000 + 60 * s : 0);
 }
 
 // Whether a decode step appends its new token inside the attention launch (append_fusable granted).
@@ -198,9 +198,9 @@ bool step_is_one_launch(const skvq_cache *c, const DecodePlan &p) {
 // decode_wide_kernel sixteen by sixteen, which takes longer to start, walks the fp16 tokens with two teams
 // of wavefronts instead of eight, and takes longer per tile (more so with two groups and 3 or 4 bits, where
 // it spills).  The wide kernel pays where the compute units have no room for the other workgroups and the
-// chunks are long: the costs of both are compared, with constants fitted to 3600 calls of every format, 5 ..
-// 64 rows, 1 .. 256 kv heads over the batch, 600 .. 160000 tokens, windows of 8 .. 1000 tokens (chosen against
-// the faster: 0.2 % longer on average, 12 % at most).  Narrow and wide, us per call: 8 q / 1 kv x 1000
+// chunks are long: the costs of both are compared, with constants fitted to 4000 calls of every format, 5 ..
+// 64 rows, 1 .. 256 kv heads over the batch, 300 .. 1000000 tokens, windows of 8 .. 1000 tokens (chosen against
+// the faster: 0.1 % longer on average, 10 % at most).  Narrow and wide, us per call: 8 q / 1 kv x 1000
 // tokens 12.9 / 26.3, x 16000 13.1 / 14.3; 32 q / 8 kv, four query tokens, x 4000 15.9 / 21.0, x 16000 16.1 /
 // 16.0, x 40000 23.0 / 17.1; 8 x 64 q / 8 kv x 4000 19.0 / 21.3, x 16000 35.6 / 29.0; 3-bit in two groups, two
 // query tokens, x 64000 27.7 / 41.9.
@@ -221,9 +221,9 @@ DecodePlan plan_decode(const skvq_cache *c, long long n_quant, long long n_fp, i
   // multiple of eight, else each of them has the chunk fetched again
   const int narrow_tile_ns = narrow.n_splits > 0 && narrow.n_splits % 8 == 0 ? 200 : 250;
   const bool two = L.NG == 2, three_bit = L.k_levels == 8, four_bit = L.k_levels == 16 && L.v_levels == 16;
-  const int wide_tile_ns = !two ? 340 : three_bit ? 550 : four_bit ? 400 : 350;
-  const int wide_more_ns = !two ? 0 : three_bit ? 6400 : four_bit ? 0 : 1600;  // start-up
-  constexpr int kAppendLaunchNs = 2000;
+  const int wide_tile_ns = !two ? 340 : three_bit ? 550 : four_bit ? 400 : 340;
+  const int wide_more_ns = !two ? 0 : three_bit ? 6400 : four_bit ? 0 : 3200;  // start-up
+  constexpr int kAppendLaunchNs = 3000;
   const long long a = decode_cost(c, narrow, n_quant, n_fp, kMfmaWavesPerGroup, narrow_tile_ns) +
                       (step && step_is_one_launch(c, wide) ? kAppendLaunchNs : 0);
   const long long b = decode_cost(c, wide, n_quant, n_fp, kWideTeams, wide_tile_ns) + wide_more_ns;

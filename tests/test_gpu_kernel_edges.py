@@ -115,8 +115,11 @@ def test_many_rows_per_kv_head(case):
     for s in range(n_new):
         pair.append(*synth.make_new_token(w, s))
     q = np.random.default_rng(context).standard_normal((batch, n_new, hq, D)).astype(np.float16)
-    out = pair.gpu.skvq_decode_attention_multi(torch.from_numpy(q).to(pair.device)).cpu().numpy()
+    qd = torch.from_numpy(q).to(pair.device)
+    out = pair.gpu.skvq_decode_attention_multi(qd).cpu().numpy()
     assert np.abs(out - pair.ref.decode_multi(q)).max() <= P.TOL
+    wide = "decode_wide_kernel" in decode_kernels(lambda: pair.gpu.skvq_decode_attention_multi(qd))
+    assert wide == (case in MANY_HEADS)
     for s in range(4):   # with more than four query heads per kv head: the step's append inside the launch
         out, ref = pair.append_decode_both(*synth.make_new_token(w, 50 + s), q1)
         assert np.abs(out - ref).max() <= P.TOL, s
