@@ -193,11 +193,11 @@ __global__ __launch_bounds__(256) void prefill_kernel(Layout L, const __half *__
                                                       long long nq, int n_kept,
                                                       const int *__restrict__ kept_ids_arg,
                                                       unsigned first_ring_block, int n_win) {
-  // a new prompt: the counters of its decode calls start at zero, whatever calls that overlapped, against the
-  // rules, left in them
-  if (blockIdx.x == 0 && threadIdx.x < 2)
-    L.tickets[((size_t)threadIdx.x * L.B + blockIdx.z) * L.Hk + blockIdx.y] = 0;
   if (blockIdx.x >= first_ring_block) {
+    // a new prompt: the counters of its decode calls start at zero, whatever calls that overlapped, against the
+    // rules, left in them (every prompt has rows to copy)
+    if (blockIdx.x == first_ring_block && threadIdx.x < 2)
+      L.tickets[((size_t)threadIdx.x * L.B + blockIdx.z) * L.Hk + blockIdx.y] = 0;
     const long long x = 4ll * (blockIdx.x - first_ring_block) + (threadIdx.x >> 6);  // fp16 row: window first, then kept
     if (x >= n_win + n_kept) return;
     const bool kept = x >= n_win;
