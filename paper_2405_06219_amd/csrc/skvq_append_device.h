@@ -159,26 +159,34 @@ __device__ __forceinline__ void store_k_row3(uint8_t *row, int lane, unsigned c0
   if ((lane & 15) == 0) reinterpret_cast<unsigned *>(row + 32)[lane >> 4] = h;
 }
 
-// Appends one token per (b, hk): wavefront 0 of the calling workgroup does K, wavefront 1 does V
-// (`wave` is the caller's wavefront index; every wavefront of the workgroup must call, the others
-// only keep the barriers).  T is the number of tokens cached before the call.  If the ring is full
+// Orders a wavefront's own LDS writes before its own later LDS reads (other lanes' data): the LDS serves one
+// wavefront's operations in order, the fences only keep the compiler from moving them.
+__device__ __forceinline__ void append_lds_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// Appends one token per (b, hk): wavefront 0 of the calling workgroup does K, wavefront 1 does V (`wave` is the
+// caller's wavefront index, 0 or 1; neither waits for the other).  T is the number of tokens cached before the
+// call, ring_slot = T % W.  If the ring is full
 // the slot's old token (number T - W) leaves the window first: with keep_row >= 0 (a filter rule
 // keeps it in full precision) it is copied to row W + keep_row of the fp16 buffers, else it is
-// quantized into packed row te.  rows: 2 x 128 halves and vcodes: 128 bytes of LDS.
+// quantized into packed row te; of that, V's sub-block is left in LDS for append_store_units.
+struct AppendScratch {
+  __half rows[2][kD];                   // the leaving token's K and V as they were ...
+  float read_back[2][kD];               // ... and as they read back
+  uint8_t vcodes[kD];
+  alignas(16) uint8_t units[16 * 32];   // the 16 units of the row's V sub-block
+};
 __device__ __forceinline__ void append_token(const Layout &L, const __half *__restrict__ knew,
-                                             const __half *__restrict__ vnew, long long T, int keep_row,
-                                             long long te, int hk, int b, int wave, int lane, __half (*rows)[kD],
-                                             uint8_t *vcodes) {
+                                             const __half *__restrict__ vnew, long long T, int ring_slot,
+                                             int keep_row, long long te, int hk, int b, int wave, int lane,
+                                             AppendScratch &lds) {
   const long long head = (long long)b * L.Hk + hk;
-  const long long slot = (head * (L.W + L.S) + T % L.W) * kD;
+  static_assert(kVBlock == 32, "the block of packed row te is te >> 5");
+  const long long slot = (head * (L.W + L.S) + ring_slot) * kD;
   const bool leaves = T >= L.W, evict = leaves && keep_row < 0;  // a token leaves the window; it is packed
-  if (wave >= 2) {  // (a larger workgroup: the other wavefronts only keep the two barriers below)
-    if (evict) {
-      __syncthreads();
-      __syncthreads();
-    }
-    return;
-  }
   __half *ring = wave ? L.v_win : L.k_win;
   const __half *fresh = (wave ? vnew : knew) + head * kD;
 
@@ -186,8 +194,8 @@ __device__ __forceinline__ void append_token(const Layout &L, const __half *__re
   // the slot's old token, the permutation, the clip factor, and what is already stored of the
   // V units the old token will be merged into.
   const __half2 fresh2 = reinterpret_cast<const __half2 *>(fresh)[lane];
-  const int s = evict ? (int)(te % kVBlock) : 0, kb = s >> 3, i = s & 7;
-  uint8_t *blk = L.v_codes + (head * L.n_vblocks + (evict ? te / kVBlock : 0)) * L.v_block_bytes;
+  const int s = evict ? (int)(te & (kVBlock - 1)) : 0, kb = s >> 3, i = s & 7;
+  uint8_t *blk = L.v_codes + (head * L.n_vblocks + (evict ? te >> 5 : 0)) * L.v_block_bytes;
   const bool uneq = L.uneq != 0;
   const unsigned gmap = uneq ? L.gmaps[hk] : 0u;
   const int grp = uneq ? tile_group(gmap, lane >> 3) : (2 * lane) / L.G;
@@ -226,13 +234,13 @@ __device__ __forceinline__ void append_token(const Layout &L, const __half *__re
   if (leaves && !evict)  // kept as it is
     reinterpret_cast<__half2 *>(ring + (head * (L.W + L.S) + L.W + keep_row) * kD)[lane] = old2;
   if (!evict) return;
-  reinterpret_cast<__half2 *>(rows[wave])[lane] = old2;
-  __syncthreads();
+  reinterpret_cast<__half2 *>(lds.rows[wave])[lane] = old2;
+  append_lds_sync();
 
   const float top = (float)((wave ? L.v_levels : L.k_levels) - 1);
   unsigned c0, c1;
   MetaPair mp;
-  encode_row(rows[wave], p0, p1, alpha, L.G, top, L.meta_fmt, uneq, gmap, lane, c0, c1, mp);
+  encode_row(lds.rows[wave], p0, p1, alpha, L.G, top, L.meta_fmt, uneq, gmap, lane, c0, c1, mp);
   void *meta = wave ? L.v_meta : L.k_meta;
   const bool first_of_group =
       uneq ? ((lane & 7) == 0 && (lane == 0 || tile_group(gmap, (lane >> 3) - 1) != grp)) : (2 * lane) % L.G == 0;
@@ -248,30 +256,27 @@ __device__ __forceinline__ void append_token(const Layout &L, const __half *__re
     else
       store_k_row(krow, lane, c0, c1);
   } else {
-    vcodes[2 * lane] = (uint8_t)c0;
-    vcodes[2 * lane + 1] = (uint8_t)c1;
+    lds.vcodes[2 * lane] = (uint8_t)c0;
+    lds.vcodes[2 * lane + 1] = (uint8_t)c1;
   }
-  __syncthreads();
+  // the row as attention will read it, in original channel order
+  lds.read_back[wave][p0] = fmaf((float)c0, mp.scale, mp.zero);
+  lds.read_back[wave][p1] = fmaf((float)c1, mp.scale, mp.zero);
   if (wave == 0) return;
-
-  if (s == 0) {
-    // First token of a block: the block starts as zeros.  The 16 units of sub-block 0 are
-    // written whole below (i == 0), so only the other three sub-blocks are cleared here.
-    const int first = L.v_block_bytes / 16;  // dwords of one sub-block
-    for (int w = first + lane; w < L.v_block_bytes / 4; w += 64) reinterpret_cast<unsigned *>(blk)[w] = 0u;
-  }
+  append_lds_sync();
+  const uint8_t *vcodes = lds.vcodes;
   if (L.v_levels == 16) {
     // lane (j, nh): dwords 2nh and 2nh+1 of unit j are fields 2nh and 2nh+1
     const int j = lane & 15, nh = lane >> 4;
     const unsigned bit = 16 * (i & 1) + 4 * (i >> 1);
     old_pair.x |= (unsigned)vcodes[16 * (2 * nh) + j] << bit;  // old_pair is 0 when i == 0
     old_pair.y |= (unsigned)vcodes[16 * (2 * nh + 1) + j] << bit;
-    reinterpret_cast<uint2 *>(blk + 32 * (16 * kb + j))[nh] = old_pair;
+    reinterpret_cast<uint2 *>(lds.units)[4 * j + nh] = old_pair;
   } else if (L.v_levels == 8) {
     // lane (j, nh): dword nh of unit j holds the low two bits of fields 2nh and 2nh+1; the lanes
     // nh < 2 also own dword 4 + nh: the top bits of fields 4nh .. 4nh+3
     const int j = lane & 15, nh = lane >> 4;
-    unsigned *unit = reinterpret_cast<unsigned *>(blk + 24 * (16 * kb + j));
+    unsigned *unit = reinterpret_cast<unsigned *>(lds.units) + 6 * j;
     const unsigned bit = 16 * (i & 1) + 2 * (i >> 1);
     const unsigned add = (((unsigned)vcodes[16 * (2 * nh) + j] & 3u) << bit) |
                          (((unsigned)vcodes[16 * (2 * nh + 1) + j] & 3u) << (bit + 8));
@@ -287,10 +292,10 @@ __device__ __forceinline__ void append_token(const Layout &L, const __half *__re
     const int j = lane & 15, nh = lane >> 4;
     const unsigned bit = 16 * (i & 1) + 2 * (i >> 1);
     const unsigned add = ((unsigned)vcodes[16 * (2 * nh) + j] << bit) | ((unsigned)vcodes[16 * (2 * nh + 1) + j] << (bit + 8));
-    reinterpret_cast<unsigned *>(blk + 16 * (16 * kb + j))[nh] = old_word | add;  // old_word is 0 when i == 0
+    reinterpret_cast<unsigned *>(lds.units)[4 * j + nh] = old_word | add;  // old_word is 0 when i == 0
   } else if (lane < 16) {
     const int j = lane;
-    uint8_t *u = blk + 13 * (16 * kb + j);
+    uint8_t *u = lds.units + 13 * j;
     unsigned long long lo = 0, hi = 0;  // all zero when i == 0
 #pragma unroll
     for (int q = 0; q < 8; ++q) lo |= (unsigned long long)old_unit[q] << (8 * q);
@@ -311,6 +316,16 @@ __device__ __forceinline__ void append_token(const Layout &L, const __half *__re
 #pragma unroll
     for (int q = 0; q < 5; ++q) u[8 + q] = (uint8_t)(hi >> (8 * q));
   }
+}
+
+// Writes what append_token left of packed row te's V sub-block (one wavefront; after its append_token).
+__device__ __forceinline__ void append_store_units(const Layout &L, long long te, int hk, int b, int lane, const AppendScratch &lds) {
+  const int s = (int)(te & (kVBlock - 1)), words = L.v_block_bytes / 16;  // dwords of one sub-block
+  unsigned *blk = reinterpret_cast<unsigned *>(L.v_codes + (((long long)b * L.Hk + hk) * L.n_vblocks + (te >> 5)) * L.v_block_bytes);
+  for (int w = lane; w < words; w += 64) blk[(s >> 3) * words + w] = reinterpret_cast<const unsigned *>(lds.units)[w];
+  // The first token of a block: the block's other three sub-blocks start as zeros.
+  if (s == 0)
+    for (int w = words + lane; w < 4 * words; w += 64) blk[w] = 0u;
 }
 
 }  // namespace

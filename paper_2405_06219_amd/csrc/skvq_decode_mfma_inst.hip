@@ -31,7 +31,7 @@ hipError_t launch_decode_mfma_fmt(const Layout &L, const __half *q, long long T,
   if (mo.mode != kMergeSeparate && !mo.out_f32) return hipErrorInvalidValue;
   if (mo.mode == kMergeDirect && n_splits != 1) return hipErrorInvalidValue;
   const dim3 grid(n_splits, L.Hk * passes, L.B), block(kThreads);
-  const ChunkPlan plan = plan_chunks(L, T, nq, n_sink, n_splits, knew != nullptr);
+  const ChunkPlan plan = plan_chunks(L, T, nq, n_sink, n_splits, knew != nullptr, !wide && knew != nullptr && te >= 0);
 #define SKVQ_LAUNCH(RR, MM, GG, UU)                                                                                  \
   hipLaunchKernelGGL((decode_mfma_kernel<RR, KL, VL, MM, GG, UU>), grid, block, 0, s, L, q, T, nq, n_sink, n_splits, \
                      passes, n_new, knew, vnew, te, plan, mo)

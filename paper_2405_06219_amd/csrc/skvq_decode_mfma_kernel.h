@@ -235,6 +235,7 @@ constexpr int kThreads = 64 * kNW;
 constexpr int kOldShare = 3, kYoungShare = 2;                        // tiles per deal: waves 0..3 / 4..7
 constexpr int kDealPeriod = (kNW / 2) * (kOldShare + kYoungShare);  // tiles per deal
 constexpr int kAppendLagTiles = 12;  // tiles that the workgroup which also appends the new token is spared
+constexpr int kPackedWave = 3;       // the wavefront (last in line for ring slices) that takes the token packed in the same call
 constexpr int kRingWaves = kNW;     // every wavefront of a workgroup may own ring slices
 constexpr int kRingSlice = 4;       // ring tokens per slice (the slice code reads four rows of 16 lanes)
 
@@ -242,15 +243,15 @@ constexpr int kCombStride = kD + 16;  // floats; the padding spreads the accumul
 
 template <int R, bool TERNARY, int NG>
 struct Smem {
-  // 13-bit field -> the A operand of its eight tokens (104976 bytes, built by the workgroup
-  // from the two 81-entry tables: four base-3 digits -> the operand halves of tokens 0..3 / 4..7)
+  // 13-bit field -> the A operand of its eight tokens (104976 bytes, built by the workgroup:
+  // four base-3 digits -> the operand halves of tokens 0..3 / 4..7)
   uint4_t lut[TERNARY ? 6561 : 1];
-  uint2_t lut4[TERNARY ? 2 : 1][81];
   // per wave: the weights of the current tile, [block][group][column][token slot]; after the
   // wave's last tile the same bytes stage its O^T, [head][reordered position]
   union WaveBuf {
     _Float16 pbuf[2][NG][2 * R][32];
     float stage[R][kCombStride];
+    uint2_t high[TERNARY ? 81 : 1];  // (before the first tile) see build_ternary_table
   } wb[kNW];
   float qraw[4][kD];                   // the query heads as loaded (rows >= R are zero)
   _Float16 qa[32][4][4];               // A operands of the score product: [step][head][k slot]
@@ -260,6 +261,7 @@ struct Smem {
   // tiles (w*) and for the ring slices (r*) of the wave
   // ([head][...][wave]: the epilogue reads a head's eight entries as two 16-byte pieces)
   alignas(16) float wm[R][kNW], wl[R][kNW], wz[R][NG][kNW], rm[R][kNW], rl[R][kNW];
+  AppendScratch append;                // (the workgroup of the last chunk)
   float ring_o[kNW][R][kD];            // per wave: its ring slices' outputs, original channel order
   int ticket;                          // kMergeLast: workgroups of the kv head that ended before this one
 };
@@ -340,30 +342,32 @@ struct TileData {
   uint2_t vt0, vt1;                  // 3-bit units: their 8 bytes of top bits
 };
 
-// The workgroup builds the table of 3-level operands while its first loads are in flight (one barrier
-// inside; the table is complete after the caller's next one).
-__device__ __forceinline__ void build_ternary_table(uint2_t (*lut4)[81], uint4_t *lut, const int tid) {
-  // While the loads are in flight the workgroup builds the table: entry f (a base-3 number of
-  // eight digits, digit i = code of token i) is the operand itself, register m = codes of
-  // tokens 2m (low half) and 2m+1 (high half) as fp16 subnormals c * 2^(8-24).
-  if (tid < 162) {
-    const int half = tid >= 81, x = half ? tid - 81 : tid;
-    const unsigned d0 = x % 3, d1 = (x / 3) % 3, d2 = (x / 9) % 3, d3 = x / 27;
-    lut4[half][x] = uint2_t{(d0 << 8) | (d1 << 24), (d2 << 8) | (d3 << 24)};
-  }
-  __syncthreads();
+// The workgroup builds the table of 3-level operands while its first loads are in flight (the table is complete
+// after the caller's next barrier): entry f (a base-3 number of eight digits, digit i = code of token i) is the
+// operand itself, register m = codes of tokens 2m (low half) and 2m+1 (high half) as fp16 subnormals
+// c * 2^(8-24).  high: the wavefront's own 81 operand halves of four digits, so that none waits for another.
+__device__ __forceinline__ uint2_t four_digits(unsigned x) {
+  const unsigned d0 = x % 3, d1 = (x / 3) % 3, d2 = (x / 9) % 3, d3 = x / 27;
+  return uint2_t{(d0 << 8) | (d1 << 24), (d2 << 8) | (d3 << 24)};
+}
+__device__ __forceinline__ void build_ternary_table(uint2_t *high, uint4_t *lut, const unsigned tid) {
   // Thread t < 486 keeps the low half of its entries (digits t % 81) and walks through every
   // sixth high half from t / 81 on: one read per entry instead of two, all reads first, then
   // all writes (one LDS latency, not one per entry).
-  constexpr int kWalk = 6, kSteps = (81 + kWalk - 1) / kWalk;
-  const unsigned first_hi = tid / 81u, lo = tid - 81u * first_hi;
+  constexpr unsigned kWalk = 6, kSteps = (81 + kWalk - 1) / kWalk;
+  const unsigned lane = tid & 63, first_hi = tid / 81u, lo = tid - 81u * first_hi;
+  high[lane] = four_digits(lane);
+  if (lane < 17) high[64 + lane] = four_digits(64 + lane);
+  const uint2_t lo4 = four_digits(lo);
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
   if (first_hi < kWalk) {
-    const uint2_t lo4 = lut4[0][lo];
     uint2_t hi4[kSteps];
 #pragma unroll
-    for (int i = 0; i < kSteps; ++i) hi4[i] = lut4[1][min(first_hi + kWalk * i, 80u)];
+    for (unsigned i = 0; i < kSteps; ++i) hi4[i] = high[min(first_hi + kWalk * i, 80u)];
 #pragma unroll
-    for (int i = 0; i < kSteps; ++i) {
+    for (unsigned i = 0; i < kSteps; ++i) {
       const unsigned hi = first_hi + kWalk * i;
       if (hi < 81u) lut[81u * hi + lo] = uint4_t{lo4.x, lo4.y, hi4[i].x, hi4[i].y};
     }
@@ -400,17 +404,25 @@ struct ChunkPlan {
   int first_long;  //   tiles plus, when the last chunk's workgroup also appends the new token, the
                    //   kAppendLagTiles it is spared (the last chunk ends at the last tile either way)
   int slot0;       // ring row of the window's oldest token
+  int new_slot;    // ... and of the newest one (the one taken along)
+  // bytes from one (sequence, kv head) to the next: key rows, value blocks, (scale, zero), fp16 rows
+  long long k_head, v_head, m_head, w_head;
 };
 
-inline ChunkPlan plan_chunks(const Layout &L, long long T, long long nq, int n_sink, int n_splits, bool fused) {
+inline ChunkPlan plan_chunks(const Layout &L, long long T, long long nq, int n_sink, int n_splits, bool fused, bool packs) {
   ChunkPlan p;
-  const int n_tiles = (int)((nq + 63) >> 6);
+  const int n_tiles = (int)((nq - (packs ? 1 : 0) + 63) >> 6);
   const int lag = fused && n_tiles >= 4 * kAppendLagTiles * n_splits ? kAppendLagTiles : 0;
   const int nt = n_tiles + lag;
   p.tiles_q = nt / n_splits;
   p.first_long = n_splits - nt % n_splits;
   const long long n_win = (T - nq) - n_sink;
   p.slot0 = (int)((T - n_win) % L.W);
+  p.new_slot = (int)((T - 1) % L.W);
+  p.k_head = L.Tcap * L.k_row_bytes;
+  p.v_head = L.n_vblocks * L.v_block_bytes;
+  p.m_head = L.Tcap * L.NG * (L.meta_fmt == SKVQ_META_F32 ? 8 : L.meta_fmt == SKVQ_META_F16 ? 4 : 2);
+  p.w_head = (long long)(L.W + L.S) * kD * (long long)sizeof(__half);
   return p;
 }
 
@@ -487,7 +499,7 @@ __global__ __launch_bounds__(kThreads, 2) void decode_mfma_kernel(Layout L, cons
   const unsigned gmap = UNEQ ? L.gmaps[hk] : 0u;
   auto piece_group = [&](int n) { return (int)((gmap >> (4 * n)) & 15u); };  // group of positions 16n..16n+15
   const int head0 = passes == 1 ? 0 : (by % passes) * R;  // first of this workgroup's query heads, within the kv head's
-  const long long head = (long long)b * L.Hk + hk;
+  const unsigned head = (unsigned)b * L.Hk + hk;  // (B and Hk have 16 bits)
   const float c = L.sm_scale * kLog2e;
 
   // ---- the query and the permutations: the first requests of the workgroup, ahead of everything
@@ -495,55 +507,57 @@ __global__ __launch_bounds__(kThreads, 2) void decode_mfma_kernel(Layout L, cons
   //      requests of all workgroups) ----
   const int n_rows = n_new * L.R;  // rows of this kv head: (query token, query head)
   // row x of the kv head -> index of its (sequence, query token, query head) in q, the partials and the output
-  auto row_index = [&](int x) {
+  auto row_index = [&](int x) {  // (B has 16 bits, tokens x heads too: see launch_decode)
     const int j = n_new == 1 ? 0 : x / L.R;  // (no division on the single-token path)
-    return ((long long)b * n_new + j) * L.Hq + hk * L.R + (x - j * L.R);
+    return ((unsigned)b * n_new + j) * L.Hq + hk * L.R + (x - j * L.R);
   };
   __half2 q2 = __floats2half2_rn(0.f, 0.f);
   if (tid < 64 * R && head0 + (tid >> 6) < n_rows)
-    q2 = reinterpret_cast<const __half2 *>(q + row_index(head0 + (tid >> 6)) * kD)[lane];
+    q2 = reinterpret_cast<const __half2 *>(q + (size_t)row_index(head0 + (tid >> 6)) * kD)[lane];
   // (staging: wavefront w < 4 places head w's query at the positions lane and 64 + lane)
   const int pk0 = L.perm_k[hk * kD + lane], pk1 = L.perm_k[hk * kD + 64 + lane];
   const int pv_ch = L.perm_v[hk * kD + (tid & 127)];  // for the epilogue: channel of position tid%128
 
   // ---- the new token taken along (knew != null; one query token, passes == 1, and the token
-  //      that leaves the window, if any, is packed: the host sees to that).  T counts the new
-  //      token.  The workgroup of the last chunk does what the append kernel does (its tiles are
-  //      the only ones that read the packed row, the V block and the metadata that this writes;
-  //      nobody reads the ring slot: the new token's row is taken from knew / vnew below).  Its
-  //      stores have completed, in this compute unit's own cache order, before its first tile
-  //      load is issued, and no load of the branch is pending where the paths join. ----
+  //      that leaves the window, if any, is packed: the host sees to that).  T counts the new token.  Two
+  //      wavefronts of the last chunk's workgroup do what the append kernel does, while the others go on to the
+  //      barrier ahead of the tile loop.  Nobody in this launch reads what they write: the tiles hold the nq_tiles
+  //      tokens packed before, the token that is packed now counts as one more token in the form it reads back in
+  //      (LDS), its V sub-block, which has older tokens too, is stored when the workgroup has read its tiles, and
+  //      the new token's row is taken from knew / vnew below.  All eight wavefronts used to wait for the
+  //      append (1.8 - 2.2 us: a round trip, the encoder, the stores' acknowledgement) and, before the last tile,
+  //      for its stores; us per step without that and with, caches hot: 1 x 4 heads x 2048 tokens 8.2 / 7.7,
+  //      8 x 8 kv heads x 6007 tokens 16.6 / 15.9.  Asking for that tile again behind the barrier instead made
+  //      every other wait of the kernel conservative: 161 -> 169 us per eight calls of 100000 tokens. ----
   const bool fused = knew != nullptr;
-  if (fused && sp == n_splits - 1) {
-    append_token(L, knew, vnew, T - 1, -1, te, hk, b, wave, lane, reinterpret_cast<__half(*)[kD]>(&sm.ring_o[0][0][0]),
-                 reinterpret_cast<uint8_t *>(&sm.ring_o[0][0][0]) + 2 * kD * sizeof(__half));
-    __threadfence_block();
-    // (the fence alone need not wait for the stores.  The builtin, not inline assembly: the
-    // compiler then knows that no load of this branch is pending, and adds no wait for one to
-    // the common path below.)  vmcnt(0), the other counters left alone
+  const bool appends = fused && sp == n_splits - 1, packs = appends && te >= 0;
+  const long long nq_tiles = fused && te >= 0 ? nq - 1 : nq;
+  if (appends && wave < 2) {
+    append_token(L, knew, vnew, T - 1, plan.new_slot, -1, te, hk, b, wave, lane, sm.append);
+    // The builtin, not inline assembly: the compiler then knows that no load of this branch is pending, and adds no
+    // wait for one to the common path below.  vmcnt(0), the other counters left alone
     __builtin_amdgcn_s_waitcnt(0x0F70);
     asm volatile("" ::: "memory");
-    __syncthreads();
   }
 
   // ---- this chunk, this wave's tiles ----
   // (with the new token taken along the last chunk is shorter by about the time its workgroup
   // spends on the append)
-  const int n_tiles = (int)((nq + 63) >> 6);
-  // (the later chunks hold the odd tiles: the last chunk is never empty while there is a tile,
-  // and the tile of the token that leaves the window is always its own)
+  const int n_tiles = (int)((nq_tiles + 63) >> 6);
+  // (the later chunks hold the odd tiles)
   const int n_long = sp > plan.first_long ? sp - plan.first_long : 0;  // longer chunks before this one
   const int tile_begin = sp * plan.tiles_q + n_long;
   const int tile_end = sp == n_splits - 1 ? n_tiles : tile_begin + plan.tiles_q + (sp >= plan.first_long ? 1 : 0);
 
   constexpr int kRowBytes = K4 ? 64 : K3 ? 48 : 32;
-  const uint8_t *kc = L.k_codes + head * L.Tcap * kRowBytes;
+  const uint8_t *kc = L.k_codes + head * (unsigned long long)plan.k_head;
   typedef TileData<KL, VL, META, NG> Tile;
   typedef MetaBlock<META, NG> meta_block;
-  const meta_block *km = reinterpret_cast<const meta_block *>(L.k_meta) + head * L.Tcap;
-  const meta_block *vm = reinterpret_cast<const meta_block *>(L.v_meta) + head * L.Tcap;
-  const uint8_t *vc = L.v_codes + head * L.n_vblocks * L.v_block_bytes;
-  const int last_token = (int)(nq - 1);  // -1 when nothing is packed (then there are no tiles)
+  const unsigned long long m_at = head * (unsigned long long)plan.m_head;
+  const meta_block *km = reinterpret_cast<const meta_block *>(reinterpret_cast<const uint8_t *>(L.k_meta) + m_at);
+  const meta_block *vm = reinterpret_cast<const meta_block *>(reinterpret_cast<const uint8_t *>(L.v_meta) + m_at);
+  const uint8_t *vc = L.v_codes + head * (unsigned long long)plan.v_head;
+  const int last_token = (int)(nq_tiles - 1);  // -1 when there are no tiles
   const int last_blk = last_token >> 5;
   const int vbb = TERNARY ? kTernaryBlockBytes : V4 ? kFourBitBlockBytes : V3 ? kThreeBitBlockBytes : kTwoBitBlockBytes;
   const unsigned unit_off = TERNARY ? ((13 * lane) & ~3) : V4 ? 32 * lane : V3 ? 24 * lane : 16 * lane;
@@ -618,8 +632,9 @@ __global__ __launch_bounds__(kThreads, 2) void decode_mfma_kernel(Layout L, cons
   const int ring_first = sp + n_splits * ring_rank;
   const bool ring_owner = ring_first < n_slices;
   const int slot0 = plan.slot0;  // ring row of the window's oldest token
-  const __half *kwin = L.k_win + head * (W + L.S) * kD;
-  const __half *vwin = L.v_win + head * (W + L.S) * kD;
+  const unsigned long long w_at = head * (unsigned long long)plan.w_head;
+  const char *kwin = reinterpret_cast<const char *>(L.k_win) + w_at;
+  const char *vwin = reinterpret_cast<const char *>(L.v_win) + w_at;
   // (ring token t, clamped to the last one, sits in sink row W + t if it is a sink, else in ring
   // slot slot0 + t - n_sink modulo W; the newest token's row is the caller's when it is taken along)
   auto load_ring = [&](int slice) {
@@ -632,14 +647,12 @@ __global__ __launch_bounds__(kThreads, 2) void decode_mfma_kernel(Layout L, cons
     const int slot = t < n_sink ? W + t : (s >= W ? s - W : s);
     const int fresh = fused && t >= n_fp - 1 ? 1 : 0;  // the caller's row of the new token
     const unsigned row_bytes = (unsigned)slot * (unsigned)(kD * sizeof(__half));
-    const char *krow = fresh ? reinterpret_cast<const char *>(knew + head * kD)
-                             : reinterpret_cast<const char *>(kwin) + row_bytes;
+    const char *krow = fresh ? reinterpret_cast<const char *>(knew + (size_t)head * kD) : kwin + row_bytes;
     d.k = reinterpret_cast<const uint4_t *>(krow)[lane & 15];
 #pragma unroll
     for (int k = 0; k < kRingSlice; ++k) {
       const unsigned vb = (unsigned)__builtin_amdgcn_readlane((int)row_bytes, 16 * k);
-      const char *vrow = __builtin_amdgcn_readlane(fresh, 16 * k) ? reinterpret_cast<const char *>(vnew + head * kD)
-                                                                   : reinterpret_cast<const char *>(vwin) + vb;
+      const char *vrow = __builtin_amdgcn_readlane(fresh, 16 * k) ? reinterpret_cast<const char *>(vnew + (size_t)head * kD) : vwin + vb;
       d.v[k] = reinterpret_cast<const unsigned *>(vrow)[lane];
     }
     return d;
@@ -668,7 +681,7 @@ __global__ __launch_bounds__(kThreads, 2) void decode_mfma_kernel(Layout L, cons
   Tile buf_a, buf_b, buf_c;
   buf_a = load_tile(min(tile_a, tile_cap));
   if (TERNARY) {
-    build_ternary_table(sm.lut4, sm.lut, tid);
+    build_ternary_table(sm.wb[wave].high, sm.lut, tid);
   }
   {
     asm volatile("" ::: "memory");
@@ -765,7 +778,7 @@ __global__ __launch_bounds__(kThreads, 2) void decode_mfma_kernel(Layout L, cons
   }
 
   // ---- ring slices of this wave (plain vector arithmetic, wave-local) ----
-  if (ring_owner) {
+  if (ring_owner || (packs && wave == kPackedWave)) {
     float rm[R], rl[R], ro[R][2];  // reference, sum of weights, outputs
 #pragma unroll
     for (int r = 0; r < R; ++r) rm[r] = -INFINITY, rl[r] = 0.f, ro[r][0] = ro[r][1] = 0.f;
@@ -823,7 +836,8 @@ __global__ __launch_bounds__(kThreads, 2) void decode_mfma_kernel(Layout L, cons
         }
       }
     };
-    if (ring_first + ring_stride >= n_slices) {
+    if (!ring_owner) {
+    } else if (ring_first + ring_stride >= n_slices) {
       // one slice (the usual case): its data was requested before the tile loads
       ring_slice(ring, ring_first);
     } else {
@@ -837,6 +851,22 @@ __global__ __launch_bounds__(kThreads, 2) void decode_mfma_kernel(Layout L, cons
       }
       asm volatile("" ::"v"(ring.k.x), "v"(ring.k.y), "v"(ring.k.z), "v"(ring.k.w), "v"(ring.v[0]),
                    "v"(ring.v[1]), "v"(ring.v[2]), "v"(ring.v[3]));
+    }
+    if (packs && wave == kPackedWave) {
+      // the token that is packed in this call (seen by every row: one query token)
+      const float2 k2 = *reinterpret_cast<const float2 *>(&sm.append.read_back[0][2 * lane]);
+      const float2 v2 = *reinterpret_cast<const float2 *>(&sm.append.read_back[1][2 * lane]);
+#pragma unroll
+      for (int r = 0; r < R; ++r) {
+        const float2 q2r = *reinterpret_cast<const float2 *>(&sm.qraw[r][2 * lane]);
+        const float sum = wave_sum_in_last_lane(fmaf(q2r.x, k2.x, q2r.y * k2.y));
+        const float s = c * __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, sum), 63));
+        const float mnew = fmaxf(rm[r], s), f = fast_exp2(rm[r] - mnew), p = fast_exp2(s - mnew);
+        rl[r] = fmaf(rl[r], f, p);
+        ro[r][0] = fmaf(ro[r][0], f, p * v2.x);
+        ro[r][1] = fmaf(ro[r][1], f, p * v2.y);
+        rm[r] = mnew;
+      }
     }
 #pragma unroll
     for (int r = 0; r < R; ++r) {
@@ -1146,6 +1176,7 @@ __global__ __launch_bounds__(kThreads, 2) void decode_mfma_kernel(Layout L, cons
     }
   }
   __syncthreads();
+  if (packs && wave == kNW - 1) append_store_units(L, te, hk, b, lane, sm.append);
   if (tid < R * kD && head0 + (tid >> 7) < n_rows) {
     // thread (head r, position p); a wavefront serves one head.  The sixteen things to combine --
     // the eight wavefronts' tile sums and their eight ring-slice sums -- are spread over the lanes of
@@ -1197,12 +1228,12 @@ __global__ __launch_bounds__(kThreads, 2) void decode_mfma_kernel(Layout L, cons
     if (mo.mode == kMergeDirect) {
       // the only chunk of its kv head: this is the result
       const float o = num / den;
-      const long long idx = row_index(head0 + r) * kD + ch;
+      const size_t idx = (size_t)row_index(head0 + r) * kD + ch;
       mo.out_f32[idx] = o;
       if (mo.out_f16) mo.out_f16[idx] = __float2half_rn(o);
     } else {
       float *part =
-          L.workspace + (row_index(head0 + r) * (SKVQ_MAX_SPLITS + 1) + sp) * kPartialStride;
+          L.workspace + ((size_t)row_index(head0 + r) * (SKVQ_MAX_SPLITS + 1) + sp) * kPartialStride;
       if (mo.mode == kMergeLast) {
         __hip_atomic_store(part + 4 + ch, num, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         if (p == 0) {
@@ -1221,7 +1252,7 @@ __global__ __launch_bounds__(kThreads, 2) void decode_mfma_kernel(Layout L, cons
   if (mo.mode == kMergeLast) {
     const int r = min(tid >> 7, R - 1);
     const bool row_exists = head0 + r < n_rows;
-    const long long row = row_index(row_exists ? head0 + r : head0), idx = row * kD + (tid & (kD - 1));
+    const size_t row = row_index(row_exists ? head0 + r : head0), idx = row * kD + (tid & (kD - 1));
     const float *base = L.workspace + row * (SKVQ_MAX_SPLITS + 1) * kPartialStride;
     float *o32 = mo.out_f32 + idx;
     __half *o16 = mo.out_f16 ? mo.out_f16 + idx : nullptr;

@@ -49,13 +49,16 @@ struct WideSmem {
   };
   float ring_o[kNW][kRowQuad][kD];  // per wave: its slices' outputs, original channel order
   alignas(16) int perm_v[kD];
-  uint2_t lut4[TERNARY ? 2 : 1][81];
+  uint2_t lut4[TERNARY ? kNW : 1][81];
   // per wave and group, of the current tile's tokens: {key scale, dequantized centre} and {value scale,
   // value zero}, with the factors that the codes' places in the operands ask for
   alignas(16) float2 ktok[kNW][NG][kTokStride], vtok[kNW][NG][kTokStride];
   // B operands of the score product: [step][lane / 16][row][k slot]
   alignas(16) _Float16 qa[4][4][kWideRows][8];
-  alignas(16) _Float16 qraw[kWideRows][kD];     // the query rows as loaded (rows that do not exist are zero)
+  union {
+    alignas(16) _Float16 qraw[kWideRows][kD];   // the query rows as loaded (rows that do not exist are zero)
+    AppendScratch append;                       // (before them)
+  };
   alignas(16) float qpart[kWideRows][8];        // sums of the reordered query over 16 positions each
   alignas(16) float wm[kWideRows][kNW], wl[kWideRows][kNW], wz[kWideRows][NG][kNW];
   float rm[kWideRows][kWideTeams], rl[kWideRows][kWideTeams];
@@ -155,8 +158,11 @@ __global__ __launch_bounds__(kThreads, 2) void decode_wide_kernel(Layout L, cons
   // ---- the new token taken along: as in decode_mfma_kernel ----
   const bool fused = knew != nullptr;
   if (fused && sp == n_splits - 1) {
-    append_token(L, knew, vnew, T - 1, -1, te, hk, b, wave, lane, reinterpret_cast<__half(*)[kD]>(&sm.qraw[0][0]),
-                 reinterpret_cast<uint8_t *>(&sm.qraw[0][0]) + 2 * kD * sizeof(__half));
+    if (wave < 2) append_token(L, knew, vnew, T - 1, plan.new_slot, -1, te, hk, b, wave, lane, sm.append);
+    if (wave == 1 && te >= 0) {
+      append_lds_sync();
+      append_store_units(L, te, hk, b, lane, sm.append);
+    }
     __threadfence_block();
     __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0): the stores have completed
     asm volatile("" ::: "memory");
@@ -292,7 +298,7 @@ __global__ __launch_bounds__(kThreads, 2) void decode_wide_kernel(Layout L, cons
   int tile_a = tile_of(n_a), tile_b = tile_of(n_b), tile_c = tile_of(n_c);
   Tile buf_a, buf_b, buf_c;
   buf_a = load_tile(min(tile_a, tile_cap));
-  if constexpr (TERNARY) build_ternary_table(sm.lut4, sm.lut, tid);
+  if constexpr (TERNARY) build_ternary_table(sm.lut4[wave], sm.lut, tid);
   asm volatile("" ::: "memory");
   buf_b = load_tile(min(tile_b, tile_cap));
 #pragma unroll

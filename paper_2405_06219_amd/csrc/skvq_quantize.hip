@@ -398,12 +398,15 @@ __global__ __launch_bounds__(256) void prefill_kernel(Layout L, const __half *__
 
 // Append: one workgroup of two wavefronts per (b, hk) (skvq_append_device.h).
 __global__ __launch_bounds__(128) void append_kernel(Layout L, const __half *__restrict__ knew,
-                                                     const __half *__restrict__ vnew, long long T, int keep_row,
-                                                     long long te) {
-  __shared__ __half rows[2][kD];
-  __shared__ uint8_t vcodes[kD];
-  append_token(L, knew, vnew, T, keep_row, te, blockIdx.x, blockIdx.y, threadIdx.x >> 6, threadIdx.x & 63, rows,
-               vcodes);
+                                                     const __half *__restrict__ vnew, long long T, int ring_slot,
+                                                     int keep_row, long long te) {
+  __shared__ AppendScratch lds;
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  append_token(L, knew, vnew, T, ring_slot, keep_row, te, blockIdx.x, blockIdx.y, wave, lane, lds);
+  if (wave == 1 && T >= L.W && keep_row < 0) {
+    append_lds_sync();
+    append_store_units(L, te, blockIdx.x, blockIdx.y, lane, lds);
+  }
 }
 
 }  // namespace
@@ -443,7 +446,8 @@ hipError_t launch_prefill(const Layout &L, const __half *k, const __half *v, lon
 hipError_t launch_append(const Layout &L, const __half *k_new, const __half *v_new, long long T, int keep_row,
                          long long te, hipStream_t s) {
   if (L.B > 65535 || keep_row >= L.S || (T >= L.W && keep_row < 0 && (te < 0 || te >= L.Tcap))) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(append_kernel, dim3(L.Hk, L.B), dim3(128), 0, s, L, k_new, v_new, T, keep_row, te);
+  hipLaunchKernelGGL(append_kernel, dim3(L.Hk, L.B), dim3(128), 0, s, L, k_new, v_new, T, (int)(T % L.W),
+                     keep_row, te);
   return hipGetLastError();
 }
 
