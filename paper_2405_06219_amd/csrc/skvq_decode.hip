@@ -17,78 +17,103 @@ namespace skvq {
 
 namespace {
 
+// Cross-lane moves inside a row of 16 lanes (data-parallel moves: no round trip through LDS) ...
+template <int CTRL>
+__device__ __forceinline__ float row_move(float x) {
+  return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), CTRL, 0xf, 0xf, true));
+}
+__device__ __forceinline__ float lane_value(float x, int lane) {
+  return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, x), lane));
+}
+// ... and the maximum and the sum over the 64 lanes, in every lane.
 __device__ __forceinline__ float wave_max(float v) {
-  for (int off = 32; off; off >>= 1) v = fmaxf(v, __shfl_xor(v, off));
-  return v;
+  v = fmaxf(v, row_move<0xB1>(v));   // quad_perm [1,0,3,2]
+  v = fmaxf(v, row_move<0x4E>(v));   // quad_perm [2,3,0,1]
+  v = fmaxf(v, row_move<0x141>(v));  // row_half_mirror
+  v = fmaxf(v, row_move<0x140>(v));  // row_mirror
+  return fmaxf(fmaxf(lane_value(v, 0), lane_value(v, 16)), fmaxf(lane_value(v, 32), lane_value(v, 48)));
 }
 __device__ __forceinline__ float wave_sum(float v) {
-  for (int off = 32; off; off >>= 1) v += __shfl_xor(v, off);
-  return v;
+  v += row_move<0xB1>(v);
+  v += row_move<0x4E>(v);
+  v += row_move<0x141>(v);
+  v += row_move<0x140>(v);
+  return (lane_value(v, 0) + lane_value(v, 16)) + (lane_value(v, 32) + lane_value(v, 48));
 }
 
-
 // Combines the chunk partials of one (sequence, query head): out = sum_i acc_i 2^(m_i - m*) /
-// sum_i l_i 2^(m_i - m*).  Partials hold base-2 exponents.  grid (Hq, B), 1024 threads:
-// wavefront 0 turns the (m_i, l_i) into weights, thread (channel, slice) adds every eighth
-// partial.
-__global__ __launch_bounds__(1024) void merge_kernel(Layout L, float *__restrict__ out_f32,
-                                                     __half *__restrict__ out_f16, int n_all, int n_heads) {
-  __shared__ float wts[SKVQ_MAX_SPLITS + 1];
-  __shared__ float den_s;
-  __shared__ float red[8][kD];
-  const int hq = blockIdx.x, b = blockIdx.y, tid = threadIdx.x;
+// sum_i l_i 2^(m_i - m*).  Partials hold base-2 exponents.  grid (Hq, B), 256 threads: thread (slice,
+// four channels) adds every eighth partial.
+// Bound by latency (17 KB per workgroup): what counts is the chain from the launch to the store.  So
+// every wavefront works out all weights itself, lane i holding those of partials i and 64 + i, while the
+// partials' values are on their way: one memory round trip and one barrier.  A pass over eight layers against
+// 1024 threads, wavefront 0's weights through LDS and shuffles: 32 q / 8 kv heads, 131072 tokens, 181 -> 177 us
+// (32 partials a row), 100003 tokens in two groups 167 -> 163, four query tokens 221 -> 216.
+constexpr int kMergeThreads = 256, kMergeSlices = 8;
+static_assert(kMergeThreads == kMergeSlices * kD / 4, "one thread per slice and four channels");
+__global__ __launch_bounds__(kMergeThreads) void merge_kernel(Layout L, float *__restrict__ out_f32,
+                                                              __half *__restrict__ out_f16, int n_all, int n_heads) {
+  typedef float float4_t __attribute__((ext_vector_type(4)));
+  __shared__ __align__(16) float red[kMergeSlices][kD];
+  const int hq = blockIdx.x, b = blockIdx.y, tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   // n_heads = query tokens x query heads per sequence; hq counts (token, head) pairs
   const float *base = L.workspace + ((long long)b * n_heads + hq) * (SKVQ_MAX_SPLITS + 1) * kPartialStride;
-  const int ch = tid & 127, sl = tid >> 7;
-  // the first 32 partials' values are requested before their weights are known: one round trip
-  float pre[4];
+  constexpr int kLaneSets = SKVQ_MAX_SPLITS / 64, kBatch = 32, kSteps = kBatch / kMergeSlices;
+  static_assert(SKVQ_MAX_SPLITS % 64 == 0 && 64 % kBatch == 0, "whole sets of lanes, whole batches in them");
+  float mi[kLaneSets], li[kLaneSets];
 #pragma unroll
-  for (int k = 0; k < 4; ++k) {
-    const int i = sl + 8 * k;
-    pre[k] = i < n_all ? base[(long long)i * kPartialStride + 4 + ch] : 0.f;
+  for (int j = 0; j < kLaneSets; ++j) {
+    const int i = lane + 64 * j;
+    mi[j] = -INFINITY, li[j] = 0.f;
+    if (i < n_all) {
+      const float2 ml = *reinterpret_cast<const float2 *>(base + i * kPartialStride);
+      mi[j] = ml.x, li[j] = ml.y;
+    }
   }
-  if (tid < 64) {
-    float mi[3], li[3], mstar = -INFINITY;
+  const int x = tid & 31, sl = tid >> 5;  // (a wavefront has the slices 2 wave and 2 wave + 1)
+  auto value = [&](int i) {               // (past the end: the last partial again, with weight 0)
+    const unsigned at = (unsigned)min(i + sl, n_all - 1) * (unsigned)(kPartialStride * sizeof(float)) + 16u * x + 16u;
+    return *reinterpret_cast<const float4_t *>(reinterpret_cast<const char *>(base) + at);
+  };
+  float4_t part[SKVQ_MAX_SPLITS / kBatch][kSteps];  // every value is requested before the first weight is known
 #pragma unroll
-    for (int k = 0; k < 3; ++k) {
-      const int i = tid + 64 * k;
-      mi[k] = -INFINITY, li[k] = 0.f;
-      if (i < n_all) {
-        const float2 ml = *reinterpret_cast<const float2 *>(base + (long long)i * kPartialStride);
-        mi[k] = ml.x, li[k] = ml.y;
+  for (int t = 0; t < SKVQ_MAX_SPLITS; t += kBatch)
+    if (t < n_all) {  // (uniform)
+#pragma unroll
+      for (int k = 0; k < kSteps; ++k) part[t / kBatch][k] = value(t + kMergeSlices * k);
+    }
+  float mstar = -INFINITY;
+#pragma unroll
+  for (int j = 0; j < kLaneSets; ++j)
+    if (li[j] > 0.f) mstar = fmaxf(mstar, mi[j]);
+  mstar = wave_max(mstar);
+  float w[kLaneSets], den = 0.f;  // (partials without tokens weigh nothing)
+#pragma unroll
+  for (int j = 0; j < kLaneSets; ++j) {
+    w[j] = li[j] > 0.f ? exp2f(mi[j] - mstar) : 0.f;
+    den += w[j] * li[j];
+  }
+  den = wave_sum(den);
+  float4_t num = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int t = 0; t < SKVQ_MAX_SPLITS; t += kBatch)
+    if (t < n_all) {
+#pragma unroll
+      for (int k = 0; k < kSteps; ++k) {
+        const int i = t % 64 + kMergeSlices * k + 2 * wave;
+        const float even = lane_value(w[t / 64], i), odd = lane_value(w[t / 64], i + 1), f = sl & 1 ? odd : even;
+#pragma unroll
+        for (int c = 0; c < 4; ++c) num[c] = f > 0.f ? fmaf(f, part[t / kBatch][k][c], num[c]) : num[c];
       }
-      if (li[k] > 0.f) mstar = fmaxf(mstar, mi[k]);
     }
-    mstar = wave_max(mstar);
-    float den = 0.f;
-#pragma unroll
-    for (int k = 0; k < 3; ++k) {
-      const int i = tid + 64 * k;
-      const float w = li[k] > 0.f ? exp2f(mi[k] - mstar) : 0.f;
-      if (i < n_all) wts[i] = w;
-      den += w * li[k];
-    }
-    den = wave_sum(den);
-    if (tid == 0) den_s = den;
-  }
-  __syncthreads();
-  float num = 0.f;
-#pragma unroll
-  for (int k = 0; k < 4; ++k) {
-    const int i = sl + 8 * k;
-    if (i < n_all && wts[i] > 0.f) num = fmaf(wts[i], pre[k], num);
-  }
-  for (int i = sl + 32; i < n_all; i += 8) {
-    const float w = wts[i];
-    if (w > 0.f) num = fmaf(w, base[(long long)i * kPartialStride + 4 + ch], num);
-  }
-  red[sl][ch] = num;
+  *reinterpret_cast<float4_t *>(&red[sl][4 * x]) = num;
   __syncthreads();
   if (tid < kD) {
     float tot = 0.f;
 #pragma unroll
-    for (int k = 0; k < 8; ++k) tot += red[k][tid];
-    const float o = tot / den_s;
+    for (int k = 0; k < kMergeSlices; ++k) tot += red[k][tid];
+    const float o = tot / den;
     const long long idx = ((long long)b * n_heads + hq) * kD + tid;
     out_f32[idx] = o;
     if (out_f16) out_f16[idx] = __float2half_rn(o);
@@ -118,7 +143,7 @@ hipError_t launch_decode(const Layout &L, const __half *q, float *out_f32, __hal
   hipError_t e = launch_decode_mfma(L, q, T, n.n_quant, (int)n.n_sink, plan, n_new, k_new, v_new, te, mo, s);
   if (e != hipSuccess || mo.mode != kMergeSeparate) return e;
   // the fp16 tokens are folded into the chunks' partials
-  hipLaunchKernelGGL(merge_kernel, dim3(L.Hq * n_new, L.B), dim3(1024), 0, s, L, out_f32, out_f16, n_splits,
+  hipLaunchKernelGGL(merge_kernel, dim3(L.Hq * n_new, L.B), dim3(kMergeThreads), 0, s, L, out_f32, out_f16, n_splits,
                      L.Hq * n_new);
   return hipGetLastError();
 }

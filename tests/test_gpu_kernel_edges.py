@@ -360,3 +360,22 @@ def test_fp8_pairs_of_every_fp16_number():
         if g.dtype.itemsize == 2:
             g, r = g.view(np.uint16), r.view(np.uint16)
         assert np.array_equal(g, r), name
+
+
+# Partials combined by the merge launch, at the edges of its slices (8), batches (32) and sets of lanes (64): against
+# the oracle, and against one chunk (the same fp32 sums in another order: 1e-5 of the largest output, as in the
+# parity tests of split counts).  The workspace holds NaNs before each call.
+@pytest.mark.parametrize("splits", [2, 9, 31, 32, 33, 64, 65, 96, 97, 127, 128])
+def test_merge_at_its_edges(splits):
+    from paper_2405_06219_amd import synth
+
+    w = synth.Workload("merge", 2, 2, 2, 64 * 128 + 16, 2.0, window=16, seed=33)
+    pair, k, v, q = P.make_pair(w, extra_tokens=1)
+    pair.prefill(k, v)
+    qd, ref, outs = torch.from_numpy(q).cuda(), pair.ref.decode(q), []
+    for n in (1, splits):
+        pair.gpu.skvq_set_num_splits(n)
+        pair.gpu.buffers["workspace"].fill_(0xFF)
+        outs.append(pair.gpu.skvq_decode_attention(qd).cpu().numpy())
+        assert np.abs(outs[-1] - ref).max() <= P.TOL, n
+    assert np.abs(outs[1] - outs[0]).max() <= 1e-5 * max(1.0, np.abs(ref).max())
