@@ -248,11 +248,14 @@ struct Smem {
   uint4_t lut[TERNARY ? 6561 : 1];
   // per wave: the weights of the current tile, [block][group][column][token slot]; after the
   // wave's last tile the same bytes stage its O^T, [head][reordered position]
-  union WaveBuf {
+  // (weights and outputs go 16 bytes at a time: every wavefront's copy is a multiple of 16 bytes, which high's
+  // 648 are not)
+  union alignas(16) WaveBuf {
     _Float16 pbuf[2][NG][2 * R][32];
     float stage[R][kCombStride];
     uint2_t high[TERNARY ? 81 : 1];  // (before the first tile) see build_ternary_table
   } wb[kNW];
+  static_assert(sizeof(WaveBuf) % 16 == 0, "an array of them keeps the alignment");
   float qraw[4][kD];                   // the query heads as loaded (rows >= R are zero)
   _Float16 qa[32][4][4];               // A operands of the score product: [step][head][k slot]
   alignas(16) float qpart[4][8];       // per head: sums of the reordered query over 16 positions each

@@ -234,3 +234,50 @@ def test_read_write_yardstick_refuses_bad_arguments_before_touching_a_device(B):
     assert L.skvq_read_write_yardstick(0x1000, 0x100008, 4096, 7, None) == bad
     assert L.skvq_read_write_yardstick(0x1000, 0x100000, 4096, 0, None) == bad
     assert L.skvq_read_write_yardstick(0x1000, 0x100000, 4096, 9, None) == bad
+
+
+# The structures that the decode kernels keep in LDS: what is read or written 16 bytes at a time starts at a multiple of
+# 16 bytes, in every wavefront's copy.  Layouts are the compiler's own (its host pass), for every rows, table and groups.
+def test_lds_vectors_are_aligned(tmp_path):
+    import subprocess
+
+    from paper_2405_06219_amd import build
+
+    source = tmp_path / "lds_layout.hip"
+    source.write_text("""
+#include "skvq_decode_mfma_kernel.h"
+#include "skvq_decode_wide_kernel.h"
+#include <cstdio>
+using namespace skvq;
+#define AT(S, M) printf("%zu " #S "::" #M "\\n", __builtin_offsetof(S, M))
+template <int R, bool TERNARY, int NG> void narrow() {
+  typedef Smem<R, TERNARY, NG> S;
+  printf("# rows %d table %d groups %d\\n", R, (int)TERNARY, NG);
+  for (int w = 0; w < kNW; ++w) printf("%zu S::wb[%d]\\n", __builtin_offsetof(S, wb) + w * sizeof(typename S::WaveBuf), w);
+  AT(S, lut); AT(S, qraw); AT(S, qa); AT(S, qpart); AT(S, qtotal); AT(S, wm); AT(S, wl); AT(S, wz);
+}
+template <bool TERNARY, int NG> void wide() {
+  typedef WideSmem<TERNARY, NG> S;
+  printf("# sixteen rows, table %d groups %d\\n", (int)TERNARY, NG);
+  AT(S, lut); AT(S, stage); AT(S, ktok); AT(S, vtok); AT(S, qa); AT(S, qraw); AT(S, qpart); AT(S, wm); AT(S, wl); AT(S, wz);
+}
+template <int R> void rows() {
+  narrow<R, true, 1>(); narrow<R, true, 2>(); narrow<R, true, 4>();
+  narrow<R, false, 1>(); narrow<R, false, 2>(); narrow<R, false, 4>();
+}
+int main() {
+  rows<1>(); rows<2>(); rows<4>();
+  wide<true, 1>(); wide<true, 2>(); wide<false, 1>(); wide<false, 2>();
+}
+""")
+    program = str(tmp_path / "lds_layout")
+    hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
+    subprocess.run([hipcc, *build.COMMON, "--offload-host-only", str(source), "-o", program], check=True)
+    lines = subprocess.run([program], check=True, capture_output=True, text=True).stdout.splitlines()
+    assert len(lines) == 18 * 17 + 4 * 11
+    where = ""
+    for line in lines:
+        if line.startswith("#"):
+            where = line
+        else:
+            assert int(line.split()[0]) % 16 == 0, f"{where}: {line}"
