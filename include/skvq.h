@@ -248,8 +248,8 @@ int skvq_decode_attention_static(skvq_cache *cache, const void *q, void *out_f32
  * heads; more with one or two equal groups per head, where the cache is long for the compute units at
  * hand), it is split into at least four chunks (long caches, few sequences) or the launch has a compute
  * unit for every workgroup, and the token that leaves the window is packed (not kept as a sink), both
- * run as one launch: the workgroup that reads the
- * last packed rows quantizes the leaving token itself before it reads them, and the new token's
+ * run as one launch: the workgroup that reads the last packed rows also quantizes the leaving
+ * token, which takes part in the form it is stored in, and the new token's
  * fp16 row is taken from k_new / v_new; otherwise the two kernels are launched one after the
  * other.  k_new and v_new must stay valid until the call has finished on the stream. */
 int skvq_append_decode_attention(skvq_cache *cache, const void *k_new, const void *v_new, const void *q,

@@ -186,8 +186,10 @@ long long decode_cost(const skvq_cache *c, const DecodePlan &p, long long n_quan
 // workgroup of the launch has a compute unit to itself, however many of them append: the append then
 // lengthens the call by less than the launch it replaces (one launch against two, us per call: 1 x 4
 // heads x 800 tokens 11.0 / 12.9, 8 x 32 x 4000 23.4 / 24.9, 12 x 8 x 20000 36.6 / 39.3, 8 x 32 x 32k
-// 106.0 / 107.5).  Past that, a workgroup that starts late waits for its own append with nothing
-// beside it: 16 x 32 x 32k tokens 240 / 236.
+// 106.0 / 107.5).  The line at the compute units was drawn while all wavefronts of a workgroup waited for its
+// append (16 x 32 x 32k tokens 240 / 236).  With the append beside the start-up one launch is no longer the slower
+// one past it (16 x 32 x 32k 201.8 / 203.0, x 2000 27.4 / 29.9, 12 x 32 x 8000 55.7 / 57.2), and the line
+// only leaves that ungained.
 bool step_is_one_launch(const skvq_cache *c, const DecodePlan &p) {
   const long long workgroups = (long long)c->L.B * c->L.Hk * (p.n_splits > 1 ? p.n_splits : 1);
   return p.passes == 1 && (p.n_splits >= kMinSplitsForOneLaunch || workgroups <= c->n_cus);

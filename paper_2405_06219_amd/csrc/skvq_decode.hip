@@ -47,8 +47,10 @@ __device__ __forceinline__ float wave_sum(float v) {
 // Bound by latency (17 KB per workgroup): what counts is the chain from the launch to the store.  So
 // every wavefront works out all weights itself, lane i holding those of partials i and 64 + i, while the
 // partials' values are on their way: one memory round trip and one barrier.  A pass over eight layers against
-// 1024 threads, wavefront 0's weights through LDS and shuffles: 32 q / 8 kv heads, 131072 tokens, 181 -> 177 us
-// (32 partials a row), 100003 tokens in two groups 167 -> 163, four query tokens 221 -> 216.
+// 1024 threads, wavefront 0's weights through LDS and shuffles: 32 q / 8 kv heads, 131072 tokens, 177 -> 174 us
+// (32 partials a row), 100003 tokens in two groups 167 -> 160, four query tokens 218 -> 214.  Traced alone the kernel
+// takes as long as before (3.9 us, four query tokens 5.2): what is shorter is the way from the chunks' end to it.
+// Behind the chunks it costs 1.5 - 2.4 us a call (against calls without it).
 constexpr int kMergeThreads = 256, kMergeSlices = 8;
 static_assert(kMergeThreads == kMergeSlices * kD / 4, "one thread per slice and four channels");
 __global__ __launch_bounds__(kMergeThreads) void merge_kernel(Layout L, float *__restrict__ out_f32,

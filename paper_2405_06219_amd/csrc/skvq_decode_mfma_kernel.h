@@ -9,7 +9,7 @@
 // chunks the workgroup that ends last combines the partials (merge_by_last); many leave them to
 // merge_kernel.  (With many, merging inside this launch takes as long as the second launch or longer:
 // acknowledgement 0.3 us + ticket 0.8 us + reading and combining 32 partials 1.6 - 2.8 us on the slowest
-// workgroup's tail, against 3.0 us for merge_kernel, of which 2.0 us is what any dependent launch costs.
+// workgroup's tail, against 1.5 - 2.4 us for merge_kernel, nearly all of it what any dependent launch costs.
 // With device-scope fences each fence writes back and invalidates a whole L2: 25 us over 256
 // workgroups.)
 //
@@ -234,7 +234,12 @@ constexpr int kNW = 8;              // wavefronts per workgroup (2 per SIMD: 256
 constexpr int kThreads = 64 * kNW;
 constexpr int kOldShare = 3, kYoungShare = 2;                        // tiles per deal: waves 0..3 / 4..7
 constexpr int kDealPeriod = (kNW / 2) * (kOldShare + kYoungShare);  // tiles per deal
-constexpr int kAppendLagTiles = 12;  // tiles that the workgroup which also appends the new token is spared
+// Tiles that the workgroup which also appends the new token is spared: its two appending wavefronts start later, and
+// they are of the four that get three tiles where the others get two.  us per step with 0, 4, 8 and 12: 32 q / 8 kv heads x
+// 131072 tokens 22.05, 21.98, 21.74, 21.54; 100003 tokens in two groups 20.84, 20.50, 20.13, 20.17; eight rows (the
+// sixteen-row kernel, where all wavefronts wait for the append) 100000 tokens in two groups 29.96, 28.80, 28.67, 28.55;
+// 32 heads x 32768 tokens 19.63, 19.68, 19.59, 19.82 (runs differ by 0.2).
+constexpr int kAppendLagTiles = 12;
 constexpr int kPackedWave = 3;       // the wavefront (last in line for ring slices) that takes the token packed in the same call
 constexpr int kRingWaves = kNW;     // every wavefront of a workgroup may own ring slices
 constexpr int kRingSlice = 4;       // ring tokens per slice (the slice code reads four rows of 16 lanes)
@@ -404,8 +409,8 @@ struct RingData {
 // instructions on divisions: the share of the packed tiles per chunk and the ring's first row.
 struct ChunkPlan {
   int tiles_q;     // chunk sp holds tiles_q tiles, one more from chunk first_long on: a share of the
-  int first_long;  //   tiles plus, when the last chunk's workgroup also appends the new token, the
-                   //   kAppendLagTiles it is spared (the last chunk ends at the last tile either way)
+  int first_long;  //   tiles plus, when the last chunk's workgroup also appends the new token and the chunks
+                   //   are long, the kAppendLagTiles it is spared (the last chunk ends at the last tile either way)
   int slot0;       // ring row of the window's oldest token
   int new_slot;    // ... and of the newest one (the one taken along)
   // bytes from one (sequence, kv head) to the next: key rows, value blocks, (scale, zero), fp16 rows
@@ -436,7 +441,8 @@ inline ChunkPlan plan_chunks(const Layout &L, long long T, long long nq, int n_s
 // Up to kMaxMergeLast chunks this takes less than the second launch, us per step: 32 heads x 32768 tokens
 // (8 chunks) 20.9 -> 19.8, 8 x 8 kv heads x 6007 tokens 4-bit (4 chunks, four rows) with its prefill's
 // share 24.5 -> 23.4; the same 12 or more chunks take longer this way (32 chunks, four rows, 131072 tokens:
-// 21.5 -> 23.5), and merge_kernel combines them.
+// 21.5 -> 23.5, against a merge_kernel that took 0.3 - 0.5 us longer than the present one), and merge_kernel
+// combines them.
 template <int R>
 __device__ __forceinline__ void merge_by_last(const float *base, int *ticket, int n_splits, int tid,
                                               bool row_exists, int &shared, float *out_f32, __half *out_f16) {
@@ -544,8 +550,7 @@ __global__ __launch_bounds__(kThreads, 2) void decode_mfma_kernel(Layout L, cons
   }
 
   // ---- this chunk, this wave's tiles ----
-  // (with the new token taken along the last chunk is shorter by about the time its workgroup
-  // spends on the append)
+  // (with the new token taken along the last of long chunks is shorter: kAppendLagTiles)
   const int n_tiles = (int)((nq_tiles + 63) >> 6);
   // (the later chunks hold the odd tiles)
   const int n_long = sp > plan.first_long ? sp - plan.first_long : 0;  // longer chunks before this one

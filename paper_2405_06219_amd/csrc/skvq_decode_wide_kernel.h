@@ -155,7 +155,9 @@ __global__ __launch_bounds__(kThreads, 2) void decode_wide_kernel(Layout L, cons
   const int pk0 = L.perm_k[hk * kD + lane], pk1 = L.perm_k[hk * kD + 64 + lane];
   const int pv = L.perm_v[hk * kD + (tid & 127)];  // for the epilogue
 
-  // ---- the new token taken along: as in decode_mfma_kernel ----
+  // ---- the new token taken along: by the same two wavefronts as in decode_mfma_kernel, but ahead of everything else:
+  //      here the tiles hold the packed row too, so the last chunk's workgroup waits until it is stored (its chunk is
+  //      the shorter for it: kAppendLagTiles) ----
   const bool fused = knew != nullptr;
   if (fused && sp == n_splits - 1) {
     if (wave < 2) append_token(L, knew, vnew, T - 1, plan.new_slot, -1, te, hk, b, wave, lane, sm.append);

@@ -364,12 +364,15 @@ def test_fp8_pairs_of_every_fp16_number():
 
 # Partials combined by the merge launch, at the edges of its slices (8), batches (32) and sets of lanes (64): against
 # the oracle, and against one chunk (the same fp32 sums in another order: 1e-5 of the largest output, as in the
-# parity tests of split counts).  The workspace holds NaNs before each call.
-@pytest.mark.parametrize("splits", [2, 9, 31, 32, 33, 64, 65, 96, 97, 127, 128])
-def test_merge_at_its_edges(splits):
+# parity tests of split counts).  The workspace holds NaNs before each call.  Up to eight partials reach the merge
+# launch from more than four rows per kv head (four groups: always several workgroups of four); of one row two are
+# combined in the launch, for comparison.
+@pytest.mark.parametrize("hq,hk,group,splits", [(8, 1, 32, n) for n in (2, 3, 7, 8, 9)] + [(2, 2, 128, 2)] +
+                         [(2, 2, 128, n) for n in (9, 31, 32, 33, 64, 65, 96, 97, 127, 128)])
+def test_merge_at_its_edges(hq, hk, group, splits):
     from paper_2405_06219_amd import synth
-
-    w = synth.Workload("merge", 2, 2, 2, 64 * 128 + 16, 2.0, window=16, seed=33)
+    print("case", hq, hk, group, splits, flush=True)
+    w = synth.Workload("merge", 2, hq, hk, 64 * 128 + 16, 2.0, group_size=group, window=16, seed=33)
     pair, k, v, q = P.make_pair(w, extra_tokens=1)
     pair.prefill(k, v)
     qd, ref, outs = torch.from_numpy(q).cuda(), pair.ref.decode(q), []
@@ -379,3 +382,5 @@ def test_merge_at_its_edges(splits):
         outs.append(pair.gpu.skvq_decode_attention(qd).cpu().numpy())
         assert np.abs(outs[-1] - ref).max() <= P.TOL, n
     assert np.abs(outs[1] - outs[0]).max() <= 1e-5 * max(1.0, np.abs(ref).max())
+    names = decode_kernels(lambda: pair.gpu.skvq_decode_attention(qd))
+    assert ("merge_kernel" in names) == (hq // hk > 4 or splits > 8), names
