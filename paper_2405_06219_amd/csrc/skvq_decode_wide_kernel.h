@@ -24,8 +24,8 @@
 // At short caches, and where the compute units have room for the other workgroups, four rows a workgroup are
 // faster (up to twice: plan_decode in skvq_api.hip chooses).
 // All 256 registers are in use.  With one group per head the tile loop spills nothing, and four of the 21
-// instances five or six registers around it; with two groups every instance spills: 3 - 11 registers with 2-bit
-// keys and 2-bit or 3-level values, 9 - 21 with 4 bits on one side, 17 - 27 on both, 26 - 32 with 3 bits.  With
+// instances one to five registers around it; with two groups every instance spills: 3 - 10 registers with 2-bit
+// keys and 2-bit or 3-level values, 9 - 20 with 4 bits on one side, 17 - 26 on both, 25 - 31 with 3 bits.  With
 // four groups or unequal ones it would be slower than the workgroups of four rows at any length (measured at
 // 131072 and 60000 tokens: 46 -> 88 and 52 -> 54 us a call), so it is not built for them.
 #pragma once
