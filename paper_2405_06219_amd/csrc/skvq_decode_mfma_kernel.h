@@ -240,9 +240,8 @@ constexpr int kDealPeriod = (kNW / 2) * (kOldShare + kYoungShare);  // tiles per
 // sixteen-row kernel, where all wavefronts wait for the append) 100000 tokens in two groups 29.96, 28.80, 28.67, 28.55;
 // 32 heads x 32768 tokens 19.63, 19.68, 19.59, 19.82 (runs differ by 0.2).
 constexpr int kAppendLagTiles = 12;
-constexpr int kPackedWave = 3;       // the wavefront (last in line for ring slices) that takes the token packed in the same call
+constexpr int kPackedWave = 2;       // the wavefront (late in line for ring slices) that takes the token packed in the same call
 constexpr int kRingWaves = kNW;     // every wavefront of a workgroup may own ring slices
-constexpr int kRingSlice = 4;       // ring tokens per slice (the slice code reads four rows of 16 lanes)
 
 constexpr int kCombStride = kD + 16;  // floats; the padding spreads the accumulator columns over the banks
 
@@ -261,7 +260,7 @@ struct Smem {
     uint2_t high[TERNARY ? 81 : 1];  // (before the first tile) see build_ternary_table
   } wb[kNW];
   static_assert(sizeof(WaveBuf) % 16 == 0, "an array of them keeps the alignment");
-  float qraw[4][kD];                   // the query heads as loaded (rows >= R are zero)
+  alignas(16) _Float16 qraw[4][kD];    // the query heads as loaded (rows >= R are zero)
   _Float16 qa[32][4][4];               // A operands of the score product: [step][head][k slot]
   alignas(16) float qpart[4][8];       // per head: sums of the reordered query over 16 positions each
   alignas(16) float qtotal[4];         // per head: the sum of the whole query (one group per head)
@@ -270,7 +269,7 @@ struct Smem {
   // ([head][...][wave]: the epilogue reads a head's eight entries as two 16-byte pieces)
   alignas(16) float wm[R][kNW], wl[R][kNW], wz[R][NG][kNW], rm[R][kNW], rl[R][kNW];
   AppendScratch append;                // (the workgroup of the last chunk)
-  float ring_o[kNW][R][kD];            // per wave: its ring slices' outputs, original channel order
+  alignas(16) float ring_o[kNW][R][kD];  // per wave: its ring slices' outputs, original channel order
   int ticket;                          // kMergeLast: workgroups of the kv head that ended before this one
 };
 
@@ -399,11 +398,22 @@ __device__ __forceinline__ void ternary_fields(const Unit16 &raw, const int sh, 
   f[7] = __builtin_amdgcn_alignbit(u3, u2, 23) & 0x1fff0u;
 }
 
-// What one wavefront loads for one slice of 4 fp16 ring tokens.
+// What one wavefront loads for one slice of fp16 tokens: four tokens for one or two rows, eight for more, which go
+// through the matrix cores (see the ring slices below).
+constexpr bool ring_by_matrix(int rows) { return rows > 2; }
+template <bool MATRIX>
 struct RingData {
-  uint4_t k;      // lane (token = l/16, piece = l%16): 8 channels of the token's key row
-  unsigned v[4];  // lane = channel pair: the 4 tokens' values of channels 2l, 2l+1
+  static constexpr int kTokens = 8;
+  uint4_t k[4];   // lane (token = l % 8, quarter h = l / 16): channels 32 s + 8 h .. + 7 of the token's key row
+  unsigned v[8];  // lane = channel pair: the tokens' values of channels 2l, 2l + 1
 };
+template <>
+struct RingData<false> {
+  static constexpr int kTokens = 4;
+  uint4_t k[1];   // lane (token = l / 16, piece l % 16): 8 channels of the token's key row
+  unsigned v[4];
+};
+constexpr float kRingBias = 14.0f;  // the matrix cores' weights of a slice are at most 2^14
 
 // What the host works out once per launch, so that no workgroup spends its first few hundred
 // instructions on divisions: the share of the packed tiles per chunk and the ring's first row.
@@ -633,10 +643,14 @@ __global__ __launch_bounds__(kThreads, 2) void decode_mfma_kernel(Layout L, cons
   // the window's tokens.
   const int n_win = (int)(T - nq) - n_sink, W = L.W;
   const int n_fp = n_sink + n_win;
+  constexpr bool kRingMatrix = ring_by_matrix(R);
+  typedef RingData<kRingMatrix> Ring;
+  constexpr int kRingSlice = Ring::kTokens;
   const int n_slices = (n_fp + kRingSlice - 1) / kRingSlice;
   const int ring_stride = n_splits * kRingWaves;
   // the younger waves (which get fewer tiles) are first in line for ring slices
-  const int ring_rank = (wave + kNW / 2) % kNW;
+  // (from the last wavefront down: a share's odd tiles go to the first ones)
+  const int ring_rank = kNW - 1 - wave;
   const int ring_first = sp + n_splits * ring_rank;
   const bool ring_owner = ring_first < n_slices;
   const int slot0 = plan.slot0;  // ring row of the window's oldest token
@@ -646,21 +660,23 @@ __global__ __launch_bounds__(kThreads, 2) void decode_mfma_kernel(Layout L, cons
   // (ring token t, clamped to the last one, sits in sink row W + t if it is a sink, else in ring
   // slot slot0 + t - n_sink modulo W; the newest token's row is the caller's when it is taken along)
   auto load_ring = [&](int slice) {
-    RingData d;
-    // Lane (token l/16 of the slice, piece l%16) works out the row of its own token with vector
-    // arithmetic (the same for every slice: no scalar branches per row); the four value rows take
-    // theirs from lanes 0, 16, 32 and 48.
-    const int t = min(slice * kRingSlice + (lane >> 4), n_fp - 1);
+    Ring d;
+    // Every lane works out the row of its own token of the slice with vector arithmetic (the same for
+    // every slice: no scalar branches per row); the value rows take theirs from a lane of each token.
+    constexpr int kStep = kRingMatrix ? 1 : 16;  // from a token's lane to the next token's
+    const int t = min(slice * kRingSlice + (kRingMatrix ? lane & 7 : lane >> 4), n_fp - 1);
     const int s = slot0 + t - n_sink;
     const int slot = t < n_sink ? W + t : (s >= W ? s - W : s);
     const int fresh = fused && t >= n_fp - 1 ? 1 : 0;  // the caller's row of the new token
     const unsigned row_bytes = (unsigned)slot * (unsigned)(kD * sizeof(__half));
     const char *krow = fresh ? reinterpret_cast<const char *>(knew + (size_t)head * kD) : kwin + row_bytes;
-    d.k = reinterpret_cast<const uint4_t *>(krow)[lane & 15];
+#pragma unroll
+    for (int x = 0; x < (kRingMatrix ? 4 : 1); ++x)
+      d.k[x] = reinterpret_cast<const uint4_t *>(krow)[kRingMatrix ? 4 * x + (lane >> 4) : lane & 15];
 #pragma unroll
     for (int k = 0; k < kRingSlice; ++k) {
-      const unsigned vb = (unsigned)__builtin_amdgcn_readlane((int)row_bytes, 16 * k);
-      const char *vrow = __builtin_amdgcn_readlane(fresh, 16 * k) ? reinterpret_cast<const char *>(vnew + (size_t)head * kD) : vwin + vb;
+      const unsigned vb = (unsigned)__builtin_amdgcn_readlane((int)row_bytes, kStep * k);
+      const char *vrow = __builtin_amdgcn_readlane(fresh, kStep * k) ? reinterpret_cast<const char *>(vnew + (size_t)head * kD) : vwin + vb;
       d.v[k] = reinterpret_cast<const unsigned *>(vrow)[lane];
     }
     return d;
@@ -669,7 +685,7 @@ __global__ __launch_bounds__(kThreads, 2) void decode_mfma_kernel(Layout L, cons
   // ---- prologue: one memory round trip.  The small loads (query and permutations above, ring
   //      slice here) are issued BEFORE the tile loads: loads return in order, so the staging below
   //      only has to wait for them and not for the two tiles of packed data behind them. ----
-  RingData ring = {};
+  Ring ring = {};
   if (ring_owner) ring = load_ring(ring_first);  // landed before the tile loop either way (see below)
   asm volatile("" ::: "memory");
   // three tile buffers used in turn (no register copies): while one tile is computed the
@@ -677,12 +693,18 @@ __global__ __launch_bounds__(kThreads, 2) void decode_mfma_kernel(Layout L, cons
   // The two wavefronts of a SIMD do not share it evenly: the older one (waves 0..3) is served
   // first and gets through about three tiles while the younger one gets through two.  The
   // tiles are dealt in that ratio (per 20 tiles: three to each older, two to each younger
-  // wave) so that both finish together.
-  const int share = wave < kNW / 2 ? kOldShare : kYoungShare;
-  const int deal_base = wave < kNW / 2 ? wave : kOldShare * (kNW / 2) + (wave - kNW / 2);
+  // wave) so that both finish together.  The first deal goes to the older ones first (they start sooner, the younger
+  // ones have the fp16 slices); in a later one, of which a share's last tiles are a part, they take turns: with all of
+  // a part dealt to the older ones the younger ones of a 49-tile share (100003 tokens in 32 chunks) ended 2 us before
+  // them: 161.2 -> 157.4 us per eight calls, 32 heads x 32768 163.2 -> 161.3.  (Turns from the first deal on: 16 tiles a chunk, 4
+  // kv heads x 8000 tokens with 4-bit values, 12.7 -> 13.3 us a step.)
+  const bool older = wave < kNW / 2;
+  const int share = older ? kOldShare : kYoungShare;
   auto tile_of = [&](int n) {  // n-th tile of this wave
-    const int r = n / share;
-    return tile_begin + kDealPeriod * r + deal_base + (kNW / 2) * (n - share * r);
+    const int r = n / share, j = n - share * r, w = wave % (kNW / 2);
+    const int first = (kNW / 2) * (older ? j : kOldShare + j);                        // old, old, old, young, young
+    const int later = (kNW / 2) * (older ? (j ? j + 1 : 0) : (j ? kOldShare + 1 : 1));  // old, young, old, old, young
+    return tile_begin + kDealPeriod * r + (r ? later : first) + w;
   };
   int n_a = 0, n_b = 1, n_c = 2;
   int tile_a = tile_of(n_a), tile_b = tile_of(n_b), tile_c = tile_of(n_c);
@@ -699,8 +721,7 @@ __global__ __launch_bounds__(kThreads, 2) void decode_mfma_kernel(Layout L, cons
     // LDS serves a wavefront's operations in order) and writes the head's matrix operands and piece
     // sums.  One barrier then covers the operands, the sums and the table.
     if (tid < 256) {
-      sm.qraw[wave][2 * lane] = __low2float(q2);
-      sm.qraw[wave][2 * lane + 1] = __high2float(q2);
+      reinterpret_cast<__half2 *>(sm.qraw[wave])[lane] = q2;
       __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
       __builtin_amdgcn_wave_barrier();
       __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
@@ -713,7 +734,7 @@ __global__ __launch_bounds__(kThreads, 2) void decode_mfma_kernel(Layout L, cons
           k4_slot_of(p, step, kslot, shift);
         else
           k_slot_of(p, step, kslot, shift);
-        const float x = sm.qraw[row][j ? pk1 : pk0];
+        const float x = (float)sm.qraw[row][j ? pk1 : pk0];
         sm.qa[step][row][kslot] = (_Float16)ldexpf(x, 8 - shift);  // exact: a power of two
         both += x;
         if constexpr (UNEQ || NG > 1) {
@@ -785,62 +806,117 @@ __global__ __launch_bounds__(kThreads, 2) void decode_mfma_kernel(Layout L, cons
       }
   }
 
-  // ---- ring slices of this wave (plain vector arithmetic, wave-local) ----
+  // ---- ring slices of this wave (wave-local) ----
+  // One or two rows: plain vector arithmetic, a lane a piece of a token's key, then a channel pair.  More rows:
+  //   scores  S[head][token] by v_mfma_f32_16x16x32_f16: A = the query heads (row x: head x % 4), B = the tokens'
+  //        key rows (column x: token x % 8), so that all sixteen-lane rows hold the scores of all heads,
+  //        and lane row g goes on with head g alone: one maximum, one exponential and one sum for all heads.
+  //   outputs  O[head][channel] by v_mfma_f32_4x4x4_16b_f16, lane = channel pair: A = the weights of four tokens,
+  //        as a high and a low fp16 part (through LDS), B = the pair's values.
+  // (The weights are 2^14 at most: the split keeps 22 bits of those down to 2^-27 of the largest.)
+  // Bound by latency, beside the partner wavefront's tiles.  Four heads by vector arithmetic, one after the other and
+  // four tokens at a time, took 1.3 us a slice, and the slices' owners were the last of their workgroups: us per pass,
+  // before and after, 8 x 8 kv heads x 6007 tokens 4-bit 1248 -> 1200 (48 steps of 19.5 -> 18.5), 8 kv heads x 131072
+  // 173.3 -> 170.9, 16 x 8 x 4000 17.9 -> 17.1 a step.  One and two rows stay with the vector arithmetic: eight tokens through the matrix
+  // cores are twelve requests ahead of the first tile instead of five and two more trips through LDS, 4 heads x 2048
+  // tokens 249 -> 258, 32 x 32768 155 -> 156.5, two rows x 5000 9.46 -> 9.71 a step (x 6000 4-bit 16.2 -> 15.8).
   if (ring_owner || (packs && wave == kPackedWave)) {
-    float rm[R], rl[R], ro[R][2];  // reference, sum of weights, outputs
+    float4_t oe = {0.f, 0.f, 0.f, 0.f}, oo = oe;  // outputs of channels 2l and 2l + 1, [head]
+    float ml[R], sl[R];                           // per head, wave-uniform: reference and sum of weights
 #pragma unroll
-    for (int r = 0; r < R; ++r) rm[r] = -INFINITY, rl[r] = 0.f, ro[r][0] = ro[r][1] = 0.f;
+    for (int r = 0; r < R; ++r) ml[r] = -INFINITY, sl[r] = 0.f;
+    float rm = -INFINITY, rl = 0.f;               // matrix cores: the same, lane row g has head g's
     // query token j sees the fp16 tokens up to its own, index n_fp - n_new + j (all of them if n_new = 1)
-    int ring_last[R];
-#pragma unroll
-    for (int r = 0; r < R; ++r) ring_last[r] = n_new == 1 ? n_fp - 1 : n_fp - n_new + (head0 + r) / L.R;
-    auto ring_slice = [&](const RingData &rd, const int slice) {
-      const int tk = lane >> 4, pc = lane & 15;  // token of the slice, 8-channel piece of its row
-      const int tok = slice * kRingSlice + tk;  // index among the fp16 tokens
-      const bool valid = tok < n_fp;
-      const half8_t x = __builtin_bit_cast(half8_t, rd.k);
-      float p[R][kRingSlice];  // the four tokens' weights, wave-uniform
-#pragma unroll
-      for (int r = 0; r < R; ++r) {
-        const float4_t qa = *reinterpret_cast<const float4_t *>(&sm.qraw[r][8 * pc]);
-        const float4_t qb = *reinterpret_cast<const float4_t *>(&sm.qraw[r][8 * pc + 4]);
-        float s = qa[0] * (float)x[0];
-        s = fmaf(qa[1], (float)x[1], s);
-        s = fmaf(qa[2], (float)x[2], s);
-        s = fmaf(qa[3], (float)x[3], s);
-        s = fmaf(qb[0], (float)x[4], s);
-        s = fmaf(qb[1], (float)x[5], s);
-        s = fmaf(qb[2], (float)x[6], s);
-        s = fmaf(qb[3], (float)x[7], s);
-        s += row_move<kQuadSwap1>(s);
-        s += row_move<kQuadSwap2>(s);
-        s += row_move<kRowHalfMirror>(s);
-        s += row_move<kRowMirror>(s);  // all sixteen lanes of a token now hold its score
-        s = valid && tok <= ring_last[r] ? c * s : -INFINITY;
-        float sk[kRingSlice];  // the four tokens' scores, read from one lane of each row
-#pragma unroll
-        for (int k = 0; k < kRingSlice; ++k)
-          sk[k] = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, s), 16 * k));
-        const float mnew = fmaxf(rm[r], fmaxf(fmaxf(sk[0], sk[1]), fmaxf(sk[2], sk[3])));
-        // (a query token of a multi-token call may see none of a slice's tokens, nor of the earlier
-        // ones: then everything stays zero; -inf minus -inf must not be formed)
-        const float mref = mnew == -INFINITY ? 0.f : mnew;
-        const float f = fast_exp2(rm[r] - mref);  // 0 for the first slice
-#pragma unroll
-        for (int k = 0; k < kRingSlice; ++k) p[r][k] = fast_exp2(sk[k] - mref);  // 0 for tokens past the end
-        rl[r] = rl[r] * f + (p[r][0] + p[r][1]) + (p[r][2] + p[r][3]);
-        ro[r][0] *= f;
-        ro[r][1] *= f;
-        rm[r] = mnew;
-      }
-#pragma unroll
-      for (int k = 0; k < kRingSlice; ++k) {
-        const __half2 v2 = __builtin_bit_cast(__half2, rd.v[k]);
-        const float vx = __low2float(v2), vy = __high2float(v2);
+    auto ring_last = [&](int r) { return n_new == 1 ? n_fp - 1 : n_fp - n_new + (head0 + r) / L.R; };
+    const int group_last = kRingMatrix ? ring_last(lane >> 4) : 0;
+    _Float16 *weights = &sm.wb[wave].pbuf[0][0][0][0];  // [high, low][head][token]
+    auto ring_slice = [&](const Ring &rd, const int slice) {
+      if constexpr (!kRingMatrix) {
+        const int pc = lane & 15;  // 8-channel piece of the token's row
+        const half8_t x = __builtin_bit_cast(half8_t, rd.k[0]);
+        float p[R][kRingSlice];  // the tokens' weights, wave-uniform
 #pragma unroll
         for (int r = 0; r < R; ++r) {
-          ro[r][0] = fmaf(p[r][k], vx, ro[r][0]);
-          ro[r][1] = fmaf(p[r][k], vy, ro[r][1]);
+          const half8_t qx = *reinterpret_cast<const half8_t *>(&sm.qraw[r][8 * pc]);
+          float s = (float)qx[0] * (float)x[0];
+#pragma unroll
+          for (int e = 1; e < 8; ++e) s = fmaf((float)qx[e], (float)x[e], s);
+          s += row_move<kQuadSwap1>(s);
+          s += row_move<kQuadSwap2>(s);
+          s += row_move<kRowHalfMirror>(s);
+          s += row_move<kRowMirror>(s);  // all sixteen lanes of a token now hold its score
+          s = slice * kRingSlice + (lane >> 4) <= ring_last(r) ? c * s : -INFINITY;
+          float sk[kRingSlice];  // the tokens' scores, read from one lane of each row
+#pragma unroll
+          for (int k = 0; k < kRingSlice; ++k)
+            sk[k] = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, s), 16 * k));
+          const float mnew = fmaxf(ml[r], fmaxf(fmaxf(sk[0], sk[1]), fmaxf(sk[2], sk[3])));
+          // (a query token of a multi-token call may see none of a slice's tokens, nor of the earlier
+          // ones: then everything stays zero; -inf minus -inf must not be formed)
+          const float mref = mnew == -INFINITY ? 0.f : mnew;
+          const float f = fast_exp2(ml[r] - mref);  // 0 for the first slice
+#pragma unroll
+          for (int k = 0; k < kRingSlice; ++k) p[r][k] = fast_exp2(sk[k] - mref);  // 0 for tokens past the end
+          sl[r] = sl[r] * f + (p[r][0] + p[r][1]) + (p[r][2] + p[r][3]);
+          oe[r] *= f, oo[r] *= f;
+          ml[r] = mnew;
+        }
+#pragma unroll
+        for (int k = 0; k < kRingSlice; ++k) {
+          const __half2 v2 = __builtin_bit_cast(__half2, rd.v[k]);
+          const float vx = __low2float(v2), vy = __high2float(v2);
+#pragma unroll
+          for (int r = 0; r < R; ++r) {
+            oe[r] = fmaf(p[r][k], vx, oe[r]);
+            oo[r] = fmaf(p[r][k], vy, oo[r]);
+          }
+        }
+      } else {
+        // (four sums of 32 products each, added by the vector ALU: the matrix core truncates what it adds to)
+        float4_t d[4];
+#pragma unroll
+        for (int x = 0; x < 4; ++x)
+          d[x] = __builtin_amdgcn_mfma_f32_16x16x32_f16(*reinterpret_cast<const half8_t *>(&sm.qraw[lane & 3][32 * x + 8 * (lane >> 4)]),
+                                                        __builtin_bit_cast(half8_t, rd.k[x]), float4_t{0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
+        const float4_t sum4 = (d[0] + d[1]) + (d[2] + d[3]);
+        const float upper = lane & 16 ? sum4[3] : sum4[2], lower = lane & 16 ? sum4[1] : sum4[0];
+        const float u = slice * kRingSlice + (lane & 7) <= group_last ? c * (lane & 32 ? upper : lower) : -INFINITY;
+        float top = fmaxf(u, row_move<kQuadSwap1>(u));
+        top = fmaxf(top, row_move<kQuadSwap2>(top));
+        top = fmaxf(top, row_move<kRowHalfMirror>(top));
+        const float mnew = fmaxf(rm, top - kRingBias);
+        const float mref = mnew == -INFINITY ? 0.f : mnew;
+        const float f = fast_exp2(rm - mref);  // 0 for the first slice
+        const float p = fast_exp2(u - mref);   // 0 for tokens past the end
+        float sum = p + row_move<kQuadSwap1>(p);
+        sum += row_move<kQuadSwap2>(sum);
+        sum += row_move<kRowHalfMirror>(sum);
+        rl = fmaf(rl, f, sum);
+        rm = mnew;
+        const auto hi = __builtin_amdgcn_cvt_pkrtz(p, 0.f);
+        weights[(lane >> 4) * 8 + (lane & 7)] = hi[0];
+        weights[32 + (lane >> 4) * 8 + (lane & 7)] = (_Float16)(p - (float)hi[0]);
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+        const half8_t ph = *reinterpret_cast<const half8_t *>(&weights[(lane & 3) * 8]);
+        const half8_t pl = *reinterpret_cast<const half8_t *>(&weights[32 + (lane & 3) * 8]);
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+          const float fr = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, f), 16 * r));
+          oe[r] *= fr, oo[r] *= fr;
+        }
+#pragma unroll
+        for (int k = 0; k < 2; ++k) {
+          const unsigned *v = &rd.v[4 * k];
+          const half4_t ve = h4(__builtin_amdgcn_perm(v[1], v[0], 0x05040100u), __builtin_amdgcn_perm(v[3], v[2], 0x05040100u));
+          const half4_t vo = h4(__builtin_amdgcn_perm(v[1], v[0], 0x07060302u), __builtin_amdgcn_perm(v[3], v[2], 0x07060302u));
+          const half4_t h = k ? __builtin_shufflevector(ph, ph, 4, 5, 6, 7) : __builtin_shufflevector(ph, ph, 0, 1, 2, 3);
+          const half4_t l = k ? __builtin_shufflevector(pl, pl, 4, 5, 6, 7) : __builtin_shufflevector(pl, pl, 0, 1, 2, 3);
+          oe = __builtin_amdgcn_mfma_f32_4x4x4f16(l, ve, oe, 0, 0, 0);
+          oo = __builtin_amdgcn_mfma_f32_4x4x4f16(l, vo, oo, 0, 0, 0);
+          oe = __builtin_amdgcn_mfma_f32_4x4x4f16(h, ve, oe, 0, 0, 0);
+          oo = __builtin_amdgcn_mfma_f32_4x4x4f16(h, vo, oo, 0, 0, 0);
         }
       }
     };
@@ -852,13 +928,20 @@ __global__ __launch_bounds__(kThreads, 2) void decode_mfma_kernel(Layout L, cons
       // several slices: each next one is requested while the current one is computed; those
       // requests queue behind the tile loads, and all of them have landed when this ends
       for (int slice = ring_first; slice < n_slices; slice += ring_stride) {
-        RingData ring_next = ring;
+        Ring ring_next = ring;
         if (slice + ring_stride < n_slices) ring_next = load_ring(slice + ring_stride);
         ring_slice(ring, slice);
         ring = ring_next;
       }
-      asm volatile("" ::"v"(ring.k.x), "v"(ring.k.y), "v"(ring.k.z), "v"(ring.k.w), "v"(ring.v[0]),
-                   "v"(ring.v[1]), "v"(ring.v[2]), "v"(ring.v[3]));
+#pragma unroll
+      for (int k = 0; k < kRingSlice; ++k) asm volatile("" ::"v"(ring.v[k]), "v"(ring.k[kRingMatrix ? k / 2 : 0]));
+    }
+    if constexpr (kRingMatrix) {
+#pragma unroll
+      for (int r = 0; r < R; ++r) {
+        ml[r] = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, rm), 16 * r));
+        sl[r] = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, rl), 16 * r));
+      }
     }
     if (packs && wave == kPackedWave) {
       // the token that is packed in this call (seen by every row: one query token)
@@ -866,21 +949,20 @@ __global__ __launch_bounds__(kThreads, 2) void decode_mfma_kernel(Layout L, cons
       const float2 v2 = *reinterpret_cast<const float2 *>(&sm.append.read_back[1][2 * lane]);
 #pragma unroll
       for (int r = 0; r < R; ++r) {
-        const float2 q2r = *reinterpret_cast<const float2 *>(&sm.qraw[r][2 * lane]);
-        const float sum = wave_sum_in_last_lane(fmaf(q2r.x, k2.x, q2r.y * k2.y));
+        const __half2 q2r = reinterpret_cast<const __half2 *>(sm.qraw[r])[lane];
+        const float sum = wave_sum_in_last_lane(fmaf(__low2float(q2r), k2.x, __high2float(q2r) * k2.y));
         const float s = c * __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, sum), 63));
-        const float mnew = fmaxf(rm[r], s), f = fast_exp2(rm[r] - mnew), p = fast_exp2(s - mnew);
-        rl[r] = fmaf(rl[r], f, p);
-        ro[r][0] = fmaf(ro[r][0], f, p * v2.x);
-        ro[r][1] = fmaf(ro[r][1], f, p * v2.y);
-        rm[r] = mnew;
+        const float mnew = fmaxf(ml[r], s), f = fast_exp2(ml[r] - mnew), p = fast_exp2(s - mnew);
+        sl[r] = fmaf(sl[r], f, p);
+        oe[r] = fmaf(oe[r], f, p * v2.x);
+        oo[r] = fmaf(oo[r], f, p * v2.y);
+        ml[r] = mnew;
       }
     }
 #pragma unroll
     for (int r = 0; r < R; ++r) {
-      sm.ring_o[wave][r][2 * lane] = ro[r][0];
-      sm.ring_o[wave][r][2 * lane + 1] = ro[r][1];
-      if (lane == 0) sm.rm[r][wave] = rm[r], sm.rl[r][wave] = rl[r];
+      *reinterpret_cast<float2 *>(&sm.ring_o[wave][r][2 * lane]) = make_float2(oe[r], oo[r]);
+      if (lane == 0) sm.rm[r][wave] = ml[r], sm.rl[r][wave] = sl[r];
     }
   } else if (lane < R) {
     sm.rm[lane][wave] = -INFINITY;

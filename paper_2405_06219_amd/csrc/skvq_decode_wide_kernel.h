@@ -34,6 +34,12 @@
 namespace skvq {
 namespace {
 
+constexpr int kWideSlice = 4;                    // fp16 tokens per slice
+// What one wavefront loads for one slice.
+struct WideRing {
+  uint4_t k;      // lane (token = l/16, piece = l%16): 8 channels of the token's key row
+  unsigned v[4];  // lane = channel pair: the 4 tokens' values of channels 2l, 2l+1
+};
 constexpr int kRowQuad = 4;                      // rows that one wavefront serves in a fp16 slice
 static_assert(kWideTeams == kNW / (kWideRows / kRowQuad), "wavefronts per row quad");
 constexpr int kWideStride = kD + 4;  // floats per staged output row: sixteen rows on different banks
@@ -258,7 +264,7 @@ __global__ __launch_bounds__(kThreads, 2) void decode_wide_kernel(Layout L, cons
   //      team is first in line ----
   const int n_win = (int)(T - nq) - n_sink, W = L.W;
   const int n_fp = n_sink + n_win;
-  const int n_slices = (n_fp + kRingSlice - 1) / kRingSlice;
+  const int n_slices = (n_fp + kWideSlice - 1) / kWideSlice;
   const int ring_stride = n_splits * kWideTeams;
   const int quad = wave % (kNW / kWideTeams), team = kWideTeams - 1 - wave / (kNW / kWideTeams);
   const int ring_first = sp + n_splits * team;
@@ -266,9 +272,11 @@ __global__ __launch_bounds__(kThreads, 2) void decode_wide_kernel(Layout L, cons
   const int slot0 = plan.slot0;
   const __half *kwin = L.k_win + head * (W + L.S) * kD;
   const __half *vwin = L.v_win + head * (W + L.S) * kD;
-  auto load_ring = [&](int slice) {  // as in decode_mfma_kernel
-    RingData d;
-    const int t = min(slice * kRingSlice + (lane >> 4), n_fp - 1);
+  // (fp16 token t, clamped to the last one, sits in sink row W + t if it is a sink, else in ring slot
+  // slot0 + t - n_sink modulo W; the newest token's row is the caller's when it is taken along)
+  auto load_ring = [&](int slice) {
+    WideRing d;
+    const int t = min(slice * kWideSlice + (lane >> 4), n_fp - 1);
     const int s = slot0 + t - n_sink;
     const int slot = t < n_sink ? W + t : (s >= W ? s - W : s);
     const int fresh = fused && t >= n_fp - 1 ? 1 : 0;
@@ -277,7 +285,7 @@ __global__ __launch_bounds__(kThreads, 2) void decode_wide_kernel(Layout L, cons
                              : reinterpret_cast<const char *>(kwin) + row_bytes;
     d.k = reinterpret_cast<const uint4_t *>(krow)[lane & 15];
 #pragma unroll
-    for (int k = 0; k < kRingSlice; ++k) {
+    for (int k = 0; k < kWideSlice; ++k) {
       const unsigned vb = (unsigned)__builtin_amdgcn_readlane((int)row_bytes, 16 * k);
       const char *vrow = __builtin_amdgcn_readlane(fresh, 16 * k) ? reinterpret_cast<const char *>(vnew + head * kD)
                                                                    : reinterpret_cast<const char *>(vwin) + vb;
@@ -287,7 +295,7 @@ __global__ __launch_bounds__(kThreads, 2) void decode_wide_kernel(Layout L, cons
   };
 
   // ---- prologue: small loads, two tiles, the table and the queries' staging in their shadow ----
-  RingData ring = {};
+  WideRing ring = {};
   if (ring_owner) ring = load_ring(ring_first);
   asm volatile("" ::: "memory");
   const int share = wave < kNW / 2 ? kOldShare : kYoungShare;
@@ -374,11 +382,11 @@ __global__ __launch_bounds__(kThreads, 2) void decode_wide_kernel(Layout L, cons
 #pragma unroll
       for (int r = 0; r < kRowQuad; ++r)
         ring_last[r] = n_new == 1 ? n_fp - 1 : n_fp - n_new + (row0 + kRowQuad * quad + r) / L.R;
-      auto ring_slice = [&](const RingData &rd, const int slice) {
-        const int tok = slice * kRingSlice + (lane >> 4), pc = lane & 15;
+      auto ring_slice = [&](const WideRing &rd, const int slice) {
+        const int tok = slice * kWideSlice + (lane >> 4), pc = lane & 15;
         const bool valid = tok < n_fp;
         const half8_t x = __builtin_bit_cast(half8_t, rd.k);
-        float p[kRowQuad][kRingSlice];
+        float p[kRowQuad][kWideSlice];
 #pragma unroll
         for (int r = 0; r < kRowQuad; ++r) {
           const half8_t qr = *reinterpret_cast<const half8_t *>(&sm.qraw[kRowQuad * quad + r][8 * pc]);
@@ -390,23 +398,23 @@ __global__ __launch_bounds__(kThreads, 2) void decode_wide_kernel(Layout L, cons
           s += row_move<kRowHalfMirror>(s);
           s += row_move<kRowMirror>(s);  // all sixteen lanes of a token now hold its score
           s = valid && tok <= ring_last[r] ? c * s : -INFINITY;
-          float sk[kRingSlice];
+          float sk[kWideSlice];
 #pragma unroll
-          for (int k = 0; k < kRingSlice; ++k)
+          for (int k = 0; k < kWideSlice; ++k)
             sk[k] = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, s), 16 * k));
           const float mnew = fmaxf(rm[r], fmaxf(fmaxf(sk[0], sk[1]), fmaxf(sk[2], sk[3])));
           // (a row may see none of a slice's tokens, nor of the earlier ones: everything stays zero)
           const float mref = mnew == -INFINITY ? 0.f : mnew;
           const float f = fast_exp2(rm[r] - mref);
 #pragma unroll
-          for (int k = 0; k < kRingSlice; ++k) p[r][k] = fast_exp2(sk[k] - mref);
+          for (int k = 0; k < kWideSlice; ++k) p[r][k] = fast_exp2(sk[k] - mref);
           rl[r] = rl[r] * f + (p[r][0] + p[r][1]) + (p[r][2] + p[r][3]);
           ro[r][0] *= f;
           ro[r][1] *= f;
           rm[r] = mnew;
         }
 #pragma unroll
-        for (int k = 0; k < kRingSlice; ++k) {
+        for (int k = 0; k < kWideSlice; ++k) {
           const __half2 v2 = __builtin_bit_cast(__half2, rd.v[k]);
           const float vx = __low2float(v2), vy = __high2float(v2);
 #pragma unroll
@@ -420,7 +428,7 @@ __global__ __launch_bounds__(kThreads, 2) void decode_wide_kernel(Layout L, cons
         ring_slice(ring, ring_first);
       } else {
         for (int slice = ring_first; slice < n_slices; slice += ring_stride) {
-          RingData ring_next = ring;
+          WideRing ring_next = ring;
           if (slice + ring_stride < n_slices) ring_next = load_ring(slice + ring_stride);
           ring_slice(ring, slice);
           ring = ring_next;

@@ -31,3 +31,26 @@ def test_packed_row_at_the_edges(P, hq, hk, k_bits, v_bits, group, meta, packed,
         out, ref = pair.append_decode_both(*synth.make_new_token(w, s), q)
         assert np.abs(out - ref).max() <= P.TOL, s
         pair.assert_buffers_equal()
+
+
+@pytest.mark.parametrize("hq,hk,n_new", [(3, 1, 1), (8, 2, 1), (2, 2, 2), (1, 1, 4)])
+@pytest.mark.parametrize("context,window,sinks", [(4, 64, 0), (7, 64, 0), (8, 64, 0), (9, 64, 0), (17, 64, 0), (64, 64, 0), (200, 200, 0),
+                                                  (75, 16, 5), (40, 9, 1)])
+def test_fp16_tokens_in_slices(P, hq, hk, n_new, context, window, sinks):
+    # three and four rows take the fp16 tokens eight at a time through the matrix cores, two rows four at a time
+    w = synth.Workload("slices", 2, hq, hk, context, 2.0, window=window, seed=77)
+    pair, k, v, _ = P.make_pair(w, extra_tokens=16, n_sink=sinks, max_new_tokens=n_new)
+    pair.prefill(k, v)
+    pair.gpu.skvq_set_num_splits(1)
+    for s in range(6):  # (the ring's oldest row is not its first one afterwards)
+        kn, vn = synth.make_new_token(w, s)
+        pair.append(kn, vn)
+        k, v = np.concatenate([k, kn[:, :, None]], 2), np.concatenate([v, vn[:, :, None]], 2)
+    q = np.random.default_rng(context).standard_normal((2, n_new, hq, 128)).astype(np.float16)
+    out = pair.gpu.skvq_decode_attention_multi(torch.from_numpy(q).to(pair.device)).cpu().numpy()
+    # a score of 128 products summed in 32 bits (base-2 exponent: times 1.45) shifts a weight by as much, and a weight's
+    # two fp16 parts keep 22 bits; both once in the sum of weights and once in the outputs
+    kq = np.repeat(np.abs(k.astype(np.float64)), hq // hk, 1)
+    score = 1.45 * (np.abs(q.astype(np.float64)).transpose(0, 2, 1, 3) @ kq.transpose(0, 1, 3, 2)).max() / np.sqrt(128.0)
+    bound = 2 * (136 * 2.0 ** -24 * score + 2.0 ** -21) * np.abs(v.astype(np.float64)).max()
+    assert np.abs(out - pair.ref.decode_multi(q)).max() <= bound
