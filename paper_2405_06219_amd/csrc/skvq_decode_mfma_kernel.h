@@ -50,6 +50,7 @@
 namespace skvq {
 namespace {
 
+typedef _Float16 half2_t __attribute__((ext_vector_type(2)));
 typedef _Float16 half4_t __attribute__((ext_vector_type(4)));
 typedef _Float16 half8_t __attribute__((ext_vector_type(8)));
 typedef float float4_t __attribute__((ext_vector_type(4)));
@@ -152,6 +153,13 @@ __device__ __forceinline__ float wave_max(float v) {
   return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), 63));
 }
 
+// The transposing LDS read: every sixteen lanes read four rows of sixteen fp16 numbers, lane i the 8 bytes at its
+// address (row i / 4, columns 4 (i % 4) ..), and lane i receives column i of the four rows.
+__device__ __forceinline__ half4_t transposed_read(const _Float16 *p) {
+  typedef __fp16 fp16x4_t __attribute__((__vector_size__(4 * sizeof(__fp16))));
+  return __builtin_bit_cast(half4_t, __builtin_amdgcn_ds_read_tr16_b64_v4f16((__attribute__((address_space(3))) fp16x4_t *)p));
+}
+
 __device__ __forceinline__ half4_t h4(unsigned a, unsigned b) { return __builtin_bit_cast(half4_t, uint2_t{a, b}); }
 
 // Key dword (16 codes, position e at bit 2e) -> four B operands of the 4x4x4 product.
@@ -245,17 +253,36 @@ constexpr int kRingWaves = kNW;     // every wavefront of a workgroup may own ri
 
 constexpr int kCombStride = kD + 16;  // floats; the padding spreads the accumulator columns over the banks
 
+// The weights of a tile on their way from lane = token to the B operand of the value product (lane = column, eight
+// tokens): a row per token that the lane writes as it has it -- per group the high fp16 parts of the heads, then the low
+// ones -- in 16-byte pieces, read back through the transposing LDS read (16 lanes: four rows of sixteen columns,
+// turned).  The product has sixteen columns: an operand takes all groups that fit beside one another (two with four
+// rows), and a channel tile's results are those of its own group's columns.
+// Bound: the tile's serial chain.  A column per LDS row took a 2-byte store per number (8 a tile with four heads, 16 and 32
+// with two and four groups) and an operand per group; now 1, 2 and 4 stores of 16 bytes.  us per pass, before and after: 4 x 8
+// kv heads x 602976 tokens in four groups, four rows 290.0 -> 271.4, eight calls of 100003 tokens in two groups 153.4 -> 151.5, 48
+// steps of 8 x 8 kv heads x 6007 tokens 4-bit with their prompts 1191 -> 1187, one group the same.
+template <int R, int NG>
+struct Weights {
+  static constexpr int kAll = 2 * R * NG;                                // columns that mean something
+  static constexpr int kOps = kAll > 16 ? kAll / 16 : 1;                 // operands of a block of 32 tokens
+  static constexpr int kCols = kAll > 16 ? 16 : kAll < 4 ? 4 : kAll;     // columns of a row (8 bytes at least)
+  // first column and operand of a group
+  __device__ static constexpr int column(int g) { return (2 * R * g) % 16; }
+  __device__ static constexpr int operand(int g) { return 2 * R * g / 16; }
+};
+
 template <int R, bool TERNARY, int NG>
 struct Smem {
   // 13-bit field -> the A operand of its eight tokens (104976 bytes, built by the workgroup:
   // four base-3 digits -> the operand halves of tokens 0..3 / 4..7)
   uint4_t lut[TERNARY ? 6561 : 1];
-  // per wave: the weights of the current tile, [block][group][column][token slot]; after the
+  // per wave: the weights of the current tile, [operand][token row][column]; after the
   // wave's last tile the same bytes stage its O^T, [head][reordered position]
   // (weights and outputs go 16 bytes at a time: every wavefront's copy is a multiple of 16 bytes, which high's
   // 648 are not)
   union alignas(16) WaveBuf {
-    _Float16 pbuf[2][NG][2 * R][32];
+    _Float16 pbuf[Weights<R, NG>::kOps][64][Weights<R, NG>::kCols];
     float stage[R][kCombStride];
     uint2_t high[TERNARY ? 81 : 1];  // (before the first tile) see build_ternary_table
   } wb[kNW];
@@ -829,7 +856,7 @@ __global__ __launch_bounds__(kThreads, 2) void decode_mfma_kernel(Layout L, cons
     // query token j sees the fp16 tokens up to its own, index n_fp - n_new + j (all of them if n_new = 1)
     auto ring_last = [&](int r) { return n_new == 1 ? n_fp - 1 : n_fp - n_new + (head0 + r) / L.R; };
     const int group_last = kRingMatrix ? ring_last(lane >> 4) : 0;
-    _Float16 *weights = &sm.wb[wave].pbuf[0][0][0][0];  // [high, low][head][token]
+    _Float16 *weights = &sm.wb[wave].pbuf[0][0][0];  // [high, low][head][token]
     auto ring_slice = [&](const Ring &rd, const int slice) {
       if constexpr (!kRingMatrix) {
         const int pc = lane & 15;  // 8-channel piece of the token's row
@@ -986,6 +1013,15 @@ __global__ __launch_bounds__(kThreads, 2) void decode_mfma_kernel(Layout L, cons
   for (int n = 0; n < 8; ++n) acc[n] = float4_t{0.f, 0.f, 0.f, 0.f};
   bool first = true;
 
+  // Weights in LDS (see Weights): the rows of every second eight tokens have their halves exchanged, so that the lanes
+  // that a transposing read serves together (two times four rows of 32 bytes, eight rows apart) touch different banks.
+  typedef Weights<R, NG> Weight;
+  constexpr int kPops = Weight::kOps == 1 ? 1 : UNEQ ? 8 : Weight::kOps;
+  _Float16 *weight_row = &sm.wb[wave].pbuf[0][lane ^ ((lane >> 1) & 4)][0];
+  // lane 16 kb + i: row i / 4 of the eight tokens 8 kb .., four columns from 4 (i % 4) on (columns past the row's
+  // last re-read the first ones: nobody reads their results); the other four tokens: exclusive or with four rows
+  const int weight_read = ((8 * (lane >> 4) + ((lane >> 2) & 3)) ^ ((lane >> 2) & 4)) * Weight::kCols + (4 * (lane & 3)) % Weight::kCols;
+
   auto compute_tile = [&](const Tile &cur, const int tile) {
     const bool valid = tile * 64 + lane <= last_token;
 
@@ -1115,7 +1151,6 @@ __global__ __launch_bounds__(kThreads, 2) void decode_mfma_kernel(Layout L, cons
 
     // ---- weights: p = 2^u, P' = p * vscale * beta * 2^-(bit-4), split into high and low fp16 ----
     const float bk = beta * kslot_scale;
-    _Float16 *pw = &sm.wb[wave].pbuf[lane >> 5][0][0][lane & 31];
     // (the high part is the weight converted to fp16 toward zero, two heads per instruction; the
     // low part the fp32 weight minus that fp16 number -- exact -- rounded to fp16 once, as one
     // mixed-precision multiply-add: minus_one is -1 in a form the compiler does not see through)
@@ -1125,6 +1160,7 @@ __global__ __launch_bounds__(kThreads, 2) void decode_mfma_kernel(Layout L, cons
       pr[r] = fast_exp2(u[r]);
       lsum[r] += pr[r];
     }
+    unsigned words[NG * R];  // the token's row: two columns each
 #pragma unroll
     for (int g = 0; g < NG; ++g) {
       const float vsb = vs[g] * bk;
@@ -1133,13 +1169,30 @@ __global__ __launch_bounds__(kThreads, 2) void decode_mfma_kernel(Layout L, cons
         const float pa = pr[r] * vsb, pb = r + 1 < R ? pr[r + 1] * vsb : 0.f;
         const auto hi = __builtin_amdgcn_cvt_pkrtz(pa, pb);
         zacc[r][g] = fmaf(pr[r], vz[g], zacc[r][g]);
-        pw[(g * 2 * R + r) * 32] = hi[0];
-        pw[(g * 2 * R + R + r) * 32] = (_Float16)__builtin_fmaf((float)hi[0], minus_one, pa);
-        if (r + 1 < R) {
+        const half2_t high = __builtin_bit_cast(half2_t, hi);
+        half2_t low;
+        low[0] = (_Float16)__builtin_fmaf((float)hi[0], minus_one, pa);
+        if constexpr (R == 1) {
+          words[g] = __builtin_bit_cast(unsigned, half2_t{high[0], low[0]});
+        } else {
           zacc[r + 1][g] = fmaf(pr[r + 1], vz[g], zacc[r + 1][g]);
-          pw[(g * 2 * R + r + 1) * 32] = hi[1];
-          pw[(g * 2 * R + R + r + 1) * 32] = (_Float16)__builtin_fmaf((float)hi[1], minus_one, pb);
+          low[1] = (_Float16)__builtin_fmaf((float)hi[1], minus_one, pb);
+          words[g * R + r / 2] = __builtin_bit_cast(unsigned, high);
+          words[g * R + R / 2 + r / 2] = __builtin_bit_cast(unsigned, low);
         }
+      }
+    }
+    {
+      constexpr int kPiece = NG * R < 4 ? NG * R : 4;  // words a store
+#pragma unroll
+      for (int w = 0; w < NG * R; w += kPiece) {
+        _Float16 *to = weight_row + (w / 8) * 64 * Weight::kCols + 2 * (w % 8);
+        if constexpr (kPiece == 4)
+          *reinterpret_cast<uint4_t *>(to) = uint4_t{words[w], words[w + 1], words[w + 2], words[w + 3]};
+        else if constexpr (kPiece == 2)
+          *reinterpret_cast<uint2_t *>(to) = uint2_t{words[w], words[w + 1]};
+        else
+          *reinterpret_cast<unsigned *>(to) = words[w];
       }
     }
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
@@ -1147,16 +1200,15 @@ __global__ __launch_bounds__(kThreads, 2) void decode_mfma_kernel(Layout L, cons
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 
     // ---- values: two blocks of 32 tokens, 8 channel tiles each ----
-    const int col = lane & 15, kb = lane >> 4;
 #pragma unroll
     for (int blk = 0; blk < 2; ++blk) {
-      half8_t pop[NACC];  // the weights (B operand) of each group (or piece) of channel tiles
+      half8_t pop[kPops];  // the weights (B operand): all groups', or those of a piece's group
 #pragma unroll
-      for (int x = 0; x < NACC; ++x) {
-        const int g = UNEQ ? piece_group(x) : x;
-        // (columns from 2R on re-read the first ones: nobody reads their results, and an
-        // unconditional read needs neither a zeroed operand nor a change of the execution mask)
-        pop[x] = *reinterpret_cast<const half8_t *>(&sm.wb[wave].pbuf[blk][g][col % (2 * R)][8 * kb]);
+      for (int x = 0; x < kPops; ++x) {
+        const int o = UNEQ && kPops > 1 ? Weight::operand(piece_group(x)) : x;
+        const _Float16 *from = &sm.wb[wave].pbuf[o][32 * blk][0];
+        const half4_t first4 = transposed_read(from + weight_read), last4 = transposed_read(from + (weight_read ^ (4 * Weight::kCols)));
+        pop[x] = __builtin_shufflevector(first4, last4, 0, 1, 2, 3, 4, 5, 6, 7);
       }
       const Unit16 raw = blk ? cur.v10 : cur.v00;
       if constexpr (V4) {
@@ -1164,7 +1216,7 @@ __global__ __launch_bounds__(kThreads, 2) void decode_mfma_kernel(Layout L, cons
         const unsigned w[8] = {raw.x, raw.y, raw.z, raw.w, raw2.x, raw2.y, raw2.z, raw2.w};
 #pragma unroll
         for (int n = 0; n < 8; ++n)
-          acc[n] = __builtin_amdgcn_mfma_f32_16x16x32_f16(unpack_v4_field(w[n]), pop[n * NACC / 8], acc[n], 0, 0, 0);
+          acc[n] = __builtin_amdgcn_mfma_f32_16x16x32_f16(unpack_v4_field(w[n]), pop[n * kPops / 8], acc[n], 0, 0, 0);
       } else if (TERNARY) {
         unsigned f[8];
         ternary_fields(raw, unit_sh, f);
@@ -1174,13 +1226,13 @@ __global__ __launch_bounds__(kThreads, 2) void decode_mfma_kernel(Layout L, cons
           aop[n] = *reinterpret_cast<const uint4_t *>(reinterpret_cast<const char *>(sm.lut) + f[n]);
 #pragma unroll
         for (int n = 0; n < 8; ++n)
-          acc[n] = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(half8_t, aop[n]), pop[n * NACC / 8],
+          acc[n] = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(half8_t, aop[n]), pop[n * kPops / 8],
                                                           acc[n], 0, 0, 0);
       } else if constexpr (V3) {
         const uint2_t top = blk ? cur.vt1 : cur.vt0;
 #define SKVQ_PV3(N, WORD, TOP)                                                                              \
   acc[N] = __builtin_amdgcn_mfma_f32_16x16x32_f16(unpack_v3_field<(N) & 3>(((N) & 1) ? (WORD) >> 8 : (WORD), TOP), \
-                                                  pop[(N) * NACC / 8], acc[N], 0, 0, 0)
+                                                  pop[(N) * kPops / 8], acc[N], 0, 0, 0)
         SKVQ_PV3(0, raw.x, top.x); SKVQ_PV3(1, raw.x, top.x); SKVQ_PV3(2, raw.y, top.x); SKVQ_PV3(3, raw.y, top.x);
         SKVQ_PV3(4, raw.z, top.y); SKVQ_PV3(5, raw.z, top.y); SKVQ_PV3(6, raw.w, top.y); SKVQ_PV3(7, raw.w, top.y);
 #undef SKVQ_PV3
@@ -1189,7 +1241,7 @@ __global__ __launch_bounds__(kThreads, 2) void decode_mfma_kernel(Layout L, cons
 #pragma unroll
         for (int n = 0; n < 8; ++n) {
           const unsigned f = (n & 1) ? (w[n >> 1] >> 8) : w[n >> 1];
-          acc[n] = __builtin_amdgcn_mfma_f32_16x16x32_f16(unpack_v_field(f), pop[n * NACC / 8], acc[n], 0, 0, 0);
+          acc[n] = __builtin_amdgcn_mfma_f32_16x16x32_f16(unpack_v_field(f), pop[n * kPops / 8], acc[n], 0, 0, 0);
         }
       }
     }
@@ -1262,7 +1314,8 @@ __global__ __launch_bounds__(kThreads, 2) void decode_mfma_kernel(Layout L, cons
 #pragma unroll
       for (int rr = 0; rr < 4; ++rr)
         o4[rr] = (acc[n][rr] + row_move<kRowShl + R>(acc[n][rr])) * unscale;  // + column R + r: the low halves' sum
-      if (col < R) *reinterpret_cast<float4_t *>(&sm.wb[wave].stage[col][16 * n + 4 * kb]) = o4;
+      const int head_col = col - Weight::column(UNEQ ? piece_group(n) : n * NG / 8);
+      if (head_col >= 0 && head_col < R) *reinterpret_cast<float4_t *>(&sm.wb[wave].stage[head_col][16 * n + 4 * kb]) = o4;
     }
   }
   __syncthreads();

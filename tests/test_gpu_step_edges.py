@@ -54,3 +54,15 @@ def test_fp16_tokens_in_slices(P, hq, hk, n_new, context, window, sinks):
     score = 1.45 * (np.abs(q.astype(np.float64)).transpose(0, 2, 1, 3) @ kq.transpose(0, 1, 3, 2)).max() / np.sqrt(128.0)
     bound = 2 * (136 * 2.0 ** -24 * score + 2.0 ** -21) * np.abs(v.astype(np.float64)).max()
     assert np.abs(out - pair.ref.decode_multi(q)).max() <= bound
+
+
+@pytest.mark.parametrize("hq,hk", [(1, 1), (2, 1), (4, 1), (7, 1)])
+@pytest.mark.parametrize("group,bounds", [(128, None), (64, None), (32, None), (64, (0, 32, 128)), (32, (0, 16, 32, 64, 128))])
+@pytest.mark.parametrize("packed", [1, 40, 65])
+def test_weights_of_every_row_and_group_count(P, hq, hk, group, bounds, packed):
+    # the weights' columns in LDS: 2, 4 or 8 per group, in one operand of sixteen or two
+    w = synth.Workload("weights", 1, hq, hk, 8 + packed, 1.5, group_size=group, window=8, seed=9)
+    pair, k, v, q = P.make_pair(w, group_bounds=bounds)
+    pair.prefill(k, v)
+    out, ref = pair.decode_both(q)
+    assert np.abs(out - ref).max() <= P.TOL
