@@ -15,7 +15,9 @@
 //
 // One workgroup of 8 wavefronts per chunk (one per compute unit when the cache is long
 // enough).  Per wavefront, per tile of 64 packed tokens:
-//   QK   S^T[head][token] by 32 v_mfma_f32_4x4x4_16b_f16 (16 independent 4x4 blocks, lane =
+//   QK   2- and 4-bit keys in one or two equal groups: S^T[head, part of the query][token] by 4 or 8
+//        v_mfma_scale_f32_16x16x128_f8f6f4 on the codes as FP4 or FP8 numbers (see keys_as_numbers); the others:
+//        S^T[head][token] by 32 v_mfma_f32_4x4x4_16b_f16 (16 independent 4x4 blocks, lane =
 //        token): the B operand is the lane's own 32-byte key row, its 2-bit codes turned into
 //        fp16 SUBNORMALS by one AND each (a code c sitting at mantissa bit s is the fp16 value
 //        c*2^(s-24)); the A operand is the reordered query, pre-multiplied by the matching
@@ -31,7 +33,7 @@
 // The zero-points never enter the matrix products: sum_p q_p (s c_p + z) = s sum q c + z sum q
 // and sum_t w_t (s_t c + z_t) = sum (w_t s_t) c + sum w_t z_t, per group.
 //
-// The matrix core accumulates products of subnormal inputs as if their mantissa were full, so
+// (v_mfma_f32_4x4x4 and the value product:) the matrix core accumulates products of subnormal inputs as if their mantissa were full, so
 // a code at mantissa bit s costs about (10 - s) bits of the accumulator's precision; every
 // 2-bit code is therefore moved to bit 4, 6 or 8 before it is masked out, every 4-bit code to
 // bit 4 (its top bit must stay inside the 10 mantissa bits).  A 3-bit code is its two low bits,
@@ -136,6 +138,12 @@ __device__ __forceinline__ float wave_sum_in_last_lane(float v) {
   v += __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), 0x142, 0xA, 0xF, false));
   v += __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), 0x143, 0xC, 0xF, false));
   return v;
+}
+
+// Bits moved likewise; lanes that nothing reaches get 0.
+template <int CTRL, int ROWS>
+__device__ __forceinline__ unsigned move_bits(unsigned x) {
+  return (unsigned)__builtin_amdgcn_update_dpp(0, (int)x, CTRL, ROWS, 0xf, ROWS == 0xf);
 }
 
 // The maximum over the 64 lanes as a wave-uniform value: the same moves with maxima (rows that a
@@ -272,7 +280,46 @@ struct Weights {
   __device__ static constexpr int operand(int g) { return 2 * R * g / 16; }
 };
 
-template <int R, bool TERNARY, int NG>
+// 2- and 4-bit keys of one and two equal groups go through v_mfma_scale_f32_16x16x128_f8f6f4, sixteen tokens and all 128
+// channels a product, as numbers that need no shifting into place: a 2-bit code in the low bits of an FP4 E2M1 number is
+// code / 2, a 4-bit code in the low bits of an FP8 E4M3 number code / 512.  A dword of codes takes three instructions (ten
+// and seven before) and a tile four products instead of a chain of 32.
+//   The query enters as four FP8 numbers per channel, rows 4 part + head of the A operand, each part the rounded remainder
+// of those before it times 2^kPartBits; the block scales take that back.  The head's largest channel is brought to 8 (2
+// for 4-bit codes): the product adds exactly as long as the largest and the smallest bit of its 128 terms are no more than
+// 2^14.6 apart (values below 16 against halves of codes: no error in 4000 sums; below 32: 6 in 2^-10), and E4M3's smallest
+// step, 2^-9, keeps a part within that.  What the four parts miss is 2^-27 (2^-25) of the largest channel at most; fp16
+// queries are exact down to 2^-14 (2^-12) of it.
+//   Two groups: rows 8 group + 4 (part % 2) + head, zero in the other group's channels, and two products in a chain.
+//   Bound: the tiles' vector and matrix instructions.  us per pass, before and after: eight calls of 32 heads x 32768 tokens
+// 161.8 -> 153.8, 8 kv heads x 131072, four rows, 173.0 -> 167.8, 100003 tokens in two groups 159.3 -> 149.4, 11 x 8 kv heads x 118865
+// 152.4 -> 132.1, 48 steps of 8 x 8 kv heads x 6007 tokens 4-bit with their prompts 1187 -> 1175; 4 heads x 2048, a tile a
+// wavefront, the same (the query's split costs what the products save).
+//   Three-bit codes lie in two planes, four groups would take sixteen products, and unequal groups need a sum per sixteen
+// channels: they keep v_mfma_f32_4x4x4_16b_f16.
+constexpr bool keys_as_numbers(int kl, int ng, bool uneq) { return (kl == 4 || kl == 16) && ng <= 2 && !uneq; }
+typedef int int_x8_t __attribute__((ext_vector_type(8)));
+constexpr int kQueryParts = 4, kPartBits = 5;
+template <bool NUMBERS>
+struct QueryOperands {
+  _Float16 qa[32][4][4];               // A operands of the score product: [step][head][k slot]
+};
+template <>
+struct QueryOperands<true> {
+  alignas(32) uint8_t q8[4 * kQueryParts][kD];  // [4 part + head][k]
+  int exponent[4];                              // per head: its query was multiplied by 2^exponent
+};
+// Lanes 32-63 of a trade places with lanes 0-31 of b (odd rows of sixteen lanes of a with even rows of b); the sum of the two.
+__device__ __forceinline__ float swap_halves_and_add(float a, float b) {
+  const auto r = __builtin_amdgcn_permlane32_swap(__builtin_bit_cast(unsigned, a), __builtin_bit_cast(unsigned, b), false, false);
+  return __builtin_bit_cast(float, (unsigned)r[0]) + __builtin_bit_cast(float, (unsigned)r[1]);
+}
+__device__ __forceinline__ float swap_rows_and_add(float a, float b) {
+  const auto r = __builtin_amdgcn_permlane16_swap(__builtin_bit_cast(unsigned, a), __builtin_bit_cast(unsigned, b), false, false);
+  return __builtin_bit_cast(float, (unsigned)r[0]) + __builtin_bit_cast(float, (unsigned)r[1]);
+}
+
+template <int R, bool TERNARY, int NG, bool NUMBERS>
 struct Smem {
   // 13-bit field -> the A operand of its eight tokens (104976 bytes, built by the workgroup:
   // four base-3 digits -> the operand halves of tokens 0..3 / 4..7)
@@ -288,7 +335,7 @@ struct Smem {
   } wb[kNW];
   static_assert(sizeof(WaveBuf) % 16 == 0, "an array of them keeps the alignment");
   alignas(16) _Float16 qraw[4][kD];    // the query heads as loaded (rows >= R are zero)
-  _Float16 qa[32][4][4];               // A operands of the score product: [step][head][k slot]
+  QueryOperands<NUMBERS> query;
   alignas(16) float qpart[4][8];       // per head: sums of the reordered query over 16 positions each
   alignas(16) float qtotal[4];         // per head: the sum of the whole query (one group per head)
   // epilogue: per-wave running reference, sum of weights, sum of weight*zero, for the packed
@@ -537,7 +584,8 @@ __global__ __launch_bounds__(kThreads, 2) void decode_mfma_kernel(Layout L, cons
   constexpr float kCentre = 0.5f * (KL - 1);  // the key codes enter the products centred
   // score accumulators / weight operands: one per group, or (unequal groups) one per 16 positions
   constexpr int NACC = UNEQ ? 8 : NG;
-  __shared__ Smem<R, TERNARY, NG> sm;
+  constexpr bool NUMBERS = keys_as_numbers(KL, NG, UNEQ);
+  __shared__ Smem<R, TERNARY, NG, NUMBERS> sm;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int sp = blockIdx.x, by = blockIdx.y;
@@ -558,10 +606,14 @@ __global__ __launch_bounds__(kThreads, 2) void decode_mfma_kernel(Layout L, cons
     return ((unsigned)b * n_new + j) * L.Hq + hk * L.R + (x - j * L.R);
   };
   __half2 q2 = __floats2half2_rn(0.f, 0.f);
-  if (tid < 64 * R && head0 + (tid >> 6) < n_rows)
-    q2 = reinterpret_cast<const __half2 *>(q + (size_t)row_index(head0 + (tid >> 6)) * kD)[lane];
-  // (staging: wavefront w < 4 places head w's query at the positions lane and 64 + lane)
-  const int pk0 = L.perm_k[hk * kD + lane], pk1 = L.perm_k[hk * kD + 64 + lane];
+  // (NUMBERS, one group: wavefront 4 + w adds up head w's query, while wavefront w places it)
+  const int q_row = NUMBERS && NG == 1 ? wave & 3 : wave;
+  if (q_row < R && head0 + q_row < n_rows) q2 = reinterpret_cast<const __half2 *>(q + (size_t)row_index(head0 + q_row) * kD)[lane];
+  // (staging: wavefront w < 4 places head w's query at the positions lane and 64 + lane; NUMBERS: at the places 2 lane and
+  // 2 lane + 1 of the operand, where a dword's even codes come first, then its odd ones)
+  const int place = (K4 ? 7 : 15) & (2 * lane);
+  const int pos = !NUMBERS ? lane : 2 * lane - place + (K4 ? 2 * (place & 3) + (place >> 2) : 2 * (place & 7) + (place >> 3));
+  const int pk0 = L.perm_k[hk * kD + pos], pk1 = L.perm_k[hk * kD + pos + (NUMBERS ? 2 : 64)];
   const int pv_ch = L.perm_v[hk * kD + (tid & 127)];  // for the epilogue: channel of position tid%128
 
   // ---- the new token taken along (knew != null; one query token, passes == 1, and the token
@@ -623,6 +675,9 @@ __global__ __launch_bounds__(kThreads, 2) void decode_mfma_kernel(Layout L, cons
   // (a tile index past the workgroup's share is redirected to tile_cap, the share's last tile, or tile
   // 0 of an empty cache, by the callers: one scalar minimum per load)
   const int tile_cap = max(min(tile_end - 1, safe_last_tile), 0);
+  // NUMBERS: a lane takes quarter lane / 16 of the rows of tokens lane % 16 + 0, 16, 32, 48 (tokens past the last one: the
+  // last quarter of its row)
+  const unsigned piece_off = (K4 ? 64u : 32u) * (lane & 15) + (K4 ? 16u : 8u) * (lane >> 4);
   auto load_tile = [&](const int tile) {
     Tile d;
     // every address is a wave-uniform base (the tile's first row, its two V blocks) plus a 32-bit lane
@@ -632,9 +687,24 @@ __global__ __launch_bounds__(kThreads, 2) void decode_mfma_kernel(Layout L, cons
     const unsigned row = min((unsigned)lane, (unsigned)rows_here);
     const uint8_t *kt = kc + (size_t)tile * (64 * kRowBytes);
     const uint8_t *krow = kt + row * (unsigned)kRowBytes;
-    d.k0 = stream_load<kStreamK>(reinterpret_cast<const uint4_t *>(krow));
-    d.k1 = stream_load<kStreamK>(reinterpret_cast<const uint4_t *>(krow + 16));
-    if constexpr (K4) {
+    if constexpr (NUMBERS && K4) {
+      const unsigned off_last = (unsigned)rows_here * 64u + 48u;
+      d.k0 = stream_load<kStreamK>(reinterpret_cast<const uint4_t *>(kt + min(piece_off, off_last)));
+      d.k1 = stream_load<kStreamK>(reinterpret_cast<const uint4_t *>(kt + min(piece_off + 1024u, off_last)));
+      d.k2 = stream_load<kStreamK>(reinterpret_cast<const uint4_t *>(kt + min(piece_off + 2048u, off_last)));
+      d.k3 = stream_load<kStreamK>(reinterpret_cast<const uint4_t *>(kt + min(piece_off + 3072u, off_last)));
+    } else if constexpr (NUMBERS) {
+      uint2_t piece[4];
+#pragma unroll
+      for (int x = 0; x < 4; ++x)
+        piece[x] = load_as<kStreamK>(reinterpret_cast<const uint2_t *>(kt + min(piece_off + 512u * x, (unsigned)rows_here * 32u + 24u)));
+      d.k0 = uint4_t{piece[0].x, piece[0].y, piece[1].x, piece[1].y};
+      d.k1 = uint4_t{piece[2].x, piece[2].y, piece[3].x, piece[3].y};
+    } else {
+      d.k0 = stream_load<kStreamK>(reinterpret_cast<const uint4_t *>(krow));
+      d.k1 = stream_load<kStreamK>(reinterpret_cast<const uint4_t *>(krow + 16));
+    }
+    if constexpr (K4 && !NUMBERS) {
       d.k2 = stream_load<kStreamK>(reinterpret_cast<const uint4_t *>(krow + 32));
       d.k3 = stream_load<kStreamK>(reinterpret_cast<const uint4_t *>(krow + 48));
     }
@@ -747,44 +817,121 @@ __global__ __launch_bounds__(kThreads, 2) void decode_mfma_kernel(Layout L, cons
     // fp16 slices later), reads it back through the permutation (its own writes: no barrier, the
     // LDS serves a wavefront's operations in order) and writes the head's matrix operands and piece
     // sums.  One barrier then covers the operands, the sums and the table.
-    if (tid < 256) {
+    if (tid < (NUMBERS && R < 4 ? 64 * R : 256)) {  // (NUMBERS: nobody reads what a head past R would give)
       reinterpret_cast<__half2 *>(sm.qraw[wave])[lane] = q2;
       __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
       __builtin_amdgcn_wave_barrier();
       __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-      float both = 0.f;  // the lane's two positions
+      [[maybe_unused]] float both = 0.f;  // the lane's two positions
+      if constexpr (NUMBERS) {
+        const float x0 = (float)sm.qraw[wave][pk0], x1 = (float)sm.qraw[wave][pk1];
+        // (its largest value from the channels as loaded, while those two come back; as the bits of a number without a sign)
+        const float y0 = __low2float(q2), y1 = __high2float(q2);
+        unsigned top = max(__builtin_bit_cast(unsigned, fabsf(y0)), __builtin_bit_cast(unsigned, fabsf(y1)));
+        top = max(top, move_bits<kQuadSwap1, 0xf>(top));
+        top = max(top, move_bits<kQuadSwap2, 0xf>(top));
+        top = max(top, move_bits<kRowHalfMirror, 0xf>(top));
+        top = max(top, move_bits<kRowMirror, 0xf>(top));
+        top = max(top, move_bits<0x142, 0xa>(top));  // (the broadcasts of wave_max)
+        top = max(top, move_bits<0x143, 0xc>(top));
+        // below 2^(e - 126); a head of zeros counts as one of 2^-26, less than fp16 holds
+        const int e = max(__builtin_amdgcn_readlane((int)top, 63) >> 23, 100);
+        constexpr int kTop = K4 ? 1 : 3;  // the largest is brought below 2^kTop
+        const int exponent = kTop + 126 - e;
+        sm.query.exponent[wave] = exponent;  // (by every lane)
+        float r0 = ldexpf(x0, exponent), r1 = ldexpf(x1, exponent);
+        constexpr float kStep = 1 << kPartBits;
 #pragma unroll
-      for (int j = 0; j < 2; ++j) {
-        const int row = wave, p = lane + 64 * j;
-        int step, kslot, shift;
-        if (K4)
-          k4_slot_of(p, step, kslot, shift);
-        else
-          k_slot_of(p, step, kslot, shift);
-        const float x = (float)sm.qraw[row][j ? pk1 : pk0];
-        sm.qa[step][row][kslot] = (_Float16)ldexpf(x, 8 - shift);  // exact: a power of two
-        both += x;
-        if constexpr (UNEQ || NG > 1) {
-          // sum of the reordered query over the 16 positions of this row of lanes
-          float s16 = x;
+        for (int part = 0; part < kQueryParts; ++part) {
+          const int two = __builtin_amdgcn_cvt_pk_fp8_f32(r0, r1, 0, false);
+          *reinterpret_cast<uint16_t *>(&sm.query.q8[4 * part + wave][2 * lane]) = (uint16_t)two;
+          r0 = fmaf(__builtin_amdgcn_cvt_f32_fp8(two, 0), -kStep, kStep * r0);  // exact
+          r1 = fmaf(__builtin_amdgcn_cvt_f32_fp8(two, 1), -kStep, kStep * r1);
+        }
+        if constexpr (NG > 1) {
+          // sums of the reordered query over 16 positions: eight lanes
+          float s16 = x0 + x1;
           s16 += row_move<kQuadSwap1>(s16);
           s16 += row_move<kQuadSwap2>(s16);
           s16 += row_move<kRowHalfMirror>(s16);
-          s16 += row_move<kRowMirror>(s16);
-          if ((lane & 15) == 0) sm.qpart[row][p >> 4] = s16;
+          if ((lane & 7) == 0) sm.qpart[wave][lane >> 3] = s16;
+        }
+      } else {
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+          const int row = wave, p = lane + 64 * j;
+          int step, kslot, shift;
+          if (K4)
+            k4_slot_of(p, step, kslot, shift);
+          else
+            k_slot_of(p, step, kslot, shift);
+          const float x = (float)sm.qraw[row][j ? pk1 : pk0];
+          sm.query.qa[step][row][kslot] = (_Float16)ldexpf(x, 8 - shift);  // exact: a power of two
+          both += x;
+          if constexpr (UNEQ || NG > 1) {
+            // sum of the reordered query over the 16 positions of this row of lanes
+            float s16 = x;
+            s16 += row_move<kQuadSwap1>(s16);
+            s16 += row_move<kQuadSwap2>(s16);
+            s16 += row_move<kRowHalfMirror>(s16);
+            s16 += row_move<kRowMirror>(s16);
+            if ((lane & 15) == 0) sm.qpart[row][p >> 4] = s16;
+          }
         }
       }
-      if constexpr (!UNEQ && NG == 1) {
+      if constexpr (!UNEQ && NG == 1 && !NUMBERS) {
         // one group per head: the head's whole sum, formed here once instead of by every wavefront
         both = wave_sum_in_last_lane(both);
         if (lane == 63) sm.qtotal[wave] = both;
       }
     }
+    if constexpr (NUMBERS && NG == 1) {
+      if (wave >= 4 && q_row < R) {
+        const float sum = wave_sum_in_last_lane(__low2float(q2) + __high2float(q2));
+        if (lane == 63) sm.qtotal[q_row] = sum;
+      }
+    }
     __syncthreads();
   }
   // lane l supplies row l%4 (= head) of step l/4 (first register pair) and 16 + l/4 (second)
-  const half4_t qop_lo = *reinterpret_cast<const half4_t *>(sm.qa[lane >> 2][lane & 3]);
-  const half4_t qop_hi = *reinterpret_cast<const half4_t *>(sm.qa[16 + (lane >> 2)][lane & 3]);
+  half4_t qop_lo = {}, qop_hi = {};
+  // (NUMBERS) lane l supplies row l % 16 and its scale: of the FP8 operand channels 16 (l / 16) .. + 15 of either half, where
+  // the FP4 operand has channels 32 (l / 16) .. + 31; against an FP8 one 32 in a row do
+  int_x8_t qop8 = {}, qop8_low = {};
+  int qscale = 0;
+  constexpr int kUnitScale = 127 + (K4 ? 9 : 1);  // a code enters as code / 512 or code / 2
+  if constexpr (NUMBERS && NG == 2) {
+    const int group = (lane >> 3) & 1, part = (lane >> 2) & 1;
+    const uint8_t *row = sm.query.q8[4 * part + (lane & 3)];
+    if constexpr (K4) {
+      const bool mine = group == lane >> 5;
+      const int_x8_t high = *reinterpret_cast<const int_x8_t *>(row + 32 * (lane >> 4));
+      const int_x8_t low = *reinterpret_cast<const int_x8_t *>(row + 8 * kD + 32 * (lane >> 4));
+#pragma unroll
+      for (int i = 0; i < 8; ++i) qop8[i] = mine ? high[i] : 0, qop8_low[i] = mine ? low[i] : 0;
+    } else {
+      const uint8_t *piece = row + 64 * group + 16 * (lane >> 4);
+      const uint4_t high = *reinterpret_cast<const uint4_t *>(piece), low = *reinterpret_cast<const uint4_t *>(piece + 8 * kD);
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        qop8[i] = group ? 0 : (int)high[i], qop8[4 + i] = group ? (int)high[i] : 0;
+        qop8_low[i] = group ? 0 : (int)low[i], qop8_low[4 + i] = group ? (int)low[i] : 0;
+      }
+    }
+    qscale = kUnitScale - kPartBits * part - sm.query.exponent[lane & 3];
+    qscale |= (qscale - 2 * kPartBits) << 8;  // the second byte: of parts 2 and 3
+  } else if constexpr (NUMBERS && K4) {
+    qop8 = *reinterpret_cast<const int_x8_t *>(&sm.query.q8[lane & 15][32 * (lane >> 4)]);
+    qscale = kUnitScale - kPartBits * ((lane >> 2) & 3) - sm.query.exponent[lane & 3];
+  } else if constexpr (NUMBERS) {
+    const uint8_t *row = &sm.query.q8[lane & 15][16 * (lane >> 4)];
+    const uint4_t lo4 = *reinterpret_cast<const uint4_t *>(row), hi4 = *reinterpret_cast<const uint4_t *>(row + 64);
+    qop8 = int_x8_t{(int)lo4.x, (int)lo4.y, (int)lo4.z, (int)lo4.w, (int)hi4.x, (int)hi4.y, (int)hi4.z, (int)hi4.w};
+    qscale = kUnitScale - kPartBits * ((lane >> 2) & 3) - sm.query.exponent[lane & 3];
+  } else {
+    qop_lo = *reinterpret_cast<const half4_t *>(sm.query.qa[lane >> 2][lane & 3]);
+    qop_hi = *reinterpret_cast<const half4_t *>(sm.query.qa[16 + (lane >> 2)][lane & 3]);
+  }
   // Per group: sm_scale*log2(e) * sum of the reordered query (qsc), and the start value of the
   // score accumulators, -centre*sum(q) in the product's units (2^-16), centre = 1.5 (2-bit) or 7.5
   // (4-bit): the products then sum q*(c - centre), centred codes, which keeps both halves of
@@ -806,7 +953,7 @@ __global__ __launch_bounds__(kThreads, 2) void decode_mfma_kernel(Layout L, cons
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
       if (r < R) qsc[r][0] = c * tot[r];
-      dinit[0][r] = -kCentre * tot[r] * (1.0f / 65536.0f);
+      dinit[0][r] = NUMBERS ? -kCentre * tot[r] : -kCentre * tot[r] * (1.0f / 65536.0f);
     }
   } else if constexpr (UNEQ) {
     // (a piece's accumulator sums only 16 products: it starts from zero, uncentred)
@@ -829,8 +976,18 @@ __global__ __launch_bounds__(kThreads, 2) void decode_mfma_kernel(Layout L, cons
 #pragma unroll
         for (int x = 0; x < 8 / NG; ++x) sum += qp[r][g * (8 / NG) + x];
         if (r < R) qsc[r][g] = c * sum;
-        dinit[g][r] = -kCentre * sum * (1.0f / 65536.0f);
+        dinit[g][r] = NUMBERS ? -kCentre * sum : -kCentre * sum * (1.0f / 65536.0f);
       }
+  }
+
+  // (NUMBERS) the start values enter with the small part that is added to the large one first
+  float4_t code_start = {0.f, 0.f, 0.f, 0.f};
+  if constexpr (NUMBERS) {
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      if constexpr (NG == 2) code_start[r] = lane & 16 ? 0.f : lane & 32 ? dinit[NG - 1][r] : dinit[0][r];
+      else code_start[r] = (lane >> 4) == 2 ? dinit[0][r] : 0.f;
+    }
   }
 
   // ---- ring slices of this wave (wave-local) ----
@@ -1029,7 +1186,7 @@ __global__ __launch_bounds__(kThreads, 2) void decode_mfma_kernel(Layout L, cons
     float4_t dg[NACC];
 #pragma unroll
     for (int g = 0; g < NACC; ++g) dg[g] = UNEQ ? float4_t{0.f, 0.f, 0.f, 0.f} : dinit[g];
-    if constexpr (K4) {
+    if constexpr (K4 && !NUMBERS) {
 #define SKVQ_QK4(Q, C, DW) dg[(DW) * NACC / 16] = qk_dword4<DW>(cur.k##Q.C, qop_lo, qop_hi, dg[(DW) * NACC / 16])
       SKVQ_QK4(0, x, 0);  SKVQ_QK4(0, y, 1);  SKVQ_QK4(0, z, 2);  SKVQ_QK4(0, w, 3);
       SKVQ_QK4(1, x, 4);  SKVQ_QK4(1, y, 5);  SKVQ_QK4(1, z, 6);  SKVQ_QK4(1, w, 7);
@@ -1045,6 +1202,40 @@ __global__ __launch_bounds__(kThreads, 2) void decode_mfma_kernel(Layout L, cons
       dg[5 * NACC / 8] = qk_dword3<5>(cur.k1.y, cur.k2.z, qop_lo, qop_hi, dg[5 * NACC / 8]);
       dg[6 * NACC / 8] = qk_dword3<6>(cur.k1.z, cur.k2.w, qop_lo, qop_hi, dg[6 * NACC / 8]);
       dg[7 * NACC / 8] = qk_dword3<7>(cur.k1.w, cur.k2.w, qop_lo, qop_hi, dg[7 * NACC / 8]);
+    } else if constexpr (NUMBERS) {
+      // four products; lane l has the scores of token 16 x + l % 16 against part l / 16 of the four heads.  Two
+      // exchanges of lanes leave lane l with the sum of the parts for token l.
+      float4_t d[4];
+#pragma unroll
+      for (int x = 0; x < 4; ++x) {
+        int_x8_t codes;
+        constexpr int kFormat = K4 ? 0 : 4;  // FP8 E4M3, FP4 E2M1
+        if constexpr (K4) {
+          const uint4_t w = x == 0 ? cur.k0 : x == 1 ? cur.k1 : x == 2 ? cur.k2 : cur.k3;
+#pragma unroll
+          for (int i = 0; i < 4; ++i) codes[2 * i] = w[i] & 0x0f0f0f0fu, codes[2 * i + 1] = (w[i] >> 4) & 0x0f0f0f0fu;
+        } else {
+          const uint4_t two = x < 2 ? cur.k0 : cur.k1;
+          const unsigned w0 = two[2 * (x & 1)], w1 = two[2 * (x & 1) + 1];
+          constexpr unsigned kCodes = 0x33333333u;
+          codes = int_x8_t{(int)(w0 & kCodes), (int)((w0 >> 2) & kCodes), (int)(w1 & kCodes), (int)((w1 >> 2) & kCodes), 0, 0, 0, 0};
+        }
+        d[x] = code_start;
+        if constexpr (NG == 2) d[x] = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(qop8_low, codes, d[x], 0, kFormat, 1, qscale, 0, 127);
+        d[x] = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(qop8, codes, d[x], 0, kFormat, 0, qscale, 0, 127);
+      }
+#pragma unroll
+      for (int r = 0; r < R; ++r) {
+        if constexpr (NG == 2) {
+          // (lane row 2 group + part % 2: the parts by an exchange of rows, then each group's tokens by one of halves)
+          const auto both = __builtin_amdgcn_permlane32_swap(__builtin_bit_cast(unsigned, swap_rows_and_add(d[0][r], d[1][r])),
+                                                             __builtin_bit_cast(unsigned, swap_rows_and_add(d[2][r], d[3][r])), false, false);
+          dg[0][r] = __builtin_bit_cast(float, (unsigned)both[0]);
+          dg[1][r] = __builtin_bit_cast(float, (unsigned)both[1]);
+        } else {
+          dg[0][r] = swap_rows_and_add(swap_halves_and_add(d[0][r], d[2][r]), swap_halves_and_add(d[1][r], d[3][r]));
+        }
+      }
     } else {
       dg[0 * NACC / 8] = qk_dword<0>(cur.k0.x, qop_lo, qop_hi, dg[0 * NACC / 8]);
       dg[1 * NACC / 8] = qk_dword<1>(cur.k0.y, qop_lo, qop_hi, dg[1 * NACC / 8]);
@@ -1081,7 +1272,7 @@ __global__ __launch_bounds__(kThreads, 2) void decode_mfma_kernel(Layout L, cons
 #pragma unroll
       for (int g = 0; g < NG; ++g) {
         const float2 kmeta = meta_value(cur.kmeta.m[g]);
-        const float a_t = kmeta.x * (c * 65536.0f);       // codes carry 2^(s-24), the query 2^(8-s)
+        const float a_t = kmeta.x * (NUMBERS ? c : c * 65536.0f);  // (else codes carry 2^(s-24), the query 2^(8-s))
         const float zc = fmaf(kCentre, kmeta.x, kmeta.y);  // dequantized value of the centre code
 #pragma unroll
         for (int r = 0; r < R; ++r) u[r] = fmaf(dg[g][r], a_t, fmaf(zc, qsc[r][g], u[r]));

@@ -66,3 +66,33 @@ def test_weights_of_every_row_and_group_count(P, hq, hk, group, bounds, packed):
     pair.prefill(k, v)
     out, ref = pair.decode_both(q)
     assert np.abs(out - ref).max() <= P.TOL
+
+
+@pytest.mark.parametrize("hq,hk", [(1, 1), (4, 2), (3, 1), (4, 1)])
+@pytest.mark.parametrize("k_bits,group,v_bits,meta", [(2.0, 128, 1.5, "f32"), (2.0, 64, 2.0, "e4m3"), (4.0, 128, 4.0, "f32"),
+                                                      (4.0, 64, 1.5, "e4m3")])
+@pytest.mark.parametrize("packed", [1, 15, 16, 17, 48, 63, 64, 65, 130])
+def test_keys_against_queries_in_parts(P, hq, hk, k_bits, group, v_bits, meta, packed):
+    # 2- and 4-bit keys of one and two groups meet the query as four FP8 numbers per channel, sixteen tokens a product
+    w = synth.Workload("parts", 1, hq, hk, 8 + packed, v_bits, group_size=group, window=8, seed=5 + packed, k_bits=k_bits)
+    pair, k, v, q = P.make_pair(w, meta=meta)
+    pair.prefill(k, v)
+    rng = np.random.default_rng(packed)
+    k_top, v_top = np.abs(k.astype(np.float64)).max(), np.abs(v.astype(np.float64)).max()
+    one = np.zeros_like(q)
+    one[..., packed % 128] = -1.75
+    for kind, x in {"normal": q, "wide": q * 10.0 ** rng.uniform(-6, 0.5, q.shape), "one channel": one, "zero": 0 * one,
+                    "subnormal": q * 1e-6, "large": q * 30}.items():
+        x = x.astype(np.float16)
+        out, ref = pair.decode_both(x)
+        # a score of 128 products summed in 32 bits, of a query that its parts miss by 2^-25 of its largest channel at most;
+        # values by weights of 22 bits, summed with codes that start six bits below the accumulator's first
+        a = np.abs(x.astype(np.float64))
+        score = 1.45 / np.sqrt(128.0) * k_top * (136 * 2.0 ** -24 * a.sum(-1).max() + 128 * 2.0 ** -25 * a.max())
+        assert np.abs(out - ref).max() <= 2 * (score + 2.0 ** -18) * v_top, kind
+    # an infinite channel spoils its own head only
+    x = q.copy()
+    x[0, -1, 3] = np.inf
+    out = pair.gpu.skvq_decode_attention(torch.from_numpy(x).to(pair.device)).cpu().numpy()
+    assert np.isnan(out[0, -1]).all()
+    assert np.abs(out[0, :-1] - pair.ref.decode(q)[0, :-1]).max(initial=0) <= P.TOL
