@@ -67,9 +67,10 @@ typedef uint2_t uint2_a4_t __attribute__((aligned(4)));
 // streaming (STREAM): the data then need not displace what the caches hold for longer (the query,
 // the permutations, the partials).  That pays where one load instruction takes all that a
 // wavefront wants of a cache line soon (32-byte key rows, 13- and 16-byte V units: 4-7 % at long
-// contexts); where a row or unit is fetched by several instructions in turn (48- and 64-byte key
-// rows, 24- and 32-byte V units) the later ones would miss, and the kernel is 20 % slower: those
-// formats load plainly.
+// contexts; 64-byte key rows whose quarters are the pieces of one instruction, see keys_as_numbers: 1175 -> 1140 us for
+// 48 steps of 8 x 8 kv heads x 6007 tokens with their prompts); where a row or unit is fetched by several instructions in
+// turn (48-byte and the other 64-byte key rows, 24- and 32-byte V units) the later ones would miss, and the kernel is 20 %
+// slower: those formats load plainly.
 template <bool STREAM, class T>
 __device__ __forceinline__ T load_as(const T *p) {
   if constexpr (STREAM) return __builtin_nontemporal_load(p); else return *p;
@@ -671,7 +672,7 @@ __global__ __launch_bounds__(kThreads, 2) void decode_mfma_kernel(Layout L, cons
   const int safe_last_token = last_token > 0 ? last_token : 0;
   const int safe_last_blk = last_blk > 0 ? last_blk : 0;
   // which of the streams are marked as streaming loads (see load_as)
-  constexpr bool kStreamK = KL == 4, kStreamV = VL == 3 || VL == 4;
+  constexpr bool kStreamK = KL == 4 || NUMBERS, kStreamV = VL == 3 || VL == 4;
   // (a tile index past the workgroup's share is redirected to tile_cap, the share's last tile, or tile
   // 0 of an empty cache, by the callers: one scalar minimum per load)
   const int tile_cap = max(min(tile_end - 1, safe_last_tile), 0);
