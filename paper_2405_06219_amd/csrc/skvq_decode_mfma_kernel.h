@@ -303,12 +303,15 @@ typedef int int_x8_t __attribute__((ext_vector_type(8)));
 constexpr int kQueryParts = 4, kPartBits = 5;
 template <bool NUMBERS>
 struct QueryOperands {
-  _Float16 qa[32][4][4];               // A operands of the score product: [step][head][k slot]
+  typedef _Float16 type[32][4][4];  // [step][head][k slot]
+};
+struct QueryParts {
+  alignas(32) uint8_t q8[4 * kQueryParts][kD];  // [4 part + head][k]
+  int exponent[4];                              // per head: its query was multiplied by 2^exponent
 };
 template <>
 struct QueryOperands<true> {
-  alignas(32) uint8_t q8[4 * kQueryParts][kD];  // [4 part + head][k]
-  int exponent[4];                              // per head: its query was multiplied by 2^exponent
+  typedef QueryParts type;
 };
 // Lanes 32-63 of a trade places with lanes 0-31 of b (odd rows of sixteen lanes of a with even rows of b); the sum of the two.
 __device__ __forceinline__ float swap_halves_and_add(float a, float b) {
@@ -320,7 +323,7 @@ __device__ __forceinline__ float swap_rows_and_add(float a, float b) {
   return __builtin_bit_cast(float, (unsigned)r[0]) + __builtin_bit_cast(float, (unsigned)r[1]);
 }
 
-template <int R, bool TERNARY, int NG, bool NUMBERS>
+template <int R, bool TERNARY, int NG, bool NUMBERS = false>
 struct Smem {
   // 13-bit field -> the A operand of its eight tokens (104976 bytes, built by the workgroup:
   // four base-3 digits -> the operand halves of tokens 0..3 / 4..7)
@@ -336,7 +339,7 @@ struct Smem {
   } wb[kNW];
   static_assert(sizeof(WaveBuf) % 16 == 0, "an array of them keeps the alignment");
   alignas(16) _Float16 qraw[4][kD];    // the query heads as loaded (rows >= R are zero)
-  QueryOperands<NUMBERS> query;
+  typename QueryOperands<NUMBERS>::type qa;  // A operands of the score product
   alignas(16) float qpart[4][8];       // per head: sums of the reordered query over 16 positions each
   alignas(16) float qtotal[4];         // per head: the sum of the whole query (one group per head)
   // epilogue: per-wave running reference, sum of weights, sum of weight*zero, for the packed
@@ -839,13 +842,13 @@ __global__ __launch_bounds__(kThreads, 2) void decode_mfma_kernel(Layout L, cons
         const int e = max(__builtin_amdgcn_readlane((int)top, 63) >> 23, 100);
         constexpr int kTop = K4 ? 1 : 3;  // the largest is brought below 2^kTop
         const int exponent = kTop + 126 - e;
-        sm.query.exponent[wave] = exponent;  // (by every lane)
+        sm.qa.exponent[wave] = exponent;  // (by every lane)
         float r0 = ldexpf(x0, exponent), r1 = ldexpf(x1, exponent);
         constexpr float kStep = 1 << kPartBits;
 #pragma unroll
         for (int part = 0; part < kQueryParts; ++part) {
           const int two = __builtin_amdgcn_cvt_pk_fp8_f32(r0, r1, 0, false);
-          *reinterpret_cast<uint16_t *>(&sm.query.q8[4 * part + wave][2 * lane]) = (uint16_t)two;
+          *reinterpret_cast<uint16_t *>(&sm.qa.q8[4 * part + wave][2 * lane]) = (uint16_t)two;
           r0 = fmaf(__builtin_amdgcn_cvt_f32_fp8(two, 0), -kStep, kStep * r0);  // exact
           r1 = fmaf(__builtin_amdgcn_cvt_f32_fp8(two, 1), -kStep, kStep * r1);
         }
@@ -867,7 +870,7 @@ __global__ __launch_bounds__(kThreads, 2) void decode_mfma_kernel(Layout L, cons
           else
             k_slot_of(p, step, kslot, shift);
           const float x = (float)sm.qraw[row][j ? pk1 : pk0];
-          sm.query.qa[step][row][kslot] = (_Float16)ldexpf(x, 8 - shift);  // exact: a power of two
+          sm.qa[step][row][kslot] = (_Float16)ldexpf(x, 8 - shift);  // exact: a power of two
           both += x;
           if constexpr (UNEQ || NG > 1) {
             // sum of the reordered query over the 16 positions of this row of lanes
@@ -903,7 +906,7 @@ __global__ __launch_bounds__(kThreads, 2) void decode_mfma_kernel(Layout L, cons
   constexpr int kUnitScale = 127 + (K4 ? 9 : 1);  // a code enters as code / 512 or code / 2
   if constexpr (NUMBERS && NG == 2) {
     const int group = (lane >> 3) & 1, part = (lane >> 2) & 1;
-    const uint8_t *row = sm.query.q8[4 * part + (lane & 3)];
+    const uint8_t *row = sm.qa.q8[4 * part + (lane & 3)];
     if constexpr (K4) {
       const bool mine = group == lane >> 5;
       const int_x8_t high = *reinterpret_cast<const int_x8_t *>(row + 32 * (lane >> 4));
@@ -919,19 +922,19 @@ __global__ __launch_bounds__(kThreads, 2) void decode_mfma_kernel(Layout L, cons
         qop8_low[i] = group ? 0 : (int)low[i], qop8_low[4 + i] = group ? (int)low[i] : 0;
       }
     }
-    qscale = kUnitScale - kPartBits * part - sm.query.exponent[lane & 3];
+    qscale = kUnitScale - kPartBits * part - sm.qa.exponent[lane & 3];
     qscale |= (qscale - 2 * kPartBits) << 8;  // the second byte: of parts 2 and 3
   } else if constexpr (NUMBERS && K4) {
-    qop8 = *reinterpret_cast<const int_x8_t *>(&sm.query.q8[lane & 15][32 * (lane >> 4)]);
-    qscale = kUnitScale - kPartBits * ((lane >> 2) & 3) - sm.query.exponent[lane & 3];
+    qop8 = *reinterpret_cast<const int_x8_t *>(&sm.qa.q8[lane & 15][32 * (lane >> 4)]);
+    qscale = kUnitScale - kPartBits * ((lane >> 2) & 3) - sm.qa.exponent[lane & 3];
   } else if constexpr (NUMBERS) {
-    const uint8_t *row = &sm.query.q8[lane & 15][16 * (lane >> 4)];
+    const uint8_t *row = &sm.qa.q8[lane & 15][16 * (lane >> 4)];
     const uint4_t lo4 = *reinterpret_cast<const uint4_t *>(row), hi4 = *reinterpret_cast<const uint4_t *>(row + 64);
     qop8 = int_x8_t{(int)lo4.x, (int)lo4.y, (int)lo4.z, (int)lo4.w, (int)hi4.x, (int)hi4.y, (int)hi4.z, (int)hi4.w};
-    qscale = kUnitScale - kPartBits * ((lane >> 2) & 3) - sm.query.exponent[lane & 3];
+    qscale = kUnitScale - kPartBits * ((lane >> 2) & 3) - sm.qa.exponent[lane & 3];
   } else {
-    qop_lo = *reinterpret_cast<const half4_t *>(sm.query.qa[lane >> 2][lane & 3]);
-    qop_hi = *reinterpret_cast<const half4_t *>(sm.query.qa[16 + (lane >> 2)][lane & 3]);
+    qop_lo = *reinterpret_cast<const half4_t *>(sm.qa[lane >> 2][lane & 3]);
+    qop_hi = *reinterpret_cast<const half4_t *>(sm.qa[16 + (lane >> 2)][lane & 3]);
   }
   // Per group: sm_scale*log2(e) * sum of the reordered query (qsc), and the start value of the
   // score accumulators, -centre*sum(q) in the product's units (2^-16), centre = 1.5 (2-bit) or 7.5
