@@ -48,6 +48,7 @@
 
 #include "skvq_internal.h"
 #include "skvq_append_device.h"
+#include "skvq_key_pieces.h"
 
 namespace skvq {
 namespace {
@@ -679,29 +680,26 @@ __global__ __launch_bounds__(kThreads, 2) void decode_mfma_kernel(Layout L, cons
   // (a tile index past the workgroup's share is redirected to tile_cap, the share's last tile, or tile
   // 0 of an empty cache, by the callers: one scalar minimum per load)
   const int tile_cap = max(min(tile_end - 1, safe_last_tile), 0);
-  // NUMBERS: a lane takes quarter lane / 16 of the rows of tokens lane % 16 + 0, 16, 32, 48 (tokens past the last one: the
-  // last quarter of its row)
-  const unsigned piece_off = (K4 ? 64u : 32u) * (lane & 15) + (K4 ? 16u : 8u) * (lane >> 4);
   auto load_tile = [&](const int tile) {
     Tile d;
     // every address is a wave-uniform base (the tile's first row, its two V blocks) plus a 32-bit lane
     // offset: the bases are scalar arithmetic, the offsets cost one vector instruction per stream
     // (lanes past the last token -- only in the last tile, masked below -- repeat its row)
-    const int rows_here = safe_last_token - tile * 64;  // >= 0
-    const unsigned row = min((unsigned)lane, (unsigned)rows_here);
+    const unsigned rows_after = rows_after_first(safe_last_token, tile);
+    const unsigned row = min((unsigned)lane, rows_after);
     const uint8_t *kt = kc + (size_t)tile * (64 * kRowBytes);
     const uint8_t *krow = kt + row * (unsigned)kRowBytes;
+    // (NUMBERS: a lane takes a quarter of four rows, see key_piece_offset)
+    [[maybe_unused]] auto piece_at = [&](unsigned x) { return kt + key_piece_offset<kRowBytes>(lane, x, rows_after); };
     if constexpr (NUMBERS && K4) {
-      const unsigned off_last = (unsigned)rows_here * 64u + 48u;
-      d.k0 = stream_load<kStreamK>(reinterpret_cast<const uint4_t *>(kt + min(piece_off, off_last)));
-      d.k1 = stream_load<kStreamK>(reinterpret_cast<const uint4_t *>(kt + min(piece_off + 1024u, off_last)));
-      d.k2 = stream_load<kStreamK>(reinterpret_cast<const uint4_t *>(kt + min(piece_off + 2048u, off_last)));
-      d.k3 = stream_load<kStreamK>(reinterpret_cast<const uint4_t *>(kt + min(piece_off + 3072u, off_last)));
+      d.k0 = stream_load<kStreamK>(reinterpret_cast<const uint4_t *>(piece_at(0)));
+      d.k1 = stream_load<kStreamK>(reinterpret_cast<const uint4_t *>(piece_at(1)));
+      d.k2 = stream_load<kStreamK>(reinterpret_cast<const uint4_t *>(piece_at(2)));
+      d.k3 = stream_load<kStreamK>(reinterpret_cast<const uint4_t *>(piece_at(3)));
     } else if constexpr (NUMBERS) {
       uint2_t piece[4];
 #pragma unroll
-      for (int x = 0; x < 4; ++x)
-        piece[x] = load_as<kStreamK>(reinterpret_cast<const uint2_t *>(kt + min(piece_off + 512u * x, (unsigned)rows_here * 32u + 24u)));
+      for (int x = 0; x < 4; ++x) piece[x] = load_as<kStreamK>(reinterpret_cast<const uint2_t *>(piece_at(x)));
       d.k0 = uint4_t{piece[0].x, piece[0].y, piece[1].x, piece[1].y};
       d.k1 = uint4_t{piece[2].x, piece[2].y, piece[3].x, piece[3].y};
     } else {

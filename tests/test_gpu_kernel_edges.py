@@ -384,3 +384,26 @@ def test_merge_at_its_edges(hq, hk, group, splits):
     assert np.abs(outs[1] - outs[0]).max() <= 1e-5 * max(1.0, np.abs(ref).max())
     names = decode_kernels(lambda: pair.gpu.skvq_decode_attention(qd))
     assert ("merge_kernel" in names) == (hq // hk > 4 or splits > 8), names
+
+
+# caches so long that the distance from a tile to the last packed token, in bytes of key rows, is past 32 bits: the first
+# tile's 64 tokens have keys of a prompt, all others a score that makes their weight exactly zero
+@pytest.mark.parametrize("k_bits,group,packed", [(4.0, 128, 2 ** 26 + 6), (4.0, 64, 2 ** 26 + 6), (2.0, 128, 2 ** 27 + 6),
+                                                 (2.0, 64, 2 ** 27 + 6)])
+def test_caches_past_four_gigabytes_of_keys(k_bits, group, packed):
+    from paper_2405_06219_amd import synth
+    print("case", k_bits, group, packed, flush=True)
+    w = synth.Workload("long", 1, 4, 1, 8 + 64, 1.5, group_size=group, window=8, seed=31, k_bits=k_bits)
+    pair, k, v, _ = P.make_pair(w, meta="e4m3")
+    pair.prefill(k, v)
+    q = np.random.default_rng(31).uniform(0.5, 1.5, (1, 4, 128)).astype(np.float16)
+    ref = pair.ref.decode(q)
+    gpu = type(pair.gpu)(1, 4, 1, group, 1.5, 8, packed, *pair.gpu._keep[:4], k_bits=k_bits, meta="e4m3", fill=0)
+    gpu.buffers["k_meta"][1::2] = 0xD8  # zeros of -16, scales of 0: scores below -150, the prompt has some above 0
+    for name, buffer in pair.gpu.buffers.items():  # the prompt's 64 packed tokens and its window
+        if name != "workspace":
+            gpu.buffers[name][:buffer.numel()] = buffer
+    gpu.skvq_set_state(packed + 8)
+    out = gpu.skvq_decode_attention(torch.from_numpy(q).to("cuda:0"))
+    torch.cuda.synchronize()
+    assert np.abs(out.cpu().numpy() - ref).max() <= P.TOL
