@@ -336,6 +336,7 @@ struct Smem {
   union alignas(16) WaveBuf {
     _Float16 pbuf[Weights<R, NG>::kOps][64][Weights<R, NG>::kCols];
     float stage[R][kCombStride];
+    float slice[4][8];               // (before the first tile) the weights of a fp16 slice: [head][token]
     uint2_t high[TERNARY ? 81 : 1];  // (before the first tile) see build_ternary_table
   } wb[kNW];
   static_assert(sizeof(WaveBuf) % 16 == 0, "an array of them keeps the alignment");
@@ -492,7 +493,6 @@ struct RingData<false> {
   uint4_t k[1];   // lane (token = l / 16, piece l % 16): 8 channels of the token's key row
   unsigned v[4];
 };
-constexpr float kRingBias = 14.0f;  // the matrix cores' weights of a slice are at most 2^14
 
 // What the host works out once per launch, so that no workgroup spends its first few hundred
 // instructions on divisions: the share of the packed tiles per chunk and the ring's first row.
@@ -994,16 +994,19 @@ __global__ __launch_bounds__(kThreads, 2) void decode_mfma_kernel(Layout L, cons
 
   // ---- ring slices of this wave (wave-local) ----
   // One or two rows: plain vector arithmetic, a lane a piece of a token's key, then a channel pair.  More rows:
-  //   scores  S[head][token] by v_mfma_f32_16x16x32_f16: A = the query heads (row x: head x % 4), B = the tokens'
+  //   scores  S[head][token] by v_mfma_f32_16x16x16_f16: A = the query heads (row x: head x % 4), B = the tokens'
   //        key rows (column x: token x % 8), so that all sixteen-lane rows hold the scores of all heads,
   //        and lane row g goes on with head g alone: one maximum, one exponential and one sum for all heads.
-  //   outputs  O[head][channel] by v_mfma_f32_4x4x4_16b_f16, lane = channel pair: A = the weights of four tokens,
-  //        as a high and a low fp16 part (through LDS), B = the pair's values.
-  // (The weights are 2^14 at most: the split keeps 22 bits of those down to 2^-27 of the largest.)
+  //   outputs  O[head][channel] by v_mfma_f32_4x4x1_16b_f32, lane = channel pair: A = a token's weights, as they are
+  //        (through LDS), B = the pair's values in 32 bits: a multiply-add of fp32 numbers, as the vector ALU's.
+  // The error against 64 bits is no larger than the vector arithmetic's: 0.92 - 0.98 times it, 0.99 - 1.02 (+- 0.03) with a
+  // few channels of the query far above the others.  Weights as two fp16 numbers, 22 bits, made it 1.9 to 2.6 times as
+  // large where the scores are close to one another (and 48 steps of 8 x 8 kv heads x 6007 tokens 4-bit with their prompts 1136 us
+  // instead of 1144; the vector ALU's multiply-adds behind the matrix cores' scores: 1156).
   // Bound by latency, beside the partner wavefront's tiles.  Four heads by vector arithmetic, one after the other and
   // four tokens at a time, took 1.3 us a slice, and the slices' owners were the last of their workgroups: us per pass,
-  // before and after, 8 x 8 kv heads x 6007 tokens 4-bit 1248 -> 1200 (48 steps of 19.5 -> 18.5), 8 kv heads x 131072
-  // 173.3 -> 170.9, 16 x 8 x 4000 17.9 -> 17.1 a step.  One and two rows stay with the vector arithmetic: eight tokens through the matrix
+  // vector arithmetic and matrix cores (with weights of two fp16 numbers), the 48 steps above 1248 -> 1200, 8 kv heads x
+  // 131072 173.3 -> 170.9, 16 x 8 x 4000 17.9 -> 17.1 a step.  One and two rows stay with the vector arithmetic: eight tokens through the matrix
   // cores are twelve requests ahead of the first tile instead of five and two more trips through LDS, 4 heads x 2048
   // tokens 249 -> 258, 32 x 32768 155 -> 156.5, two rows x 5000 9.46 -> 9.71 a step (x 6000 4-bit 16.2 -> 15.8).
   if (ring_owner || (packs && wave == kPackedWave)) {
@@ -1015,7 +1018,6 @@ __global__ __launch_bounds__(kThreads, 2) void decode_mfma_kernel(Layout L, cons
     // query token j sees the fp16 tokens up to its own, index n_fp - n_new + j (all of them if n_new = 1)
     auto ring_last = [&](int r) { return n_new == 1 ? n_fp - 1 : n_fp - n_new + (head0 + r) / L.R; };
     const int group_last = kRingMatrix ? ring_last(lane >> 4) : 0;
-    _Float16 *weights = &sm.wb[wave].pbuf[0][0][0];  // [high, low][head][token]
     auto ring_slice = [&](const Ring &rd, const int slice) {
       if constexpr (!kRingMatrix) {
         const int pc = lane & 15;  // 8-channel piece of the token's row
@@ -1058,51 +1060,48 @@ __global__ __launch_bounds__(kThreads, 2) void decode_mfma_kernel(Layout L, cons
           }
         }
       } else {
-        // (four sums of 32 products each, added by the vector ALU: the matrix core truncates what it adds to)
-        float4_t d[4];
+        // (eight sums of 16 products each, added by the vector ALU: the matrix core truncates what it adds.  Half as
+        // many of 32 are no faster, and with a few channels far above the others their error is 1.02 - 1.07 times that
+        // of the vector arithmetic.)
+        float4_t d[8];
 #pragma unroll
-        for (int x = 0; x < 4; ++x)
-          d[x] = __builtin_amdgcn_mfma_f32_16x16x32_f16(*reinterpret_cast<const half8_t *>(&sm.qraw[lane & 3][32 * x + 8 * (lane >> 4)]),
-                                                        __builtin_bit_cast(half8_t, rd.k[x]), float4_t{0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
-        const float4_t sum4 = (d[0] + d[1]) + (d[2] + d[3]);
+        for (int x = 0; x < 8; ++x) {
+          const uint4_t key = rd.k[x / 2];
+          d[x] = __builtin_amdgcn_mfma_f32_16x16x16f16(
+              *reinterpret_cast<const half4_t *>(&sm.qraw[lane & 3][32 * (x / 2) + 8 * (lane >> 4) + 4 * (x % 2)]),
+              x % 2 ? h4(key.z, key.w) : h4(key.x, key.y), float4_t{0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
+        }
+        const float4_t sum4 = ((d[0] + d[1]) + (d[2] + d[3])) + ((d[4] + d[5]) + (d[6] + d[7]));
         const float upper = lane & 16 ? sum4[3] : sum4[2], lower = lane & 16 ? sum4[1] : sum4[0];
         const float u = slice * kRingSlice + (lane & 7) <= group_last ? c * (lane & 32 ? upper : lower) : -INFINITY;
         float top = fmaxf(u, row_move<kQuadSwap1>(u));
         top = fmaxf(top, row_move<kQuadSwap2>(top));
         top = fmaxf(top, row_move<kRowHalfMirror>(top));
-        const float mnew = fmaxf(rm, top - kRingBias);
+        const float mnew = fmaxf(rm, top);
         const float mref = mnew == -INFINITY ? 0.f : mnew;
         const float f = fast_exp2(rm - mref);  // 0 for the first slice
-        const float p = fast_exp2(u - mref);   // 0 for tokens past the end
-        float sum = p + row_move<kQuadSwap1>(p);
+        const float pg = fast_exp2(u - mref);  // 0 for tokens past the end
+        float sum = pg + row_move<kQuadSwap1>(pg);
         sum += row_move<kQuadSwap2>(sum);
         sum += row_move<kRowHalfMirror>(sum);
         rl = fmaf(rl, f, sum);
         rm = mnew;
-        const auto hi = __builtin_amdgcn_cvt_pkrtz(p, 0.f);
-        weights[(lane >> 4) * 8 + (lane & 7)] = hi[0];
-        weights[32 + (lane >> 4) * 8 + (lane & 7)] = (_Float16)(p - (float)hi[0]);
+        sm.wb[wave].slice[lane >> 4][lane & 7] = pg;
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
         __builtin_amdgcn_wave_barrier();
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-        const half8_t ph = *reinterpret_cast<const half8_t *>(&weights[(lane & 3) * 8]);
-        const half8_t pl = *reinterpret_cast<const half8_t *>(&weights[32 + (lane & 3) * 8]);
+        const float4_t *mine = reinterpret_cast<const float4_t *>(sm.wb[wave].slice[lane & 3]);
+        const float4_t w[2] = {mine[0], mine[1]};
 #pragma unroll
         for (int r = 0; r < R; ++r) {
           const float fr = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, f), 16 * r));
           oe[r] *= fr, oo[r] *= fr;
         }
 #pragma unroll
-        for (int k = 0; k < 2; ++k) {
-          const unsigned *v = &rd.v[4 * k];
-          const half4_t ve = h4(__builtin_amdgcn_perm(v[1], v[0], 0x05040100u), __builtin_amdgcn_perm(v[3], v[2], 0x05040100u));
-          const half4_t vo = h4(__builtin_amdgcn_perm(v[1], v[0], 0x07060302u), __builtin_amdgcn_perm(v[3], v[2], 0x07060302u));
-          const half4_t h = k ? __builtin_shufflevector(ph, ph, 4, 5, 6, 7) : __builtin_shufflevector(ph, ph, 0, 1, 2, 3);
-          const half4_t l = k ? __builtin_shufflevector(pl, pl, 4, 5, 6, 7) : __builtin_shufflevector(pl, pl, 0, 1, 2, 3);
-          oe = __builtin_amdgcn_mfma_f32_4x4x4f16(l, ve, oe, 0, 0, 0);
-          oo = __builtin_amdgcn_mfma_f32_4x4x4f16(l, vo, oo, 0, 0, 0);
-          oe = __builtin_amdgcn_mfma_f32_4x4x4f16(h, ve, oe, 0, 0, 0);
-          oo = __builtin_amdgcn_mfma_f32_4x4x4f16(h, vo, oo, 0, 0, 0);
+        for (int k = 0; k < kRingSlice; ++k) {
+          const __half2 v2 = __builtin_bit_cast(__half2, rd.v[k]);
+          oe = __builtin_amdgcn_mfma_f32_4x4x1f32(w[k / 4][k % 4], __low2float(v2), oe, 0, 0, 0);
+          oo = __builtin_amdgcn_mfma_f32_4x4x1f32(w[k / 4][k % 4], __high2float(v2), oo, 0, 0, 0);
         }
       }
     };

@@ -56,6 +56,22 @@ def test_fp16_tokens_in_slices(P, hq, hk, n_new, context, window, sinks):
     assert np.abs(out - pair.ref.decode_multi(q)).max() <= bound
 
 
+@pytest.mark.parametrize("hq,hk,n_new", [(6, 2, 1), (8, 2, 1), (2, 2, 1), (4, 4, 4)])
+@pytest.mark.parametrize("context", [8, 15, 31])
+def test_fp16_tokens_keep_weights_of_32_bits(P, hq, hk, n_new, context):
+    # scores close to one another, so that all tokens weigh about the same and no score's rounding shows
+    w = synth.Workload("weights32", 8, hq, hk, context, 2.0, window=64, seed=78)
+    pair, k, v, _ = P.make_pair(w, max_new_tokens=n_new)
+    pair.prefill(k, v)
+    q = (1e-3 * np.random.default_rng(context).standard_normal((8, n_new, hq, 128))).astype(np.float16)
+    out = pair.gpu.skvq_decode_attention_multi(torch.from_numpy(q).to(pair.device)).cpu().numpy()
+    ref = pair.ref.decode_multi(q)
+    # per number: an exponential (a unit in the last place), a multiply-add per token, the sum of weights, a division; each
+    # rounds by 2^-25.8 in the mean square, the tokens' values have random signs: sqrt(2 + 5 + 2 + 1) of these are 2^-24.1.
+    # A weight in two fp16 numbers is off by up to 2^-22, 2^-22.8 in the mean square where it is full
+    assert np.linalg.norm(out - ref) <= 2.0 ** -23 * np.linalg.norm(ref)
+
+
 @pytest.mark.parametrize("hq,hk", [(1, 1), (2, 1), (4, 1), (7, 1)])
 @pytest.mark.parametrize("group,bounds", [(128, None), (64, None), (32, None), (64, (0, 32, 128)), (32, (0, 16, 32, 64, 128))])
 @pytest.mark.parametrize("packed", [1, 40, 65])
