@@ -646,6 +646,10 @@ def main() -> int:
     kernel_name = (f"decode_mfma_kernel<R={min(w.n_q_heads // w.n_kv_heads, 4)}, K levels {int(2 ** w.k_bits)}, "
                    f"V levels {3 if w.v_bits == 1.5 else int(2 ** w.v_bits)}, meta {args.meta}, "
                    f"{D // w.group_size} group(s)> + merge_kernel")
+    # (keys of 2 and 4 bits in one or two equal groups are numbers of the matrix cores' own, the query four of them per channel)
+    as_numbers = w.k_bits in (2.0, 4.0) and w.group_size >= 64 and not bounds
+    dtype = f"f16 query as 4 FP8 numbers x {'FP4' if w.k_bits == 2.0 else 'FP8'} key codes, " if as_numbers else ""
+    dtype += "f16 MFMA operands, f32 accumulate"
     result = {
         "metric": "decode-attention us/token at 128k ctx" if w.context == 131072 else f"decode-attention us/token at {w.context} ctx",
         "value": ms_per_step * 1e3,
@@ -657,7 +661,7 @@ def main() -> int:
         "higher_is_better": False,
         "scaling": "weak",
         "vs_baseline": None,
-        "dtype": "f16 MFMA operands, f32 accumulate",
+        "dtype": dtype,
         "data": "synthetic",
         "config": {"workload": w.name, "layers": n_layers, "batch": w.batch, "n_q_heads": w.n_q_heads,
                    "n_kv_heads": w.n_kv_heads, "head_dim": D, "context": w.context, "k_bits": w.k_bits,

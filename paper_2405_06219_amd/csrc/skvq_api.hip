@@ -173,7 +173,10 @@ int choose_splits(const skvq_cache *c, long long n_quant, long long n_fp, int n_
 
 // What a call of more than four rows takes, in ns, with n_splits chunks: the waves of workgroups that the
 // compute units need, each with a start-up, the wavefronts' slices of four fp16 tokens (`teams` of a
-// workgroup's wavefronts share them) and the workgroup's tiles, and the merge launch.
+// workgroup's wavefronts share them) and the workgroup's tiles, and the merge launch.  Fitted to a four-row
+// kernel that took its fp16 tokens four at a time by vector arithmetic and all keys as fp16 numbers: it takes
+// eight at a time now, and calls with 2- and 4-bit keys of one and two groups are 2 - 13 % shorter at long contexts, so
+// the sixteen-row kernel may be chosen somewhat early.
 long long decode_cost(const skvq_cache *c, const DecodePlan &p, long long n_quant, long long n_fp, int teams, int tile_ns) {
   const long long s = p.n_splits > 1 ? p.n_splits : 1, workgroups = (long long)c->L.B * c->L.Hk * p.passes * s;
   const long long waves = (workgroups + c->n_cus - 1) / c->n_cus;
@@ -202,7 +205,8 @@ bool step_is_one_launch(const skvq_cache *c, const DecodePlan &p) {
 // it spills).  The wide kernel pays where the compute units have no room for the other workgroups and the
 // chunks are long: the costs of both are compared, with constants fitted to 4000 calls of every format, 5 ..
 // 64 rows, 1 .. 256 kv heads over the batch, 300 .. 1000000 tokens, windows of 8 .. 1000 tokens (chosen against
-// the faster: 0.1 % longer on average, 10 % at most).  Narrow and wide, us per call: 8 q / 1 kv x 1000
+// the faster: 0.1 % longer on average, 10 % at most, with the four-row kernel of that time: see decode_cost).
+// Narrow and wide, us per call: 8 q / 1 kv x 1000
 // tokens 12.9 / 26.3, x 16000 13.1 / 14.3; 32 q / 8 kv, four query tokens, x 4000 15.9 / 21.0, x 16000 16.1 /
 // 16.0, x 40000 23.0 / 17.1; 8 x 64 q / 8 kv x 4000 19.0 / 21.3, x 16000 35.6 / 29.0; 3-bit in two groups, two
 // query tokens, x 64000 27.7 / 41.9.

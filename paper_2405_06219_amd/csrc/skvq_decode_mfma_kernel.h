@@ -257,7 +257,7 @@ constexpr int kDealPeriod = (kNW / 2) * (kOldShare + kYoungShare);  // tiles per
 // 131072 tokens 22.05, 21.98, 21.74, 21.54; 100003 tokens in two groups 20.84, 20.50, 20.13, 20.17; eight rows (the
 // sixteen-row kernel, where all wavefronts wait for the append) 100000 tokens in two groups 29.96, 28.80, 28.67, 28.55;
 // 32 heads x 32768 tokens 19.63, 19.68, 19.59, 19.82 (runs differ by 0.2).
-constexpr int kAppendLagTiles = 12;
+constexpr int kAppendLagTiles = 12;  // (measured before keys went through the matrix cores as numbers)
 constexpr int kPackedWave = 2;       // the wavefront (late in line for ring slices) that takes the token packed in the same call
 constexpr int kRingWaves = kNW;     // every wavefront of a workgroup may own ring slices
 
@@ -290,8 +290,12 @@ struct Weights {
 // of those before it times 2^kPartBits; the block scales take that back.  The head's largest channel is brought to 8 (2
 // for 4-bit codes): the product adds exactly as long as the largest and the smallest bit of its 128 terms are no more than
 // 2^14.6 apart (values below 16 against halves of codes: no error in 4000 sums; below 32: 6 in 2^-10), and E4M3's smallest
-// step, 2^-9, keeps a part within that.  What the four parts miss is 2^-27 (2^-25) of the largest channel at most; fp16
-// queries are exact down to 2^-14 (2^-12) of it.
+// step, 2^-9, keeps a part within that.  fp16 channels are exact down to 2^-16 (2^-14) of the largest one; of smaller ones
+// the four parts miss 2^-27 (2^-25) of it at most, where queries as fp16 operands were whole but their sums cut off at 2^-23
+// of themselves, step by step.  Against 64 bits the outputs' error, geometric means over 24 to 80 caches per format, is
+// 0.16 - 0.67 times that of fp16 operands with a few channels far above the others, 0.54 - 0.98 with channels over decades,
+// 0.66 - 0.99 (+- 0.02) with large scores, 0.95 - 1.00 with normal and small ones, 4-bit keys at the upper ends; single calls
+// go either way.
 //   Two groups: rows 8 group + 4 (part % 2) + head, zero in the other group's channels, and two products in a chain.
 //   Bound: the tiles' vector and matrix instructions.  us per pass, before and after: eight calls of 32 heads x 32768 tokens
 // 161.8 -> 153.8, 8 kv heads x 131072, four rows, 173.0 -> 167.8, 100003 tokens in two groups 159.3 -> 149.4, 11 x 8 kv heads x 118865
@@ -340,7 +344,7 @@ struct Smem {
     uint2_t high[TERNARY ? 81 : 1];  // (before the first tile) see build_ternary_table
   } wb[kNW];
   static_assert(sizeof(WaveBuf) % 16 == 0, "an array of them keeps the alignment");
-  alignas(16) _Float16 qraw[4][kD];    // the query heads as loaded (rows >= R are zero)
+  alignas(16) _Float16 qraw[4][kD];    // the query heads as loaded (rows >= R: zero, or not written with NUMBERS; nobody reads them)
   typename QueryOperands<NUMBERS>::type qa;  // A operands of the score product
   alignas(16) float qpart[4][8];       // per head: sums of the reordered query over 16 positions each
   alignas(16) float qtotal[4];         // per head: the sum of the whole query (one group per head)
@@ -736,8 +740,8 @@ __global__ __launch_bounds__(kThreads, 2) void decode_mfma_kernel(Layout L, cons
     return d;
   };
 
-  // ---- the fp16 ring: slices of 4 tokens, slice j belongs to workgroup j % n_splits and to
-  //      the wave whose rank is (j / n_splits) % kRingWaves ----
+  // ---- the fp16 ring: slices of four tokens (eight with three and four rows), slice j belongs to workgroup
+  //      j % n_splits and to the wave whose rank is (j / n_splits) % kRingWaves ----
   // The fp16 tokens in token order: the n_sink sink rows (rows W.. of the ring buffers), then
   // the window's tokens.
   const int n_win = (int)(T - nq) - n_sink, W = L.W;
@@ -1006,9 +1010,10 @@ __global__ __launch_bounds__(kThreads, 2) void decode_mfma_kernel(Layout L, cons
   // Bound by latency, beside the partner wavefront's tiles.  Four heads by vector arithmetic, one after the other and
   // four tokens at a time, took 1.3 us a slice, and the slices' owners were the last of their workgroups: us per pass,
   // vector arithmetic and matrix cores (with weights of two fp16 numbers), the 48 steps above 1248 -> 1200, 8 kv heads x
-  // 131072 173.3 -> 170.9, 16 x 8 x 4000 17.9 -> 17.1 a step.  One and two rows stay with the vector arithmetic: eight tokens through the matrix
-  // cores are twelve requests ahead of the first tile instead of five and two more trips through LDS, 4 heads x 2048
-  // tokens 249 -> 258, 32 x 32768 155 -> 156.5, two rows x 5000 9.46 -> 9.71 a step (x 6000 4-bit 16.2 -> 15.8).
+  // 131072 173.3 -> 170.9, 16 x 8 x 4000 17.9 -> 17.1 a step.
+  // One and two rows stay with the vector arithmetic: eight tokens through the matrix cores are twelve requests ahead of
+  // the first tile instead of five and two more trips through LDS (with weights of two fp16 numbers), 4 heads x 2048 tokens
+  // 249 -> 258, 32 x 32768 155 -> 156.5, two rows x 5000 9.46 -> 9.71 a step (x 6000 4-bit 16.2 -> 15.8).
   if (ring_owner || (packs && wave == kPackedWave)) {
     float4_t oe = {0.f, 0.f, 0.f, 0.f}, oo = oe;  // outputs of channels 2l and 2l + 1, [head]
     float ml[R], sl[R];                           // per head, wave-uniform: reference and sum of weights
@@ -1183,7 +1188,7 @@ __global__ __launch_bounds__(kThreads, 2) void decode_mfma_kernel(Layout L, cons
   auto compute_tile = [&](const Tile &cur, const int tile) {
     const bool valid = tile * 64 + lane <= last_token;
 
-    // ---- scores: 32 products of 4 channels each, one accumulator per group ----
+    // ---- scores, one accumulator per group: 32 products of 4 channels each, or (NUMBERS) four or eight of 128 ----
     float4_t dg[NACC];
 #pragma unroll
     for (int g = 0; g < NACC; ++g) dg[g] = UNEQ ? float4_t{0.f, 0.f, 0.f, 0.f} : dinit[g];
@@ -1204,8 +1209,9 @@ __global__ __launch_bounds__(kThreads, 2) void decode_mfma_kernel(Layout L, cons
       dg[6 * NACC / 8] = qk_dword3<6>(cur.k1.z, cur.k2.w, qop_lo, qop_hi, dg[6 * NACC / 8]);
       dg[7 * NACC / 8] = qk_dword3<7>(cur.k1.w, cur.k2.w, qop_lo, qop_hi, dg[7 * NACC / 8]);
     } else if constexpr (NUMBERS) {
-      // four products; lane l has the scores of token 16 x + l % 16 against part l / 16 of the four heads.  Two
-      // exchanges of lanes leave lane l with the sum of the parts for token l.
+      // Sixteen tokens a product: one (two groups: two, in a chain).  Lane l then has the scores of token 16 x + l % 16
+      // against part l / 16 of the four heads (two groups: of group l / 32, parts l / 16 % 2 and that plus two).  Three
+      // exchanges of lanes per head leave lane l with the sums of the parts for token l.
       float4_t d[4];
 #pragma unroll
       for (int x = 0; x < 4; ++x) {

@@ -1,7 +1,10 @@
 // Matrix-core kernel of skvq_decode_attention for more than four rows per kv head (query heads of the
 // kv head x query tokens) over long caches: up to sixteen rows per workgroup.  The cache formats, the
-// operands made of codes, the grid, the shares, the fp16 slices and the partials are those of
-// skvq_decode_mfma_kernel.h; what differs is the shape of the products:
+// fp16 operands made of codes, the grid, the workgroups' shares and the partials are those of
+// skvq_decode_mfma_kernel.h.  The later deals of tiles go to the older wavefronts first here too, where that
+// kernel takes turns; all fp16 slices are of four tokens and plain vector arithmetic, two teams of wavefronts
+// for them; no keys go through the matrix cores as FP4 or FP8 numbers.  (None of these three has been measured
+// here.)  The products have another shape:
 //
 //   QK   S[token][row] by v_mfma_f32_16x16x32_f16: A = sixteen key rows, B = the rows' reordered
 //        queries (sixteen columns, held in registers).  Lane (m = lane % 16, h = lane / 16) feeds a
